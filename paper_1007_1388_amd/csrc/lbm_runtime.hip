@@ -318,9 +318,37 @@ void order_items_by_xcd(lbm_ctx* c) {
       if (k < q[x].size()) c->items_h.push_back(q[x][k]);
 }
 
+// Cells per work item of this sweep: the schedule's item_cells, whose default
+// 512 gives each wave of a 4-wave workgroup two 64-cell tasks, halved or
+// doubled by what bounds the sweep (measured on gfx950, default schedule, us
+// per step; results do not depend on it).
+//  * FP64, and FP32 without obstacles that does not write its Blocks' x faces
+//    itself: half, one task per wave.  These are bound by memory, and a
+//    second task's loads wait behind the first one's stores: 256^3 channel
+//    FP32 474 -> 454, FP64 951 -> 942, 200^3 FP32 250 -> 238, 128^3 FP64
+//    124 -> 117, one-Block open duct 100 -> 95.  With obstacles, or sending x
+//    faces, FP32 keeps two tasks (128^3 porous 65.7 against 66.8, porous
+//    512x256x256 in 250 Blocks 1102 against 1146: more of a task is set-up).
+//  * Fewer than three items per compute unit: half, whatever the variant, to
+//    occupy the chip: 32^3 FP64 cavity 12.8 -> 8.7, 64^3 FP32 in 8 Blocks
+//    22.9 -> 21.3 (64x64x128 porous, four per unit, 18.7 against 19.1).
+//  * 16-bit storage with at least six items per compute unit left: double,
+//    four tasks per wave.  The dispatcher starts about 240 workgroups per us,
+//    which half-size values outrun: 256^3 cavity FP16S 273 -> 263, 128^3 38.7
+//    -> 36.9, 256^3 in 8 Blocks 358 -> 318 (64^3, one per unit, 19.4
+//    against 23.8).
+int item_target(const lbm_ctx* c) {
+  const int t = std::max(1, c->sched.item_cells);
+  if (c->sched.persistent > 0) return t;  // workgroups loop over the items anyway
+  const long long items = c->n_cells / t, cus = c->cu_count;
+  if (c->prec >= 2) return items >= 12 * cus ? 2 * t : t;
+  const bool streams = c->prec == 0 || (!c->has_mask && c->sched.fused_exchange != 2);
+  return streams || items < 3 * cus ? std::max(1, t / 2) : t;
+}
+
 void build_items(lbm_ctx* c) {
   c->items_h.clear();
-  const int target = std::max(1, c->sched.item_cells);
+  const int target = item_target(c);
   const int vec = cells_per_lane(c, c->sched), nw = std::max(1, c->sched.wg_size / 64);
   for (int j = 0; j < (int)c->bh.size(); ++j) {
     const BlockDev& B = c->bh[j];
@@ -1388,6 +1416,7 @@ lbm_status lbm_set_geometry(lbm_ctx* c, const uint8_t* solid) {
                                 "included) must stay below 4 GiB (about 89 M cells in FP64, 178 M in FP32, "
                                 "357 M in 16-bit storage)");
   drop_graphs(c);
+  const bool had_mask = c->has_mask;
   if (any) {
     if (!c->d_mask) {
       long long moff = 0;
@@ -1412,6 +1441,12 @@ lbm_status lbm_set_geometry(lbm_ctx* c, const uint8_t* solid) {
     HIPCHK(hipGetLastError());
   } else {
     c->has_mask = false;
+  }
+  if (c->has_mask != had_mask) {  // the items' size depends on obstacles
+    HIPCHK(hipStreamSynchronize(c->stream));
+    build_items(c);
+    lbm_status si = upload_items(c);
+    if (si != LBM_OK) return si;
   }
   c->n_fluid = c->n_cells - nsolid;
   lbm_status s = zero_grids(c);
