@@ -187,6 +187,40 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, unsigne
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)bytes, 0x00020000);
 }
 
+// Epilogue of eight consecutive channels of a voxel (lo: the first four):
+// bias, ReLU, ReLU' mask, accumulation, rounding, one 16-byte store (channel
+// counts are multiples of 8).
+__device__ __forceinline__ void store8(const DArgs& a, long long vo, int col, f32x4 lo, f32x4 hi) {
+  float v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = k < 4 ? lo[k] : hi[k - 4];
+  auto half = [](const u32x4& m, int k) { return bf2f((uint16_t)(m[k >> 1] >> (16 * (k & 1)))); };
+  if (a.bias) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] += a.bias[col + k];
+  }
+  if (a.relu) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = v[k] > 0.f ? v[k] : 0.f;
+  }
+  if (a.act) {
+    const u32x4 m = *(const u32x4*)(a.act + vo * a.act_ldc + col);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (!(half(m, k) > 0.f)) v[k] = 0.f;
+  }
+  uint16_t* o = a.out + vo * a.go.ldc + col;
+  if (a.accumulate) {
+    const u32x4 p = *(const u32x4*)o;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] += half(p, k);
+  }
+  u32x4 q;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) q[k] = (unsigned)f2bf(v[2 * k]) | (unsigned)f2bf(v[2 * k + 1]) << 16;
+  *(u32x4*)o = q;
+}
+
 template <int MODE, bool CLS, int FM, int FN>
 __global__ void __launch_bounds__(256) k_conv_tap(DArgs a) {
   constexpr int BN = 16 * FN, WM = 16 * FM, BMW = 4 * WM;
@@ -480,164 +514,167 @@ __global__ void __launch_bounds__(256) k_conv_wgrad(const uint16_t* __restrict__
     }
 }
 
-// ------------------------------------ fwd / bwd-data, stride 1, 3x3x3 halos
-// The stride-1 3x3x3 products with 32 or 64 output columns (the
-// full-resolution layers), where every gathered A element feeds only two or
-// four MFMAs and the tap-major kernel runs at the L1/L2 gather rate.  A
-// workgroup owns an 8 x 32 block of output voxels (rows h0.., columns w0..
-// of one plane) and all output columns; per kernel plane kd and 32-channel
-// chunk it stages in LDS
-//   * the input halo  [10 rows][34 columns][32 channels] of source plane
-//     d + kd - 1 (forward) or d + 1 - kd (input gradient), and
-//   * the weights     [9 taps][columns][32 channels] of that plane and chunk,
-// then runs the nine (kh, kw) taps on them: both MFMA operands are 16-byte
-// LDS reads with channels as K, so each input value is fetched from memory
-// once per (kd, chunk) instead of nine times.  The next stage's loads go to
-// registers while the taps run and reach LDS after the next barrier.  Wave v owns output rows
-// h0 + 2v and h0 + 2v + 1 (four 16-voxel fragments).  MODE 1 reads the taps
-// mirrored (source i + 1 - k) with the transposed weights.
-template <int MODE, int FN>
-__global__ void __launch_bounds__(256) k_conv_halo(DArgs a) {
-  constexpr int BN = 16 * FN;
-  constexpr int HR = 10, HC = 34, PC = 40;  // halo rows, columns, cell pitch (bf16)
-  constexpr int PW = 40;                    // weight row pitch (bf16)
-  constexpr int NX = HR * HC * 4;           // halo chunks of 8 channels
-  constexpr int NW = 9 * BN * 4;            // weight chunks
+// ------------------------------ fwd / bwd-data, stride 1, 3x3x3, row tiles
+typedef __attribute__((address_space(3))) void lds_void;
+
+// 16 bytes per lane from a buffer straight into LDS: lane l's bytes land at
+// dst + 16 l (dst uniform), an offset past the range stores zeros.
+__device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rs, uint16_t* dst, unsigned voff, unsigned soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, (int)voff, (int)soff, 0, 0);
+}
+
+// The stride-1 3x3x3 products.  A workgroup owns a TH x 16 tile of output
+// voxels (rows h0.., columns w0.. of one plane) and 32 output channels; per
+// source plane and 32-channel chunk it brings the input halo (TH + 2) x 18 x 32
+// and the nine taps' weights into LDS by 16-byte buffer loads that write LDS
+// directly (no staging registers, no ds_write), then multiplies.  Wave v owns R
+// rows of 16 voxels.  What the tile is built around is LDS reads per MFMA:
+//  * an operand of 16 voxels of halo row r serves the taps kh = 0, 1, 2 of
+//    output rows r, r - 1 and r - 2 from registers, and the nine taps' weights
+//    stay in registers for the whole stage: 3 (R + 2) voxel and 18 weight
+//    reads for 18 R MFMAs (36 for 72 with R = 4; reading both operands tap by
+//    tap takes 54);
+//  * 39 KB of LDS and 122 VGPRs (R = 4) keep four workgroups per compute unit,
+//    so one's loads run under the others' MFMAs and a stage needs no second
+//    buffer (three workgroups, without the register limit: 258 against 237 us
+//    on the first layer below).  Tiles of 8 rows per wave or 64 channels read
+//    LDS less, leave two workgroups and measured slower.
+// Every output sums its products in the order (plane kd, 32-channel chunk, kh,
+// kw), so a layer's result does not depend on the tile.
+// The weights are the MFMA's row operand, its row m of fragment j standing for
+// channel 8 (m / 4) + 4 j + m % 4: a lane then ends with eight consecutive
+// channels of one voxel, one 16-byte store (two 8-byte stores: forward 4 %,
+// input gradient with its mask 7 % slower).  LDS cells are 64 bytes, unpadded
+// as the direct loads want them; the 16-byte chunks of a cell are permuted by
+// its column (by the channel / 8 for weights) so that the 8 lanes of a read
+// cycle meet 8 different bank groups.
+// MODE 1 (input gradient) runs the mirrored taps on the transposed weights.
+// Channels in 8s: the part of a chunk past C loads zeros (TAIL).
+// Measured on gfx950, forward / input gradient, against the kernels this
+// replaced (batch 8): 128x64x64 32->32 346 / 465 -> 237 / 256 us, 64->32 540 /
+// 1033 -> 417 / 489; 64x32x32 128->64 238 / 378 -> 187 / 222 (1240 TFLOP/s; a
+// large library matrix product reaches 1280-1380 here); input gradients of
+// 32x16x16 256->128 157 -> 95 and of 16x8x8 256->256 90 -> 52 (half of each
+// tile is padding).  The full-resolution layers are held by HBM (0.54 GB
+// forward, 0.8 with the mask) beside the MFMAs, the rest by the matrix cores.
+template <int MODE, int R, bool TAIL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_conv_rows(DArgs a) {
+  constexpr int FN = 2, BN = 16 * FN;
+  constexpr int TW = 16, TH = R * 4;            // output tile of the workgroup
+  constexpr int HC = TW + 2, HR = TH + 2;       // its halo
+  constexpr int CELLS = HR * HC;
+  constexpr int NXI = (CELLS * 4 + 63) / 64;    // wave-wide 16-byte loads of the halo
+  constexpr int NWI = 9 * BN * 4 / 64;          // ... of the weights
+  constexpr int SX = (NXI + 3) / 4, SW = (NWI + 3) / 4;
+  constexpr int TPI = 256 / (BN * 4);           // taps per round of weight loads
   constexpr unsigned OOB = 0x80000000u;
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[HR * HC * PC];
-  __shared__ __attribute__((aligned(16))) uint16_t Ws[9 * BN * PW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[NXI * 512];
+  __shared__ __attribute__((aligned(1024))) uint16_t Ws[NWI * 512];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const Geo gs = a.gs, go = a.go;
-  // output block of this workgroup
-  const int nwb = go.w / 32, nhb = (go.h + 7) / 8;
-  int bx = blockIdx.x;
-  const int wb = bx % nwb;
+  const int ncols = go.c, C = a.C;
+  // XCD-aware work index: neighbouring tiles and the column tiles of one
+  // voxel tile share an XCD's L2
+  const int total = (int)gridDim.x, id0 = (int)blockIdx.x, q8 = total / 8 * 8;
+  int bx = id0 < q8 ? (id0 % 8) * (total / 8) + id0 / 8 : id0;
+  const int nct = (ncols + BN - 1) / BN, nwb = (go.w + TW - 1) / TW, nhb = (go.h + TH - 1) / TH;
+  const int n0 = bx % nct * BN;
+  bx /= nct;
+  const int w0 = bx % nwb * TW;
   bx /= nwb;
-  const int hb = bx % nhb;
+  const int h0 = bx % nhb * TH;
   bx /= nhb;
   const int d = bx % go.d, n = bx / go.d;
-  const int h0 = hb * 8, w0 = wb * 32;
-  const int C = a.C;
-  const int ncols = go.c;
+
   const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.src, a.src_bytes);
   const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wk, a.wk_bytes);
-
-  f32x4 acc[4][FN];
-#pragma unroll
-  for (int f = 0; f < 4; ++f)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[f][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // Per-thread staging slots.  Halo slot i covers cell (r, c) and 8
-  // channels q; its offset within the source plane is fixed, the plane and
-  // the chunk change per stage.  Weight slot j covers one column's 8
-  // channels of one (kh, kw) tap.  A slot outside the tensor takes the
-  // offset 2^30 elements, which lands past the buffer's range (real offsets
-  // stay below 2^30 elements); a plane outside is sent there by the high bit.
-  constexpr int SX = (NX + 255) / 256, SW = (NW + 255) / 256;
-  constexpr int FAR = 1 << 30;
-  int xoff[SX];
+  // load slots: 16-byte chunk (id & 3) of a cell holds channels
+  // 8 (chunk ^ (column / 2 mod 4)) .. + 7 of the stage's 32
+  unsigned xoff[SX];
+  int xq[SX];
 #pragma unroll
   for (int i = 0; i < SX; ++i) {
-    const int id = tid + i * 256;
-    const int cell = id >> 2, q = id & 3;
-    const int r = cell / HC, c = cell - r * HC;
+    const int id = (i * 4 + wave) * 64 + lane;
+    const int cell = id >> 2, r = cell / HC, c = cell - r * HC;
+    const int q = (id & 3) ^ ((c >> 1) & 3);
     const int hs = h0 - 1 + r, ws = w0 - 1 + c;
-    const bool ok = id < NX && hs >= 0 && hs < gs.h && ws >= 0 && ws < gs.w;
-    xoff[i] = ok ? (hs * gs.w + ws) * gs.ldc + q * 8 : FAR;
+    const bool ok = cell < CELLS && hs >= 0 && hs < gs.h && ws >= 0 && ws < gs.w;
+    xq[i] = q;
+    xoff[i] = ok ? (unsigned)((hs * gs.w + ws) * gs.ldc + q * 8) * 2u : OOB;
   }
-  int woff[SW];
-#pragma unroll
-  for (int j = 0; j < SW; ++j) {
-    const int id = tid + j * 256;
-    const int t9 = id / (BN * 4), rem = id - t9 * (BN * 4);
-    const int col = rem >> 2, q = rem & 3;
-    woff[j] = id < NW && col < ncols ? col * a.kstride + t9 * C + q * 8 : FAR;
+  unsigned woff;
+  int wq;
+  {
+    const int rem = tid % (BN * 4), t = tid / (BN * 4);
+    const int col = rem >> 2;
+    wq = (rem & 3) ^ ((col >> 3) & 3);
+    woff = n0 + col < ncols ? (unsigned)((n0 + col) * a.kstride + t * C + wq * 8) * 2u : OOB;
   }
-  const int plane = gs.h * gs.w * gs.ldc;
-  u32x4 xr[SX], wr[SW];
-  // issue the loads of stage st = kd * (C / 32) + chunk into registers
-  auto fetch = [&](int st) {
-    const int cpk = C >> 5;
-    const int kd = st / cpk, c0 = (st - kd * cpk) * 32;
-    const int ds = MODE == 0 ? d + kd - 1 : d + 1 - kd;
-    const unsigned dpen = ds >= 0 && ds < gs.d ? 0u : OOB;
-    const int pb = (n * gs.d + ds) * plane + c0;
-#pragma unroll
-    for (int i = 0; i < SX; ++i)
-      xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)(pb + xoff[i]) * 2u | dpen, 0, 0);
-    const int wb_ = kd * 9 * C + c0;
-#pragma unroll
-    for (int j = 0; j < SW; ++j)
-      wr[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, (unsigned)(woff[j] + wb_) * 2u, 0, 0);
-  };
-  // LDS homes of the slots
-  auto xdst = [&](int i) {
-    const int id = tid + i * 256;
-    return (id >> 2) * PC + (id & 3) * 8;
-  };
-  auto wdst = [&](int j) {
-    const int id = tid + j * 256;
-    const int t9 = id / (BN * 4), rem = id - t9 * (BN * 4);
-    return (t9 * BN + (rem >> 2)) * PW + (rem & 3) * 8;
-  };
-
   const int L = lane & 15, g = lane >> 4;
-  const int nst = 3 * (C >> 5);
-  fetch(0);
-  for (int st = 0; st < nst; ++st) {
-    __syncthreads();  // the previous stage's readers are done
+  const int hr0 = wave * R;
+  // LDS bases of the operand reads: per column shift of the halo, and weights
+  const uint16_t* xb[3];
 #pragma unroll
-    for (int i = 0; i < SX; ++i)
-      if (tid + i * 256 < NX) *(u32x4*)(&Xs[xdst(i)]) = xr[i];
+  for (int ow = 0; ow < 3; ++ow)
+    xb[ow] = Xs + (hr0 * HC + L + ow) * 32 + ((g ^ (((L + ow) >> 1) & 3)) * 8);
+  const uint16_t* wb = Ws + ((L >> 2) * 8 + (L & 3)) * 32 + ((g ^ (L >> 2)) * 8);
+
+  f32x4 acc[R][FN];
 #pragma unroll
-    for (int j = 0; j < SW; ++j)
-      if (tid + j * 256 < NW) *(u32x4*)(&Ws[wdst(j)]) = wr[j];
-    __syncthreads();
-    if (st + 1 < nst) fetch(st + 1);  // in flight while the taps run
+  for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int kh = 0; kh < 3; ++kh)
+    for (int j = 0; j < FN; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const unsigned plane = (unsigned)(gs.h * gs.w * gs.ldc) * 2u;
+  for (int kd = 0; kd < 3; ++kd) {
+    const int ds = MODE == 0 ? d + kd - 1 : d + 1 - kd;
+    if (ds < 0 || ds >= gs.d) continue;  // the plane beyond the volume adds nothing
+    const unsigned sp = (unsigned)(n * gs.d + ds) * plane;
+    for (int c0 = 0; c0 < C; c0 += 32) {
+      __syncthreads();  // the previous stage's readers are done
 #pragma unroll
-      for (int kw = 0; kw < 3; ++kw) {
-        // source offset of the tap in the halo: forward + (kh, kw),
-        // input gradient + (2 - kh, 2 - kw)
-        const int oh = MODE == 0 ? kh : 2 - kh, ow = MODE == 0 ? kw : 2 - kw;
-        bf16x8 af[4];
+      for (int i = 0; i < SX; ++i)
+        if (i * 4 + wave < NXI)
+          lds_dma16(rs, Xs + (i * 4 + wave) * 512, !TAIL || c0 + xq[i] * 8 < C ? xoff[i] : OOB, sp + (unsigned)c0 * 2u);
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-          const int r = 2 * wave + (f >> 1), c = (f & 1) * 16 + L;
-          af[f] = *(const bf16x8*)(&Xs[((r + oh) * HC + c + ow) * PC + g * 8]);
+      for (int i = 0; i < SW; ++i)
+        if (i * 4 + wave < NWI)
+          lds_dma16(rw, Ws + (i * 4 + wave) * 512, !TAIL || c0 + wq * 8 < C ? woff : OOB,
+                    (unsigned)((kd * 9 + i * TPI) * C + c0) * 2u);
+      __syncthreads();  // (waits for the loads)
+      bf16x8 wf[9][FN];
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) wf[t][j] = *(const bf16x8*)(wb + (t * BN + j * 4) * 32);
+#pragma unroll
+      for (int r_ = 0; r_ < R + 2; ++r_) {
+        const int r = MODE == 0 ? r_ : R + 1 - r_;  // halo row
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) {
+          const bf16x8 xf = *(const bf16x8*)(xb[MODE == 0 ? kw : 2 - kw] + r * HC * 32);
+#pragma unroll
+          for (int kh = 0; kh < 3; ++kh) {
+            const int ro = MODE == 0 ? r - kh : r - 2 + kh;  // output row that tap (kh, kw) takes this one to
+            if (ro < 0 || ro >= R) continue;
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+              acc[ro][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[kh * 3 + kw][j], xf, acc[ro][j], 0, 0, 0);
+          }
         }
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const bf16x8 bfr = *(const bf16x8*)(&Ws[((kh * 3 + kw) * BN + j * 16 + L) * PW + g * 8]);
-#pragma unroll
-          for (int f = 0; f < 4; ++f) acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[f], bfr, acc[f][j], 0, 0, 0);
-        }
-      }
-  }
-  // epilogue: lane holds D[(lane/16)*4 + q][lane%16] of each tile
-#pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    const int h = h0 + 2 * wave + (f >> 1);
-    if (h >= go.h) continue;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int w = w0 + (f & 1) * 16 + g * 4 + q;
-      const long long vo = (((long long)n * go.d + d) * go.h + h) * go.w + w;
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int col = j * 16 + L;
-        if (col >= ncols) continue;
-        float v = acc[f][j][q];
-        if (a.bias) v += a.bias[col];
-        if (a.relu) v = v > 0.f ? v : 0.f;
-        const long long o = vo * go.ldc + col;
-        if (a.act && !(bf2f(a.act[vo * a.act_ldc + col]) > 0.f)) v = 0.f;
-        if (a.accumulate) v += bf2f(a.out[o]);
-        a.out[o] = f2bf(v);
       }
     }
+  }
+  // epilogue: the two accumulators hold channels 8 g .. + 3 and + 4 .. + 7 of
+  // voxel column L of each row
+  const int w = w0 + L, col = n0 + g * 8;
+  if (w >= go.w || col >= ncols) return;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int h = h0 + hr0 + r;
+    if (h >= go.h) break;
+    const long long vo = (((long long)n * go.d + d) * go.h + h) * go.w + w;
+    store8(a, vo, col, acc[r][0], acc[r][1]);
   }
 }
 
@@ -1248,19 +1285,40 @@ void launch_tap_cols(const DArgs& a, long long rows, int nz, hipStream_t s) {
     launch_tap<MODE, CLS, 2, 8>(a, rows, nz, s);
 }
 
-// the halo kernel: stride-1 3x3x3 products onto whole 32-column row pieces
-// with at most 64 output columns
-bool halo_fits(const lbm_tensor5* src, const lbm_tensor5* out, int ksize, int stride) {
-  return ksize == 3 && stride == 1 && src->c % 32 == 0 && out->w % 32 == 0 && out->c <= 64;
+// Workgroups of the row-tile kernel with R rows per wave.
+template <int R>
+long long row_tiles(const Geo& go) {
+  return (long long)((go.w + 15) / 16) * ((go.h + 4 * R - 1) / (4 * R)) * go.d * go.n * ((go.c + 31) / 32);
 }
 
+// Stride-1 3x3x3 products: 16 x 16 tiles, or 8 x 16 where the larger ones
+// would leave compute units without a workgroup (batch 1, 32x16x16 128->128:
+// 18.6 -> 16.7 us on 128 tiles) or pad the rows enough to lose what the
+// smaller ones lose in operand reuse (1180 against 1000 TFLOP/s at 64x32x32
+// 64->64).  Two cases keep the tap-major kernel, which takes voxels in any
+// shape but channels in 32s: very narrow volumes, where even the small tiles
+// are mostly padding (at half, 16x8x8, the tiles still take 52 against 89 us),
+// and forward layers of several chunks off rows of whole 32s or with more than
+// 64 output channels, whose sums run tap by tap over all chunks: a forward
+// result rounded otherwise flips ReLU masks all through a network's backward
+// pass, so the order of those sums is kept.
 template <int MODE>
-void launch_halo(const DArgs& a, hipStream_t s) {
-  const unsigned g = (unsigned)((a.go.w / 32) * ((a.go.h + 7) / 8) * a.go.d * a.go.n);
-  if (a.go.c <= 32)
-    hipLaunchKernelGGL((k_conv_halo<MODE, 2>), dim3(g), dim3(256), 0, s, a);
+bool launch_rows(const DArgs& a, hipStream_t s) {
+  const long long big = row_tiles<4>(a.go), small = row_tiles<2>(a.go);
+  const long long vox = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
+  if (a.C % 32 == 0 && small * 128 > 4 * vox * ((a.go.c + 31) / 32)) return false;
+  if (MODE == 0 && a.C > 32 && a.C % 32 == 0 && (a.go.w % 32 != 0 || a.go.c > 64)) return false;
+  const bool four = big >= 256 && big * 2 <= small * 1.22, tail = a.C % 32 != 0;
+  const dim3 g((unsigned)(four ? big : small)), b(256);
+  if (four && tail)
+    hipLaunchKernelGGL((k_conv_rows<MODE, 4, true>), g, b, 0, s, a);
+  else if (four)
+    hipLaunchKernelGGL((k_conv_rows<MODE, 4, false>), g, b, 0, s, a);
+  else if (tail)
+    hipLaunchKernelGGL((k_conv_rows<MODE, 2, true>), g, b, 0, s, a);
   else
-    hipLaunchKernelGGL((k_conv_halo<MODE, 4>), dim3(g), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_conv_rows<MODE, 2, false>), g, b, 0, s, a);
+  return true;
 }
 
 int grid1(long long n) {
@@ -1288,14 +1346,12 @@ lbm_status lbm_conv3d_fwd(const lbm_tensor5* x, const uint16_t* w, const float* 
   hipStream_t s = (hipStream_t)stream;
   const Geo gs = geo_of(x), go = geo_of(y);
   const dim3 b(256);
-  if (x->c % 32 == 0 && tap_fits(x) && tap_fits(y)) {
+  const bool rows = ksize == 3 && stride == 1 && x->c != 8;
+  if ((x->c % 32 == 0 || rows) && tap_fits(x) && tap_fits(y) && (long long)y->c * kpad < (1ll << 30)) {
     const DArgs a{(const uint16_t*)x->ptr, gs, (unsigned)view_bytes(x), w, kpad,
                   (unsigned)((long long)y->c * kpad * 2), bias, (uint16_t*)y->ptr, go, nullptr, 0, ksize, stride,
                   relu, 0, x->c};
-    if (halo_fits(x, y, ksize, stride))
-      launch_halo<0>(a, s);
-    else
-      launch_tap_cols<0, false>(a, M, 1, s);
+    if (!rows || !launch_rows<0>(a, s)) launch_tap_cols<0, false>(a, M, 1, s);
   } else if (y->c <= 16) {
     dim3 g((unsigned)((M + BM - 1) / BM), (y->c + 15) / 16);
     hipLaunchKernelGGL((k_conv_gemm<0, 16>), g, b, 0, s, (const uint16_t*)x->ptr, gs, w, kpad, bias,
@@ -1332,7 +1388,8 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
   const uint16_t* ap = act ? (const uint16_t*)act->ptr : nullptr;
   const int aldc = act ? act->ldc : 0;
   const dim3 b(256);
-  if (dy->c % 32 == 0 && tap_fits(dy) && tap_fits(dx)) {
+  const bool rows = ksize == 3 && stride == 1;
+  if ((dy->c % 32 == 0 || rows) && tap_fits(dy) && tap_fits(dx) && (long long)dx->c * kpad < (1ll << 30)) {
     const DArgs a{(const uint16_t*)dy->ptr, gs, (unsigned)view_bytes(dy), w_t, kpad,
                   (unsigned)((long long)dx->c * kpad * 2), nullptr, (uint16_t*)dx->ptr, go, ap, aldc, ksize, stride,
                   0, accumulate, dy->c};
@@ -1340,9 +1397,7 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
       // rows of the largest parity class; smaller classes mask their tail
       const long long rows = (long long)dx->n * ((dx->d + 1) / 2) * ((dx->h + 1) / 2) * ((dx->w + 1) / 2);
       launch_tap_cols<1, true>(a, rows, 8, s);
-    } else if (halo_fits(dy, dx, ksize, stride)) {
-      launch_halo<1>(a, s);
-    } else {
+    } else if (!rows || !launch_rows<1>(a, s)) {
       launch_tap_cols<1, false>(a, M, 1, s);
     }
   } else if (dx->c <= 16) {
