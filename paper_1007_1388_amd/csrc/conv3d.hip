@@ -221,6 +221,46 @@ __device__ __forceinline__ void store8(const DArgs& a, long long vo, int col, f3
   *(u32x4*)o = q;
 }
 
+// Row m of the tap-major kernels: its output voxel (-1 past the last row),
+// the element offset of channel group kg of its source at tap (0, 0, 0), and
+// the mask of the taps whose source lies in the volume.
+template <int MODE, bool CLS>
+__device__ __forceinline__ void tap_row(const DArgs& a, int m, int Mrows, int cd, int ch, int cw, const int (&pcl)[3],
+                                        const int (&na)[3], int kg, int& base, int& voxel, unsigned& mask) {
+  const Geo& gs = a.gs;
+  const Geo& go = a.go;
+  const int pad = a.ksize == 3 ? 1 : 0;
+  const bool ok = m < Mrows;
+  int r = ok ? m : 0;
+  int c3[3];
+  c3[2] = r % cw; r /= cw;
+  c3[1] = r % ch; r /= ch;
+  c3[0] = r % cd;
+  const int n = r / cd;
+  if (CLS)
+    for (int x = 0; x < 3; ++x) c3[x] = 2 * c3[x] + pcl[x];
+  voxel = ok ? ((n * go.d + c3[0]) * go.h + c3[1]) * go.w + c3[2] : -1;
+  const int ext[3] = {gs.d, gs.h, gs.w};
+  int b3[3];
+  unsigned v3[3];
+  for (int x = 0; x < 3; ++x) {
+    b3[x] = MODE == 0 ? c3[x] * a.stride - pad : (CLS ? (c3[x] + 1) >> 1 : c3[x] + pad);
+    unsigned v = 0;
+    for (int j = 0; j < na[x]; ++j) {
+      const int sx = MODE == 0 ? b3[x] + j : b3[x] - j;
+      if (sx >= 0 && sx < ext[x]) v |= 1u << j;
+    }
+    v3[x] = v;
+  }
+  unsigned mm = 0;
+  for (int jd = 0; jd < na[0]; ++jd)
+    for (int jh = 0; jh < na[1]; ++jh)
+      for (int jw = 0; jw < na[2]; ++jw)
+        if ((v3[0] >> jd) & (v3[1] >> jh) & (v3[2] >> jw) & 1u) mm |= 1u << ((jd * na[1] + jh) * na[2] + jw);
+  mask = ok ? mm : 0u;
+  base = (((n * gs.d + b3[0]) * gs.h + b3[1]) * gs.w + b3[2]) * gs.ldc + kg * 8;
+}
+
 template <int MODE, bool CLS, int FM, int FN>
 __global__ void __launch_bounds__(256) k_conv_tap(DArgs a) {
   constexpr int BN = 16 * FN, WM = 16 * FM, BMW = 4 * WM;
@@ -257,38 +297,8 @@ __global__ void __launch_bounds__(256) k_conv_tap(DArgs a) {
   int basef[FM], voxf[FM];
   unsigned mskf[FM];
 #pragma unroll
-  for (int f = 0; f < FM; ++f) {
-    const int m = m0 + f * 16 + (lane & 15);
-    const bool ok = m < Mrows;
-    int r = ok ? m : 0;
-    int c3[3];
-    c3[2] = r % cw; r /= cw;
-    c3[1] = r % ch; r /= ch;
-    c3[0] = r % cd;
-    const int n = r / cd;
-    if (CLS)
-      for (int x = 0; x < 3; ++x) c3[x] = 2 * c3[x] + pcl[x];
-    voxf[f] = ok ? ((n * go.d + c3[0]) * go.h + c3[1]) * go.w + c3[2] : -1;
-    const int ext[3] = {gs.d, gs.h, gs.w};
-    int b3[3];
-    unsigned v3[3];
-    for (int x = 0; x < 3; ++x) {
-      b3[x] = MODE == 0 ? c3[x] * a.stride - pad : (CLS ? (c3[x] + 1) >> 1 : c3[x] + pad);
-      unsigned v = 0;
-      for (int j = 0; j < na[x]; ++j) {
-        const int sx = MODE == 0 ? b3[x] + j : b3[x] - j;
-        if (sx >= 0 && sx < ext[x]) v |= 1u << j;
-      }
-      v3[x] = v;
-    }
-    unsigned mm = 0;
-    for (int jd = 0; jd < na[0]; ++jd)
-      for (int jh = 0; jh < na[1]; ++jh)
-        for (int jw = 0; jw < na[2]; ++jw)
-          if ((v3[0] >> jd) & (v3[1] >> jh) & (v3[2] >> jw) & 1u) mm |= 1u << ((jd * na[1] + jh) * na[2] + jw);
-    mskf[f] = ok ? mm : 0u;
-    basef[f] = (((n * gs.d + b3[0]) * gs.h + b3[1]) * gs.w + b3[2]) * gs.ldc + (lane >> 4) * 8;
-  }
+  for (int f = 0; f < FM; ++f)
+    tap_row<MODE, CLS>(a, m0 + f * 16 + (lane & 15), Mrows, cd, ch, cw, pcl, na, lane >> 4, basef[f], voxf[f], mskf[f]);
 
   const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.src, a.src_bytes);
   const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wk, a.wk_bytes);
@@ -669,6 +679,139 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
   // voxel column L of each row
   const int w = w0 + L, col = n0 + g * 8;
   if (w >= go.w || col >= ncols) return;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int h = h0 + hr0 + r;
+    if (h >= go.h) break;
+    const long long vo = (((long long)n * go.d + d) * go.h + h) * go.w + w;
+    store8(a, vo, col, acc[r][0], acc[r][1]);
+  }
+}
+
+// --------------------------- forward, stride 1, 3x3x3, plane tiles, tap-major
+// The stride-1 3x3x3 forward layers of 64, 128 or 256 channels (NC chunks of
+// 32) whose sums run tap by tap with the chunks inside.  Against the tap-major
+// kernel, which gathers every operand from L1/L2 once per tap (about 10 TB/s
+// in all) and waits on those loads in every K step, a workgroup brings the
+// halo of one source plane, all chunks, into LDS once for its nine taps, and
+// streams the taps' weights ([column][32 NC channels]) through two LDS buffers
+// one tap ahead; both operands are LDS reads.  A tile is 4 R rows of 16 voxels
+// and 32 WN columns: wave v takes R rows and 32 columns.  A 16-voxel operand
+// is a row of 16 (WF = 16) or rows of 8 of two planes (WF = 8, the volumes 8
+// wide, or off 16s).  Cell layout, weight rows and stores as in k_conv_rows.
+// Bound by LDS reads (four for four MFMAs per chunk with R = 2) at full chips
+// and by the chain of nine weight loads per plane at small ones.  Measured on
+// gfx950, us, against the tap-major kernel: batch 1 16x8x8 256->256 67.6 ->
+// 18.5, 32x16x16 128->128 41 -> 15.8 and 256->128 85 -> 24.5; batch 8 88 -> 52,
+// 88 -> 56 and 160 -> 128 (904 TFLOP/s).
+template <int NC, int WF, int R, int WN>
+__global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
+  constexpr int FN = 2, BN = 16 * FN * WN;
+  constexpr int NWV = 4 * WN;                   // waves: 4 row groups x WN column groups
+  constexpr int DP = 16 / WF;                   // planes of a 16-voxel operand
+  constexpr int TH = R * 4;
+  constexpr int HC = WF + 2, HR = TH + 2;
+  constexpr int CELLS = DP * HR * HC;
+  constexpr int NXI = (CELLS * 4 + 63) / 64;    // wave-wide 16-byte loads of one chunk's halo
+  constexpr int SX = (NXI + NWV - 1) / NWV;
+  constexpr int SW = NC / 2;                    // ... of a tap's weights, per wave
+  constexpr unsigned OOB = 0x80000000u;
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[NC][NXI * 512];
+  __shared__ __attribute__((aligned(1024))) uint16_t Ws[2][NC * BN * 32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Geo gs = a.gs, go = a.go;
+  const int ncols = go.c;
+  constexpr int C = NC * 32;
+  const int total = (int)gridDim.x, id0 = (int)blockIdx.x, q8 = total / 8 * 8;
+  int bx = id0 < q8 ? (id0 % 8) * (total / 8) + id0 / 8 : id0;
+  const int nct = (ncols + BN - 1) / BN, nwb = (go.w + WF - 1) / WF, nhb = (go.h + TH - 1) / TH,
+            ndb = (go.d + DP - 1) / DP;
+  const int n0 = bx % nct * BN;
+  bx /= nct;
+  const int w0 = bx % nwb * WF;
+  bx /= nwb;
+  const int h0 = bx % nhb * TH;
+  bx /= nhb;
+  const int d0 = bx % ndb * DP, n = bx / ndb;
+
+  const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.src, a.src_bytes);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wk, a.wk_bytes);
+  unsigned xoff[SX];
+  int xp[SX];
+#pragma unroll
+  for (int i = 0; i < SX; ++i) {
+    const int id = (i * NWV + wave) * 64 + lane;
+    const int cell = id >> 2, p = cell / (HR * HC), r = cell / HC % HR, c = cell % HC;
+    const int q = (id & 3) ^ ((c >> 1) & 3);
+    const int hs = h0 - 1 + r, ws = w0 - 1 + c;
+    const bool ok = cell < CELLS && hs >= 0 && hs < gs.h && ws >= 0 && ws < gs.w;
+    xp[i] = p;
+    xoff[i] = ok ? (unsigned)(((p * gs.h + hs) * gs.w + ws) * gs.ldc + q * 8) * 2u : OOB;
+  }
+  unsigned woff[SW];
+#pragma unroll
+  for (int i = 0; i < SW; ++i) {
+    const int id = (i * NWV + wave) * 64 + lane;
+    const int ck = id / (BN * 4), rem = id % (BN * 4);
+    const int col = rem >> 2, q = (rem & 3) ^ ((col >> 3) & 3);
+    woff[i] = n0 + col < ncols ? (unsigned)((n0 + col) * a.kstride + ck * 32 + q * 8) * 2u : OOB;
+  }
+  auto load_w = [&](int t, int buf) {
+#pragma unroll
+    for (int i = 0; i < SW; ++i) lds_dma16(rw, Ws[buf] + (i * NWV + wave) * 512, woff[i], (unsigned)(t * C) * 2u);
+  };
+  const int L = lane & 15, g = lane >> 4;
+  const int hr0 = wave / WN * R, nc0 = wave % WN * 32, vp = L / WF, vc = L % WF;
+  int xb[3];
+#pragma unroll
+  for (int kw = 0; kw < 3; ++kw)
+    xb[kw] = ((vp * HR + hr0) * HC + vc + kw) * 32 + ((g ^ (((vc + kw) >> 1) & 3)) * 8);
+  const int wb = (nc0 + (L >> 2) * 8 + (L & 3)) * 32 + ((g ^ (L >> 2)) * 8);
+
+  f32x4 acc[R][FN];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const unsigned plane = (unsigned)(gs.h * gs.w * gs.ldc) * 2u;
+  for (int kd = 0; kd < 3; ++kd) {
+    const int ds = d0 + kd - 1;  // source plane of the tile's first one
+    if (ds + DP <= 0 || ds >= gs.d) continue;
+    const unsigned sp = (unsigned)(n * gs.d + ds) * plane;
+    __syncthreads();  // the previous plane's readers are done
+    load_w(kd * 9, 0);
+#pragma unroll
+    for (int i = 0; i < SX; ++i)
+      if (i * NWV + wave < NXI) {
+        const bool ok = ds + xp[i] >= 0 && ds + xp[i] < gs.d;
+        // (a tile's first plane may lie before the volume: its offset is added per lane)
+        const unsigned vo = ok && xoff[i] != OOB ? xoff[i] + sp : OOB;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) lds_dma16(rs, Xs[k] + (i * NWV + wave) * 512, vo, (unsigned)k * 64u);
+      }
+    __syncthreads();  // (waits for the loads)
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      if (t < 8) load_w(kd * 9 + t + 1, (t + 1) & 1);  // in flight while this tap runs
+      const int kh = t / 3, kw = t % 3;
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        bf16x8 wf[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) wf[j] = *(const bf16x8*)(&Ws[t & 1][wb + (k * BN + j * 4) * 32]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const bf16x8 xf = *(const bf16x8*)(&Xs[k][xb[kw] + (r + kh) * HC * 32]);
+#pragma unroll
+          for (int j = 0; j < FN; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf, acc[r][j], 0, 0, 0);
+        }
+      }
+      __syncthreads();  // this tap's weights are read, the next one's have arrived
+    }
+  }
+  const int w = w0 + vc, d = d0 + vp, col = n0 + nc0 + g * 8;
+  if (w >= go.w || d >= go.d || col >= ncols) return;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int h = h0 + hr0 + r;
@@ -1285,6 +1428,53 @@ void launch_tap_cols(const DArgs& a, long long rows, int nz, hipStream_t s) {
     launch_tap<MODE, CLS, 2, 8>(a, rows, nz, s);
 }
 
+// One shape of the plane kernel: its workgroups, and an estimate of its time
+// in units of one (WF = 8, R = 2, WN = 1) workgroup alone on a compute unit:
+// rounds of workgroups (as many per unit as LDS holds) times a workgroup's
+// time, which measured 0.8 : 1 : 1.4 for R WN = 1, 2, 4 (18.5, 23.3 and 31.7 us
+// at 256 channels).
+template <int NC, int WF, int R, int WN>
+struct PlaneTile {
+  static constexpr int DP = 16 / WF;
+  static constexpr int kLds = NC * ((DP * (4 * R + 2) * (WF + 2) * 4 + 63) / 64 * 1024 + 2 * 32 * WN * 64);
+  static long long groups(const Geo& go) {
+    return (long long)((go.w + WF - 1) / WF) * ((go.h + 4 * R - 1) / (4 * R)) * ((go.d + DP - 1) / DP) * go.n *
+           ((go.c + 32 * WN - 1) / (32 * WN));
+  }
+  static double cost(const Geo& go) {
+    const long long slots = 256 * (160 * 1024 / kLds);
+    return (double)((groups(go) + slots - 1) / slots) * (0.6 + 0.2 * R * WN);
+  }
+  static void launch(const DArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((k_conv_plane<NC, WF, R, WN>), dim3((unsigned)groups(a.go)), dim3(256 * WN), 0, s, a);
+  }
+};
+
+template <int NC>
+void launch_plane_c(const DArgs& a, hipStream_t s) {
+  using Small = PlaneTile<NC, 8, 1, 1>;
+  using Mid = PlaneTile<NC, 8, 2, 1>;
+  using Big = PlaneTile<NC, 16, 2, 2>;
+  const double cs = Small::cost(a.go), cm = Mid::cost(a.go), cb = Big::cost(a.go);
+  if (cb < cm && cb < cs)
+    Big::launch(a, s);
+  else if (cm <= cs)
+    Mid::launch(a, s);
+  else
+    Small::launch(a, s);
+}
+
+// The forward layers that keep the tap-by-tap order of their sums (see
+// launch_rows), for the channel counts the plane kernel holds in LDS.
+bool launch_plane(const DArgs& a, hipStream_t s) {
+  switch (a.C) {
+    case 64: launch_plane_c<2>(a, s); return true;
+    case 128: launch_plane_c<4>(a, s); return true;
+    case 256: launch_plane_c<8>(a, s); return true;
+  }
+  return false;
+}
+
 // Workgroups of the row-tile kernel with R rows per wave.
 template <int R>
 long long row_tiles(const Geo& go) {
@@ -1295,19 +1485,19 @@ long long row_tiles(const Geo& go) {
 // would leave compute units without a workgroup (batch 1, 32x16x16 128->128:
 // 18.6 -> 16.7 us on 128 tiles) or pad the rows enough to lose what the
 // smaller ones lose in operand reuse (1180 against 1000 TFLOP/s at 64x32x32
-// 64->64).  Two cases keep the tap-major kernel, which takes voxels in any
-// shape but channels in 32s: very narrow volumes, where even the small tiles
-// are mostly padding (at half, 16x8x8, the tiles still take 52 against 89 us),
-// and forward layers of several chunks off rows of whole 32s or with more than
-// 64 output channels, whose sums run tap by tap over all chunks: a forward
-// result rounded otherwise flips ReLU masks all through a network's backward
-// pass, so the order of those sums is kept.
+// 64->64).  Very narrow volumes, where even the small tiles are mostly padding
+// (at half, 16x8x8, they still take 52 against 89 us), keep the tap-major
+// kernel, which takes voxels in any shape but channels in 32s.  Forward layers
+// of 64, 128 or 256 channels off rows of whole 32s or with more than 64 output
+// channels go to the plane kernel, whose sums run tap by tap over all chunks:
+// a forward result rounded otherwise flips ReLU masks all through a network's
+// backward pass, so the order of those sums is kept.
 template <int MODE>
 bool launch_rows(const DArgs& a, hipStream_t s) {
   const long long big = row_tiles<4>(a.go), small = row_tiles<2>(a.go);
   const long long vox = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
+  if (MODE == 0 && (a.go.w % 32 != 0 || a.go.c > 64) && launch_plane(a, s)) return true;
   if (a.C % 32 == 0 && small * 128 > 4 * vox * ((a.go.c + 31) / 32)) return false;
-  if (MODE == 0 && a.C > 32 && a.C % 32 == 0 && (a.go.w % 32 != 0 || a.go.c > 64)) return false;
   const bool four = big >= 256 && big * 2 <= small * 1.22, tail = a.C % 32 != 0;
   const dim3 g((unsigned)(four ? big : small)), b(256);
   if (four && tail)

@@ -77,3 +77,35 @@ ROWS = [
 @pytest.mark.parametrize("case", range(len(ROWS)))
 def test_stride1_row_tiles(case):
     _check(ROWS[case], 100 + case)
+
+
+# stride 1, 64, 128 and 256 channels off rows of whole 32s or onto more than 64
+# channels: the plane tiles of one and two planes, 4 and 8 rows, 32 and 64
+# columns (with partial ones), odd depths (a tile's second plane past the
+# volume), and enough tiles for the largest kind
+PLANES = [
+    dict(n=1, d=1, h=1, w=1, ci=64, co=8),
+    dict(n=2, d=3, h=5, w=7, ci=256, co=40),
+    dict(n=1, d=5, h=9, w=17, ci=128, co=72),
+    dict(n=2, d=2, h=8, w=32, ci=64, co=96),
+    dict(n=4, d=33, h=16, w=18, ci=64, co=64),
+]
+
+
+@pytest.mark.parametrize("case", range(len(PLANES)))
+def test_stride1_plane_tiles(case):
+    _check(PLANES[case], 200 + case)
+
+
+def test_forward_does_not_depend_on_the_tile_sizes():
+    """The same sample alone and as part of a batch large enough for other tile sizes: bit for bit."""
+    from paper_1007_1388_amd import surrogate as S
+    for ci, co, d, h, w in ((64, 32, 6, 18, 40), (32, 32, 9, 17, 33), (128, 96, 4, 16, 16)):
+        rng = np.random.default_rng(ci + w)
+        x = conv.bf16_round(rng.standard_normal((24, d, h, w, ci)))
+        layer = S.Conv(ci, co, relu=True, seed=5)
+        X, Y = S.from_numpy(x), S.Act(24, d, h, w, co)
+        layer.forward(X, Y)
+        X1, Y1 = S.from_numpy(x[3:4]), S.Act(1, d, h, w, co)
+        layer.forward(X1, Y1)
+        assert np.array_equal(Y.to_numpy()[3:4], Y1.to_numpy())
