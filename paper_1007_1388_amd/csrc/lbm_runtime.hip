@@ -326,7 +326,10 @@ void order_items_by_xcd(lbm_ctx* c) {
 //    itself: half, one task per wave.  These are bound by memory, and a
 //    second task's loads wait behind the first one's stores: 256^3 channel
 //    FP32 474 -> 454, FP64 951 -> 942, 200^3 FP32 250 -> 238, 128^3 FP64
-//    124 -> 117, one-Block open duct 100 -> 95.  With obstacles, or sending x
+//    124 -> 117, one-Block open duct 100 -> 95; 2-8 % over 60 channels 64, 128
+//    and 256 wide but two (256x150x150 and 256x192x192 FP32, 4-5 % slower).
+//    Not where that leaves a wave without a task (rows of 129-192 cells, three
+//    tasks: FP32 3-8 % slower, build_items).  With obstacles, or sending x
 //    faces, FP32 keeps two tasks (128^3 porous 65.7 against 66.8, porous
 //    512x256x256 in 250 Blocks 1102 against 1146: more of a task is set-up).
 //  * Fewer than three items per compute unit: half, whatever the variant, to
@@ -337,18 +340,21 @@ void order_items_by_xcd(lbm_ctx* c) {
 //    which half-size values outrun: 256^3 cavity FP16S 273 -> 263, 128^3 38.7
 //    -> 36.9, 256^3 in 8 Blocks 358 -> 318 (64^3, one per unit, 19.4
 //    against 23.8).
+bool few_items(const lbm_ctx* c) {
+  return c->n_cells / std::max(1, c->sched.item_cells) < 3 * c->cu_count;
+}
 int item_target(const lbm_ctx* c) {
   const int t = std::max(1, c->sched.item_cells);
   if (c->sched.persistent > 0) return t;  // workgroups loop over the items anyway
-  const long long items = c->n_cells / t, cus = c->cu_count;
-  if (c->prec >= 2) return items >= 12 * cus ? 2 * t : t;
+  if (c->prec >= 2) return c->n_cells / t >= 12 * c->cu_count ? 2 * t : t;
   const bool streams = c->prec == 0 || (!c->has_mask && c->sched.fused_exchange != 2);
-  return streams || items < 3 * cus ? std::max(1, t / 2) : t;
+  return streams || few_items(c) ? std::max(1, t / 2) : t;
 }
 
 void build_items(lbm_ctx* c) {
   c->items_h.clear();
-  const int target = item_target(c);
+  const int target = item_target(c), whole = std::max(1, c->sched.item_cells);
+  const bool halved = target < whole && !few_items(c);
   const int vec = cells_per_lane(c, c->sched), nw = std::max(1, c->sched.wg_size / 64);
   for (int j = 0; j < (int)c->bh.size(); ++j) {
     const BlockDev& B = c->bh[j];
@@ -375,6 +381,10 @@ void build_items(lbm_ctx* c) {
     while (xw > 1 && xw / 2 >= lanes) xw >>= 1;
     const int rpw = 64 / xw, nseg = (lanes + 63) / 64;
     auto tasks = [&](int r) { return flat ? ((long long)r * a + 63) / 64 : (long long)((r + rpw - 1) / rpw) * nseg; };
+    if (halved && !flat && tasks(rows) % nw != 0) {
+      rows = std::max(1, std::min(b, whole / a));
+      if (B.pack) rows = std::max(2, rows & ~1);
+    }
     for (int r = rows; r <= b && c->prec >= 2; ++r) {
       if (tasks(r) % nw == 0 || r == b) {
         rows = r;
