@@ -688,9 +688,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
   }
 }
 
-// --------------------------- forward, stride 1, 3x3x3, plane tiles, tap-major
-// The stride-1 3x3x3 forward layers of 64, 128 or 256 channels (NC chunks of
-// 32) whose sums run tap by tap with the chunks inside.  Against the tap-major
+// ----------------------- fwd / bwd-data, stride 1, 3x3x3, plane tiles, tap-major
+// The stride-1 3x3x3 products of 64, 128 or 256 channels (NC chunks of 32)
+// whose sums run tap by tap with the chunks inside.  Against the tap-major
 // kernel, which gathers every operand from L1/L2 once per tap (about 10 TB/s
 // in all) and waits on those loads in every K step, a workgroup brings the
 // halo of one source plane, all chunks, into LDS once for its nine taps, and
@@ -703,8 +703,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // and by the chain of nine weight loads per plane at small ones.  Measured on
 // gfx950, us, against the tap-major kernel: batch 1 16x8x8 256->256 67.6 ->
 // 18.5, 32x16x16 128->128 41 -> 15.8 and 256->128 85 -> 24.5; batch 8 88 -> 52,
-// 88 -> 56 and 160 -> 128 (904 TFLOP/s).
-template <int NC, int WF, int R, int WN>
+// 88 -> 56 and 160 -> 128 (904 TFLOP/s); input gradients alike (89 -> 59, 88 ->
+// 65, 157 -> 120; 64x32x32 128->64 378 -> 234).  MODE 1 runs mirrored taps.
+template <int MODE, int NC, int WF, int R, int WN>
 __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
   constexpr int FN = 2, BN = 16 * FN * WN;
   constexpr int NWV = 4 * WN;                   // waves: 4 row groups x WN column groups
@@ -776,7 +777,7 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
 
   const unsigned plane = (unsigned)(gs.h * gs.w * gs.ldc) * 2u;
   for (int kd = 0; kd < 3; ++kd) {
-    const int ds = d0 + kd - 1;  // source plane of the tile's first one
+    const int ds = MODE == 0 ? d0 + kd - 1 : d0 + 1 - kd;  // source plane of the tile's first one
     if (ds + DP <= 0 || ds >= gs.d) continue;
     const unsigned sp = (unsigned)(n * gs.d + ds) * plane;
     __syncthreads();  // the previous plane's readers are done
@@ -802,7 +803,7 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
         for (int j = 0; j < FN; ++j) wf[j] = *(const bf16x8*)(&Ws[t & 1][wb + (k * BN + j * 4) * 32]);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const bf16x8 xf = *(const bf16x8*)(&Xs[k][xb[kw] + (r + kh) * HC * 32]);
+          const bf16x8 xf = *(const bf16x8*)(&Xs[k][xb[MODE == 0 ? kw : 2 - kw] + (r + (MODE == 0 ? kh : 2 - kh)) * HC * 32]);
 #pragma unroll
           for (int j = 0; j < FN; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf, acc[r][j], 0, 0, 0);
         }
@@ -1433,7 +1434,7 @@ void launch_tap_cols(const DArgs& a, long long rows, int nz, hipStream_t s) {
 // rounds of workgroups (as many per unit as LDS holds) times a workgroup's
 // time, which measured 0.8 : 1 : 1.4 for R WN = 1, 2, 4 (18.5, 23.3 and 31.7 us
 // at 256 channels).
-template <int NC, int WF, int R, int WN>
+template <int MODE, int NC, int WF, int R, int WN>
 struct PlaneTile {
   static constexpr int DP = 16 / WF;
   static constexpr int kLds = NC * ((DP * (4 * R + 2) * (WF + 2) * 4 + 63) / 64 * 1024 + 2 * 32 * WN * 64);
@@ -1446,15 +1447,15 @@ struct PlaneTile {
     return (double)((groups(go) + slots - 1) / slots) * (0.6 + 0.2 * R * WN);
   }
   static void launch(const DArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_conv_plane<NC, WF, R, WN>), dim3((unsigned)groups(a.go)), dim3(256 * WN), 0, s, a);
+    hipLaunchKernelGGL((k_conv_plane<MODE, NC, WF, R, WN>), dim3((unsigned)groups(a.go)), dim3(256 * WN), 0, s, a);
   }
 };
 
-template <int NC>
+template <int MODE, int NC>
 void launch_plane_c(const DArgs& a, hipStream_t s) {
-  using Small = PlaneTile<NC, 8, 1, 1>;
-  using Mid = PlaneTile<NC, 8, 2, 1>;
-  using Big = PlaneTile<NC, 16, 2, 2>;
+  using Small = PlaneTile<MODE, NC, 8, 1, 1>;
+  using Mid = PlaneTile<MODE, NC, 8, 2, 1>;
+  using Big = PlaneTile<MODE, NC, 16, 2, 2>;
   const double cs = Small::cost(a.go), cm = Mid::cost(a.go), cb = Big::cost(a.go);
   if (cb < cm && cb < cs)
     Big::launch(a, s);
@@ -1464,13 +1465,14 @@ void launch_plane_c(const DArgs& a, hipStream_t s) {
     Small::launch(a, s);
 }
 
-// The forward layers that keep the tap-by-tap order of their sums (see
+// The products that keep the tap-by-tap order of their sums (see
 // launch_rows), for the channel counts the plane kernel holds in LDS.
+template <int MODE>
 bool launch_plane(const DArgs& a, hipStream_t s) {
   switch (a.C) {
-    case 64: launch_plane_c<2>(a, s); return true;
-    case 128: launch_plane_c<4>(a, s); return true;
-    case 256: launch_plane_c<8>(a, s); return true;
+    case 64: launch_plane_c<MODE, 2>(a, s); return true;
+    case 128: launch_plane_c<MODE, 4>(a, s); return true;
+    case 256: launch_plane_c<MODE, 8>(a, s); return true;
   }
   return false;
 }
@@ -1487,16 +1489,17 @@ long long row_tiles(const Geo& go) {
 // smaller ones lose in operand reuse (1180 against 1000 TFLOP/s at 64x32x32
 // 64->64).  Very narrow volumes, where even the small tiles are mostly padding
 // (at half, 16x8x8, they still take 52 against 89 us), keep the tap-major
-// kernel, which takes voxels in any shape but channels in 32s.  Forward layers
-// of 64, 128 or 256 channels off rows of whole 32s or with more than 64 output
-// channels go to the plane kernel, whose sums run tap by tap over all chunks:
-// a forward result rounded otherwise flips ReLU masks all through a network's
-// backward pass, so the order of those sums is kept.
+// kernel, which takes voxels in any shape but channels in 32s.  Products of 64,
+// 128 or 256 channels off rows of whole 32s or onto more than 64 channels go to
+// the plane kernel, whose sums run tap by tap over all chunks: results rounded
+// otherwise would flip ReLU masks all through a network's passes, so the order
+// of those sums is kept (the input gradient of 32x16x16 256->128 at batch 8
+// takes 112 us there against 91 on row tiles, 64x32x32 128->64 234 against 222).
 template <int MODE>
 bool launch_rows(const DArgs& a, hipStream_t s) {
   const long long big = row_tiles<4>(a.go), small = row_tiles<2>(a.go);
   const long long vox = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
-  if (MODE == 0 && (a.go.w % 32 != 0 || a.go.c > 64) && launch_plane(a, s)) return true;
+  if ((a.go.w % 32 != 0 || a.go.c > 64) && launch_plane<MODE>(a, s)) return true;
   if (a.C % 32 == 0 && small * 128 > 4 * vox * ((a.go.c + 31) / 32)) return false;
   const bool four = big >= 256 && big * 2 <= small * 1.22, tail = a.C % 32 != 0;
   const dim3 g((unsigned)(four ? big : small)), b(256);
