@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/lbm_surrogate.h"
 
 namespace {
@@ -822,24 +824,7 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
   }
 }
 
-// ------------------------------------------------- bwd-weight, 3x3x3 halos
-// dw[co][tap*Cin + ci] += sum_v dy[v][co] * x[src(v, tap)][ci] for 3x3x3
-// kernels with Cin a multiple of 32, and (db given) db[co] += sum_v dy[v][co]
-// from the dy tiles already in LDS, by the workgroups of kernel plane 0 and
-// input-channel tile 0 (each dy tile once).  A workgroup owns one kernel plane kd,
-// 32 input channels and BM output channels, i.e. a BM x (9 taps x 32) block
-// of dw, and walks a range of 32-voxel steps of dy (R rows of W' voxels,
-// W' = min(W, 32)).  Per step it stages, in their channels-last order,
-//   * the dy tile  [32 voxels][BM channels] and
-//   * the x halo   [(R-1)s+3 rows][(W'-1)s+3 columns][32 channels] of plane
-//     z = d*s + kd - 1, which holds the sources of all nine (kh, kw) taps;
-// both MFMA operands (voxels as K) are then read from LDS by the transposing
-// read ds_read_b64_tr_b16 (a 16-lane group gives the addresses of four rows
-// of four 16-bit values; lane l receives column l%16 of that 4 x 16 block),
-// so the halo is staged once for nine taps and no lane transposes by hand.
-// Tiles are double-buffered; out-of-range sources and voxels load zeros
-// through the buffer range check.  Each wave keeps 9 x BM/32 accumulator
-// tiles and adds them to dw once at the end (FP32 atomics).
+// ------------------------------------------------------- bwd-weight operands
 struct WArgs {
   const uint16_t* x;
   Geo gx;
@@ -850,7 +835,8 @@ struct WArgs {
   float* dw;
   float* db;            // bias gradient, or nullptr
   int kpad;
-  int wp, r, nhb, nwb;  // step shape: R rows of W' voxels; steps per row block / plane
+  int wp, r;            // k_conv_wgrad_c8: step shape, R rows of W' voxels
+  int nhb, nwb;         // steps per column of rows / per row
   int steps, per_wg;    // total steps, steps per workgroup
   int nco, nci;         // output / input channel tiles
 };
@@ -865,198 +851,217 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// VS = 64 or 128 (stride 1, rows of at least 32 voxels): steps of two or
-// four 32-voxel rows, each tap's K chunks run on one staging of dy and of
-// the halo of VS/32 + 2 rows, so a barrier and a staging round cover two or
-// four times the MFMAs.
-template <int S, int BM, int VS = 32>
-__global__ void __launch_bounds__(256) k_conv_wgrad_halo(WArgs a) {
-  constexpr int PA = BM + 8;                 // dy tile row pitch (bf16)
-  constexpr int PC = 40;                     // halo cell pitch: 32 channels + 8
-  // largest halo over the step shapes (VS >= 64: rows of 32 voxels only)
-  constexpr int CELLS = VS >= 64 ? ((VS / 32 - 1) * S + 3) * (31 * S + 3) : (S == 1 ? 102 : 195);
-  constexpr int NK = VS / 32;                // 32-voxel K chunks per step
-  constexpr int NAC = VS * BM / 8;           // dy chunks of 8 channels
-  constexpr int NAP = (NAC + 255) / 256;
-  constexpr int NXP = (CELLS * 4 + 255) / 256;
-  constexpr int NSUB = BM / 32;              // 16-row output tiles per wave
+// ------------------------------------------------ bwd-weight, 3x3x3, row steps
+// dw[co][tap*Cin + ci] += sum_v dy[v][co] * x[src(v, tap)][ci] for 3x3x3
+// kernels, and (db given) db[co] += sum_v dy[v][co] from the dy tiles already
+// in LDS, by the workgroups of kernel plane 0 and input-channel tile 0 (each
+// dy tile once).  A workgroup owns one kernel plane kd, 32 input channels and
+// BM output channels, i.e. a BM x (9 taps x 32) block of dw, and walks steps of
+// RR rows of 32 voxels of dy (a row: 32 along w, or 16 or 8 along w of two or
+// four planes, whichever pads the volume least).  Per step it brings the dy
+// tile and the x halo of plane d S + kd - 1, the sources of all nine (kh, kw)
+// taps, into LDS by 16-byte buffer loads that write LDS directly; both MFMA
+// operands (voxels as K) are then transposing reads (ds_read_b64_tr_b16: a
+// 16-lane group gives the addresses of four rows of four 16-bit values; lane l
+// receives column l%16 of that 4 x 16 block).
+//  * The dy rows stay in registers, and an x row read once per column shift kw
+//    serves the three taps kh whose dy row it meets: 26 reads for 72 MFMAs of
+//    a wave (tap by tap it takes 44; 40 for 36 with 32 output channels, whose
+//    four waves now pair up on two halves of the rows and add up through LDS).
+//  * Steps go along the depth first: the workgroups of the three kernel
+//    planes, which run side by side on one XCD, then meet each x plane within
+//    three steps, in their L2 (going along the rows first read x three times
+//    from memory: 128x64x64 32->32 290 against 267 us at batch 8, 64->32 512
+//    against 460).
+//  * 768 workgroups in all: every one ends with BM x 288 FP32 atomics, of which
+//    the card takes about 95 G/s (memory side, whatever their order or the
+//    width of their runs), so more workgroups cost more than they fill
+//    (64x32x32 64->64: 128 us with 768, 143 with 1024, 176 with 2048).
+// Channels in 8s: the part of a tile past Cin or Cout loads zeros.
+// Measured on gfx950 at batch 8, us, against the tap-by-tap kernel: 128x64x64
+// 32->32 349 -> 267, 64->32 583 -> 460; 64x32x32 64->64 189 -> 128, 128->64 248 ->
+// 207 (1120 TFLOP/s); 32x16x16 128->128 113 -> 84, 256->128 187 -> 120; 16x8x8
+// 256->256 69 -> 60; stride 2 128x64x64 32->64 145 -> 140; 4 x 100x60x52 32->64
+// 138 (general kernel) -> 67; batch 1 128x64x64 32->32 129 -> 103.  Bound by the
+// atomics and, at full resolution, by HBM; the rest by LDS reads and MFMAs.
+template <int S, int BM, int WP>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1 && WP > 8 ? 4 : 2))) k_conv_wgrad_rows(WArgs a) {
+  constexpr int KS = BM == 32 ? 2 : 1;             // waves that share a dw tile, each with 4 of a step's rows
+  constexpr int RW = 4, RR = RW * KS;              // rows per wave, per step
+  constexpr int DP = 32 / WP;                      // planes of a 32-voxel row
+  constexpr int HR = (RR - 1) * S + 3, HC = (WP - 1) * S + 3;
+  constexpr int CELLS = DP * HR * HC;
+  constexpr int NXI = (CELLS * 4 + 63) / 64, NAI = RR * BM / 16;  // wave-wide loads of x and dy
+  constexpr int SX = (NXI + 3) / 4, SA = NAI / 4;
   constexpr unsigned OOB = 0x80000000u;
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][VS * PA];
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][CELLS * PC];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kX = NXI * 512, kA = NAI * 512;
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[kX + kA];
+  uint16_t* const As = Xs + kX;                    // [BM / 32][RR * 32 voxels][32 channels]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const Geo gx = a.gx, gy = a.gy;
-  // Work index from the linear workgroup id, XCD-aware: workgroups are
-  // dealt to the 8 XCDs in turn, so id L runs on XCD L % 8; consecutive
-  // indices (the weight tiles of one step range, which read the same dy and
-  // x data) are given to consecutive workgroups of one XCD and share its L2.
-  // The tail past the last multiple of 8 keeps its own index.
-  const int total = (int)gridDim.x, L8 = (int)blockIdx.x;
-  const int q8 = total / 8 * 8;
+  // XCD-aware work index (see k_conv_rows): the weight tiles of one step range
+  // read the same dy and x data and share an XCD's L2
+  const int total = (int)gridDim.x, L8 = (int)blockIdx.x, q8 = total / 8 * 8;
   const int idx = L8 < q8 ? (L8 % 8) * (total / 8) + L8 / 8 : L8;
   const int ntiles = 3 * a.nci * a.nco;
   int by = idx % ntiles;
   const int split = idx / ntiles;
-  const int co_t = by % a.nco;
+  const int co0 = by % a.nco * BM;
   by /= a.nco;
-  const int ci_t = by % a.nci;
+  const int ci0 = by % a.nci * 32;
   const int kd = by / a.nci;
-  const int co0 = co_t * BM, ci0 = ci_t * 32;
-  const int wp = a.wp, rr = a.r;
-  const int hc = (wp - 1) * S + 3, ncell = ((rr - 1) * S + 3) * hc;
 
-  // staging roles (fixed per thread): dy chunk (voxel, channel group)
-  int a_v[NAP], a_q[NAP];
-  bool a_on[NAP];
+  // load slots: dy chunk (id & 3) of voxel v of row r of channel half hf; x
+  // chunk of halo cell (plane p, row, column), for S = 2 with the cell's two
+  // 32-byte halves swapped by column so that the strided operand reads meet
+  // different banks.  Packed as row | column << 8 | plane << 16.
+  int adl[SA], apos[SA], xdl[SX], xpos[SX];
 #pragma unroll
-  for (int i = 0; i < NAP; ++i) {
-    const int id = tid + i * 256;
-    a_v[i] = id / (BM / 8);
-    a_q[i] = id % (BM / 8);
-    a_on[i] = id < NAC && co0 + a_q[i] * 8 < gy.c;
+  for (int i = 0; i < SA; ++i) {
+    const int id = (i * 4 + wave) * 64 + lane;
+    const int v = (id >> 2) % (RR * 32), hf = (id >> 2) / (RR * 32), r = v / 32, c = v % WP, p = v % 32 / WP;
+    const int ch = co0 + hf * 32 + (id & 3) * 8;
+    apos[i] = ch < gy.c ? r | c << 8 | p << 16 : -1;
+    adl[i] = ((p * gy.h + r) * gy.w + c) * gy.ldc + ch;
   }
-  int a_r[NAP], a_c[NAP];
 #pragma unroll
-  for (int i = 0; i < NAP; ++i) {
-    a_r[i] = (a_v[i] & (VS - 1)) / wp;
-    a_c[i] = (a_v[i] & (VS - 1)) % wp;
+  for (int i = 0; i < SX; ++i) {
+    const int id = (i * 4 + wave) * 64 + lane;
+    const int cell = id >> 2, p = cell / (HR * HC), r = cell / HC % HR, c = cell % HC;
+    const int q = S == 1 ? id & 3 : (id & 3) ^ (((c >> 2) & 1) << 1);
+    const int ch = ci0 + q * 8;
+    xpos[i] = cell < CELLS && ch < gx.c ? r | c << 8 | p << 16 : -1;
+    xdl[i] = ((p * S * gx.h + r) * gx.w + c) * gx.ldc + ch;
   }
-  // halo chunk (cell, channel group)
-  int x_hr[NXP], x_hc[NXP], x_q[NXP];
-  bool x_on[NXP];
+  // operand reads: 16-lane group g covers voxels 8 g .. 8 g + 7 of a row, half
+  // hh the voxels 8 g + 4 hh .. + 3; lane L addresses voxel L / 4, channels
+  // 4 (L % 4) .. + 3 of its 16
+  const int L = lane & 15, g = lane >> 4;
+  const int jsub = wave & 1, rk = KS == 2 ? (wave >> 1) * RW : 0, cs = KS == 2 ? 0 : wave >> 1;
+  int aoff[2], xoff[S == 1 ? 1 : 3][2];
 #pragma unroll
-  for (int i = 0; i < NXP; ++i) {
-    const int id = tid + i * 256;
-    const int cell = id >> 2;
-    x_on[i] = cell < ncell;
-    x_hr[i] = cell / hc;
-    x_hc[i] = cell % hc;
-    x_q[i] = id & 3;
-  }
-  // operand read offsets: 16-lane group g covers voxels 8g..8g+7, half h
-  // the rows 8g+4h .. +3; lane L of the group addresses row L/4, columns
-  // (L%4)*4 .. +3 of its 16-column block
-  const int L = lane & 15, g = lane >> 4, jsub = wave & 1;
-  int aoff[NSUB][2], xoff[2];
+  for (int hh = 0; hh < 2; ++hh) {
+    const int v = 8 * g + 4 * hh + (L >> 2), c = v % WP, p = v / WP;
+    aoff[hh] = (cs * (RR * 32) + rk * 32 + v) * 32 + (L & 3) * 4;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int v = 8 * g + 4 * h + (L >> 2);
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i) aoff[i][h] = v * PA + ((wave >> 1) * NSUB + i) * 16 + (L & 3) * 4;
-    xoff[h] = ((v / wp) * S * hc + (v % wp) * S) * PC + jsub * 16 + (L & 3) * 4;
+    for (int k = 0; k < (S == 1 ? 1 : 3); ++k) {
+      const int cc = c * S + k;
+      const int sub = S == 1 ? jsub : jsub ^ ((cc >> 2) & 1);
+      xoff[k][hh] = ((p * HR + rk * S) * HC + cc) * 32 + sub * 16 + (L & 3) * 4;
+    }
   }
 
   const __amdgpu_buffer_rsrc_t rx = rsrc_of(a.x, a.x_bytes);
   const __amdgpu_buffer_rsrc_t rd = rsrc_of(a.dy, a.dy_bytes);
   const int s_begin = split * a.per_wg;
   const int s_end = s_begin + a.per_wg < a.steps ? s_begin + a.per_wg : a.steps;
-  // uniform step coordinates, advanced without branches
-  int st = s_begin;
-  int wb = st % a.nwb, hb = (st / a.nwb) % a.nhb, pl = st / (a.nwb * a.nhb);
-  int nn = pl / gy.d, dd = pl % gy.d;
-  auto advance = [&]() {
-    ++wb;
-    const int c1 = wb == a.nwb;
-    wb = c1 ? 0 : wb;
-    hb += c1;
-    const int c2 = hb == a.nhb;
-    hb = c2 ? 0 : hb;
-    dd += c2;
-    const int c3 = dd == gy.d;
-    dd = c3 ? 0 : dd;
-    nn += c3;
-  };
-  u32x4 ar[NAP], xr[NXP];
-  auto load_step = [&](unsigned dead) {
-    const int h0 = hb * rr, w0 = wb * wp;
-#pragma unroll
-    for (int i = 0; i < NAP; ++i) {
-      const int hh = h0 + a_r[i], ww = w0 + a_c[i];
-      const bool ok = a_on[i] && hh < gy.h && ww < gy.w;
-      const unsigned vo =
-          (unsigned)((((nn * gy.d + dd) * gy.h + hh) * gy.w + ww) * gy.ldc + co0 + a_q[i] * 8) * 2u | (ok ? 0u : OOB);
-      ar[i] = __builtin_amdgcn_raw_buffer_load_b128(rd, vo | dead, 0, 0);
-    }
-    const int zs = dd * S + kd - 1, ys0 = h0 * S - 1, xs0 = w0 * S - 1;
-    const bool zok = zs >= 0 && zs < gx.d;
-#pragma unroll
-    for (int i = 0; i < NXP; ++i) {
-      const int ys = ys0 + x_hr[i], xs = xs0 + x_hc[i];
-      const bool ok = x_on[i] && zok && ys >= 0 && ys < gx.h && xs >= 0 && xs < gx.w;
-      const unsigned vo =
-          (unsigned)((((nn * gx.d + zs) * gx.h + ys) * gx.w + xs) * gx.ldc + ci0 + x_q[i] * 8) * 2u | (ok ? 0u : OOB);
-      xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, vo | dead, 0, 0);
-    }
-  };
-  auto store_step = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < NAP; ++i)
-      if (tid + i * 256 < NAC) *(u32x4*)(&As[buf][(a_v[i] & (VS - 1)) * PA + a_q[i] * 8]) = ar[i];
-#pragma unroll
-    for (int i = 0; i < NXP; ++i)
-      if (x_on[i]) *(u32x4*)(&Xs[buf][(x_hr[i] * hc + x_hc[i]) * PC + x_q[i] * 8]) = xr[i];
-  };
+  const int ndb = (gy.d + DP - 1) / DP;
+  int db = s_begin % ndb, pl = s_begin / ndb;
+  int wb = pl % a.nwb, hb = pl / a.nwb % a.nhb, nn = pl / (a.nwb * a.nhb);
 
-  f32x4 acc[NSUB][9];
+  f32x4 acc[2][9];
 #pragma unroll
-  for (int i = 0; i < NSUB; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // bias: thread sums channel b_ch over voxels b_v0 .. b_v0 + 32/BG - 1 of each step
   constexpr int BG = 256 / BM;
-  const bool do_bias = a.db != nullptr && kd == 0 && ci_t == 0;
-  const int b_ch = tid % BM, b_v0 = (tid / BM) * (VS / BG);
+  const bool do_bias = a.db != nullptr && kd == 0 && ci0 == 0;
+  const int b_ch = tid % BM, b_v0 = tid / BM * (RR * 32 / BG);
   float bsum = 0.f;
 
-  if (s_begin < s_end) {
-    load_step(0u);
-    store_step(0);
-    __syncthreads();
-  }
-  int buf = 0;
-  for (; st < s_end; ++st) {
-    advance();
-    load_step(st + 1 < s_end ? 0u : OOB);
-    __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the MFMAs
-    const uint16_t* A = As[buf];
-    const uint16_t* X = Xs[buf];
-    // K chunk c: voxels 32c..32c+31 of the step (with VS = 64 the second
-    // 32-voxel row: dy rows +32, halo rows +1)
+  for (int st = s_begin; st < s_end; ++st) {
+    const int d0 = db * DP, h0 = hb * RR, w0 = wb * WP;
+    const int ab = ((nn * gy.d + d0) * gy.h + h0) * gy.w * gy.ldc + w0 * gy.ldc;
+    const int zs = d0 * S + kd - 1, ys = h0 * S - 1, xs = w0 * S - 1;
+    const int xb = ((nn * gx.d + zs) * gx.h + ys) * gx.w * gx.ldc + xs * gx.ldc;
+    __syncthreads();  // the previous step's readers are done
 #pragma unroll
-    for (int c = 0; c < NK; ++c) {
-      bf16x8 af[NSUB];
+    for (int i = 0; i < SA; ++i) {
+      const int r = apos[i] & 255, c = apos[i] >> 8 & 255, p = apos[i] >> 16;
+      const bool ok = apos[i] >= 0 && h0 + r < gy.h && w0 + c < gy.w && d0 + p < gy.d;
+      lds_dma16(rd, As + (i * 4 + wave) * 512, ok ? (unsigned)(ab + adl[i]) * 2u : OOB, 0);
+    }
 #pragma unroll
-      for (int i = 0; i < NSUB; ++i) af[i] = tr_load8(A, aoff[i][0] + c * 32 * PA, aoff[i][1] + c * 32 * PA);
+    for (int i = 0; i < SX; ++i)
+      if (i * 4 + wave < NXI) {
+        const int r = xpos[i] & 255, c = xpos[i] >> 8 & 255, p = xpos[i] >> 16;
+        const int z = zs + p * S;
+        const bool ok = xpos[i] >= 0 && (unsigned)(ys + r) < (unsigned)gx.h && (unsigned)(xs + c) < (unsigned)gx.w &&
+                        (unsigned)z < (unsigned)gx.d;
+        lds_dma16(rx, Xs + (i * 4 + wave) * 512, ok ? (unsigned)(xb + xdl[i]) * 2u : OOB, 0);
+      }
+    ++db;
+    const int c1 = db == ndb;
+    db = c1 ? 0 : db;
+    wb += c1;
+    const int c2 = wb == a.nwb;
+    wb = c2 ? 0 : wb;
+    hb += c2;
+    const int c3 = hb == a.nhb;
+    hb = c3 ? 0 : hb;
+    nn += c3;
+    __syncthreads();  // (waits for the loads)
+    bf16x8 af[RW][2];
+    // an x row serves every tap row kh whose dy row it meets
 #pragma unroll
-      for (int kh = 0; kh < 3; ++kh)
+    for (int xr = 0; xr < (RW - 1) * S + 3; ++xr) {
+      if (xr % S == 0 && xr / S < RW) {
 #pragma unroll
-        for (int kw = 0; kw < 3; ++kw) {
-          const int to = (kh * hc + kw) * PC + c * S * hc * PC;
-          const bf16x8 bfr = tr_load8(X, xoff[0] + to, xoff[1] + to);
+        for (int i = 0; i < 2; ++i)
+          af[xr / S][i] = tr_load8(As, aoff[0] + xr / S * 1024 + i * 16, aoff[1] + xr / S * 1024 + i * 16);
+      }
 #pragma unroll
-          for (int i = 0; i < NSUB; ++i)
-            acc[i][kh * 3 + kw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr, acc[i][kh * 3 + kw], 0, 0, 0);
+      for (int kw = 0; kw < 3; ++kw) {
+        const int to = xr * HC * 32 + (S == 1 ? kw * 32 : 0);
+        const bf16x8 bfr = tr_load8(Xs, xoff[S == 1 ? 0 : kw][0] + to, xoff[S == 1 ? 0 : kw][1] + to);
+#pragma unroll
+        for (int kh = 0; kh < 3; ++kh) {
+          if (xr - kh < 0 || (xr - kh) % S != 0 || (xr - kh) / S >= RW) continue;
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            acc[i][kh * 3 + kw] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[(xr - kh) / S][i], bfr, acc[i][kh * 3 + kw], 0, 0, 0);
         }
+      }
     }
     if (do_bias) {
-#pragma unroll
-      for (int j = 0; j < VS / BG; ++j) bsum += __uint_as_float((unsigned)A[(b_v0 + j) * PA + b_ch] << 16);
+#pragma unroll 8
+      for (int j = 0; j < RR * 32 / BG; ++j)
+        bsum += bf2f(As[((b_ch >> 5) * (RR * 32) + b_v0 + j) * 32 + (b_ch & 31)]);
     }
-    store_step(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
   }
-  // lane holds D[(lane/16)*4 + q][lane%16] of each tile: rows co, columns ci
-  const int cin = gx.c;
+  if constexpr (KS == 2) {
+    // the second pair of waves hands its sums over through LDS
+    __syncthreads();
+    f32x4* red = (f32x4*)Xs + (wave & 1) * (18 * 64) + lane;
+    static_assert(2 * 18 * 64 * 16 <= (kX + kA) * 2, "the sums fit");
+    if (wave >= 2) {
 #pragma unroll
-  for (int i = 0; i < NSUB; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int co = co0 + ((wave >> 1) * NSUB + i) * 16 + g * 4 + q;
-      if (co >= gy.c) continue;
-      const int ci = ci0 + jsub * 16 + L;
-#pragma unroll
-      for (int t = 0; t < 9; ++t) atomicAdd(a.dw + (long long)co * a.kpad + (kd * 9 + t) * cin + ci, acc[i][t][q]);
+        for (int t = 0; t < 9; ++t) red[(i * 9 + t) * 64] = acc[i][t];
     }
+    __syncthreads();
+    if (wave < 2) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[i][t] += red[(i * 9 + t) * 64];
+    }
+  }
+  // lane holds D[4 g + q][L] of each tile: rows co, columns ci
+  const int cin = gx.c, ci = ci0 + jsub * 16 + L;
+  if ((KS == 1 || wave < 2) && ci < cin) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int co = co0 + (cs * 2 + i) * 16 + g * 4 + q;
+        if (co >= gy.c) continue;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) atomicAdd(a.dw + (long long)co * a.kpad + (kd * 9 + t) * cin + ci, acc[i][t][q]);
+      }
+  }
   if (do_bias && co0 + b_ch < gy.c) atomicAdd(a.db + co0 + b_ch, bsum);
 }
 
@@ -1085,7 +1090,7 @@ __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t Xs[2][(CELLS + 1) * PC];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const Geo gx = a.gx, gy = a.gy;
-  // XCD-aware work index (see k_conv_wgrad_halo)
+  // XCD-aware work index (see k_conv_wgrad_rows)
   const int total = (int)gridDim.x, L8 = (int)blockIdx.x;
   const int q8 = total / 8 * 8;
   const int idx = L8 < q8 ? (L8 % 8) * (total / 8) + L8 / 8 : L8;
@@ -1514,6 +1519,41 @@ bool launch_rows(const DArgs& a, hipStream_t s) {
   return true;
 }
 
+// Weight gradients of 3x3x3 layers by row steps: the grid holds about 768
+// workgroups (three per compute unit, see the kernel), each at least 12 x 128
+// voxels.
+template <int S, int BM, int WP>
+void launch_wgrad_rows_t(WArgs a, hipStream_t s) {
+  constexpr int RR = BM == 32 ? 8 : 4, DP = 32 / WP;
+  a.nhb = (a.gy.h + RR - 1) / RR;
+  a.nwb = (a.gy.w + WP - 1) / WP;
+  const long long steps = (long long)a.gy.n * ((a.gy.d + DP - 1) / DP) * a.nhb * a.nwb;
+  a.nco = (a.gy.c + BM - 1) / BM;
+  a.nci = (a.gx.c + 31) / 32;
+  const long long tiles = 3ll * a.nci * a.nco;
+  const long long per = std::max<long long>((steps * tiles + 767) / 768, 12 * 4 / RR);
+  a.steps = (int)steps;
+  a.per_wg = (int)per;
+  hipLaunchKernelGGL((k_conv_wgrad_rows<S, BM, WP>), dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(256), 0, s,
+                     a);
+}
+
+template <int S, int BM>
+void launch_wgrad_rows(const WArgs& a, hipStream_t s) {
+  // voxels of a row along w: what pads the volume least, the longest of equals
+  auto padded = [&](int wp) {
+    const int dp = 32 / wp;
+    return (long long)((a.gy.w + wp - 1) / wp) * wp * ((a.gy.d + dp - 1) / dp) * dp;
+  };
+  const long long p32 = padded(32), p16 = padded(16), p8 = padded(8);
+  if (p32 <= p16 && p32 <= p8)
+    launch_wgrad_rows_t<S, BM, 32>(a, s);
+  else if (p16 <= p8)
+    launch_wgrad_rows_t<S, BM, 16>(a, s);
+  else
+    launch_wgrad_rows_t<S, BM, 8>(a, s);
+}
+
 int grid1(long long n) {
   long long g = (n + 255) / 256;
   if (g > 65536) g = 65536;
@@ -1623,7 +1663,8 @@ lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, fl
   hipStream_t s = (hipStream_t)stream;
   const dim3 b(256);
   const bool wfit = dy->w >= 32 ? true : (32 % dy->w) == 0;
-  if (ksize == 3 && x->c % 32 == 0 && wfit && tap_fits(x) && tap_fits(dy) && V < (1ll << 31)) {
+  const bool fits = tap_fits(x) && tap_fits(dy) && V < (1ll << 31);
+  if (ksize == 3 && fits && !(stride == 1 && x->c == 8 && wfit)) {
     WArgs a{};
     a.x = (const uint16_t*)x->ptr;
     a.gx = geo_of(x);
@@ -1634,54 +1675,18 @@ lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, fl
     a.dw = dw;
     a.db = dbias;
     a.kpad = kpad;
-    // steps of several 32-voxel rows with rows of 32 voxels or more
-    const bool vs64 = dy->w >= 32;
-    const int vs = !vs64 ? 32 : (stride == 2 ? 64 : 128);
-    a.wp = dy->w >= 32 ? 32 : dy->w;
-    a.r = vs / a.wp;
-    a.nhb = (dy->h + a.r - 1) / a.r;
-    a.nwb = (dy->w + a.wp - 1) / a.wp;
-    const long long steps = (long long)dy->n * dy->d * a.nhb * a.nwb;
-    const int bmw = dy->c <= 32 ? 32 : 64;
-    a.nco = (dy->c + bmw - 1) / bmw;
-    a.nci = x->c / 32;
-    const long long tiles = 3ll * a.nci * a.nco;
-    // About 2048 workgroups in all, and at least 48 voxel steps each: every
-    // workgroup ends with BM x 288 FP32 atomics into dw, which dominate the
-    // layers of few voxels when their work is split finer (measured on
-    // gfx950, batch 8: 16x8x8 256->256 0.170 -> 0.115 ms, 32x16x16 128->128
-    // 0.186 -> 0.158 ms; the full-resolution layers already take 96-384
-    // steps per workgroup and lose with fewer workgroups).
-    long long per = (steps * tiles + 2047) / 2048;
-    if (per < 48 * 32 / vs) per = 48 * 32 / vs;
-    const long long splits = (steps + per - 1) / per;
-    a.steps = (int)steps;
-    a.per_wg = (int)per;
-    const dim3 g((unsigned)(splits * tiles));
-    if (vs64 && stride == 1) {
-      if (bmw == 32)
-        hipLaunchKernelGGL((k_conv_wgrad_halo<1, 32, 128>), g, b, 0, s, a);
-      else
-        hipLaunchKernelGGL((k_conv_wgrad_halo<1, 64, 128>), g, b, 0, s, a);
-    } else if (vs64) {
-      if (bmw == 32)
-        hipLaunchKernelGGL((k_conv_wgrad_halo<2, 32, 64>), g, b, 0, s, a);
-      else
-        hipLaunchKernelGGL((k_conv_wgrad_halo<2, 64, 64>), g, b, 0, s, a);
-    } else if (stride == 1) {
-      if (bmw == 32)
-        hipLaunchKernelGGL((k_conv_wgrad_halo<1, 32>), g, b, 0, s, a);
-      else
-        hipLaunchKernelGGL((k_conv_wgrad_halo<1, 64>), g, b, 0, s, a);
-    } else {
-      if (bmw == 32)
-        hipLaunchKernelGGL((k_conv_wgrad_halo<2, 32>), g, b, 0, s, a);
-      else
-        hipLaunchKernelGGL((k_conv_wgrad_halo<2, 64>), g, b, 0, s, a);
-    }
+    // 32-channel output tiles where 64 would be half empty; stride 2, whose
+    // halos leave one workgroup per compute unit with them, always takes 64
+    const bool half = dy->c % 64 > 0 && dy->c % 64 <= 32;
+    if (stride == 2)
+      launch_wgrad_rows<2, 64>(a, s);
+    else if (half)
+      launch_wgrad_rows<1, 32>(a, s);
+    else
+      launch_wgrad_rows<1, 64>(a, s);
     return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
   }
-  if (ksize == 3 && stride == 1 && x->c == 8 && wfit && tap_fits(x) && tap_fits(dy) && V < (1ll << 31)) {
+  if (ksize == 3 && fits) {
     WArgs a{};
     a.x = (const uint16_t*)x->ptr;
     a.gx = geo_of(x);

@@ -109,3 +109,36 @@ def test_forward_does_not_depend_on_the_tile_sizes():
         X1, Y1 = S.from_numpy(x[3:4]), S.Act(1, d, h, w, co)
         layer.forward(X1, Y1)
         assert np.array_equal(Y.to_numpy()[3:4], Y1.to_numpy())
+
+
+# weight gradients: rows of 32, 16 and 8 voxels (one, two and four planes, a
+# partial last group of planes), partial rows and row blocks, channel tiles of
+# 32 and 64 (partial ones), channels off 32, both strides, one voxel, and a
+# volume that is split over several workgroups
+WGRADS = [
+    dict(n=1, d=1, h=1, w=1, ci=16, co=8),
+    dict(n=2, d=3, h=5, w=31, ci=24, co=40),
+    dict(n=1, d=5, h=9, w=16, ci=40, co=64),
+    dict(n=1, d=7, h=3, w=7, ci=32, co=72),
+    dict(n=2, d=4, h=17, w=33, ci=32, co=32),
+    dict(n=1, d=5, h=7, w=9, ci=40, co=24, s=2),
+    dict(n=1, d=9, h=6, w=33, ci=32, co=72, s=2),
+    dict(n=1, d=3, h=9, w=65, ci=16, co=64, s=2),
+    dict(n=2, d=16, h=32, w=32, ci=32, co=32),
+]
+
+
+@pytest.mark.parametrize("case", range(len(WGRADS)))
+def test_weight_gradient_row_steps(case):
+    from paper_1007_1388_amd import surrogate as S
+    c = WGRADS[case]
+    s = c.get("s", 1)
+    x, w, b, dy = _operands(c, 300 + case)
+    layer = S.Conv(c["ci"], c["co"], stride=s)
+    layer.zero_grad()
+    layer.backward(_sliced(S, x, 8, 16), _sliced(S, dy, 16, 24), None)
+    dw, db = conv.conv3d_bwd_weight(x, dy, 3, s)
+    gw = layer.gw.cpu().numpy()
+    assert np.abs(gw[:, :27 * c["ci"]].reshape(dw.shape) - dw).max() <= 1e-5 * np.abs(dw).max()
+    assert np.all(gw[:, 27 * c["ci"]:] == 0)
+    assert np.abs(layer.gb.cpu().numpy() - db).max() <= 1e-5 * np.abs(db).max()
