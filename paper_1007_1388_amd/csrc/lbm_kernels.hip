@@ -1162,15 +1162,15 @@ __global__ void __launch_bounds__(256) k_bbfill(void* grid_, CellArgs A, const P
   });
 }
 
-// Open faces (on one axis a; t1 < t2 the two other axes).  The side buffer
-// holds, per face (low, high) and face cell (s1, s2) at [face][s2][s1], 16
-// doubles: the post-collision populations of the five directions that enter
-// the domain through the face (slot k: the k-th direction i in increasing
-// order with e_a(i) = +1 on the low face, -1 on the high face), then
-// drho, u_x, u_y, u_z of the cell's collision, then zeros (one 128-byte line
-// per cell).
-__device__ __forceinline__ int ecomp(int axis, int i) { return axis == 0 ? kEx[i] : (axis == 1 ? kEy[i] : kEz[i]); }
-__device__ __forceinline__ int enter_dir(int axis, int sign, int slot) {
+// Open faces (on one axis a; t1 < t2 the two other axes).  The side buffer of
+// open x faces holds, per face (low, high) and face cell (s1, s2) at
+// [face][s2][s1], 16 doubles that the sweep writes: the post-collision
+// populations of the five directions that enter the domain through the face
+// (slot k: the k-th direction i in increasing order with e_a(i) = +1 on the
+// low face, -1 on the high face), then drho, u_x, u_y, u_z of the cell's
+// collision, then zeros (one 128-byte line per cell).
+__host__ __device__ constexpr int ecomp(int axis, int i) { return axis == 0 ? EXd(i) : (axis == 1 ? EYd(i) : EZd(i)); }
+__host__ __device__ constexpr int enter_dir(int axis, int sign, int slot) {
   int k = 0;
   for (int i = 1; i < kQ; ++i)
     if (ecomp(axis, i) == sign) {
@@ -1179,118 +1179,121 @@ __device__ __forceinline__ int enter_dir(int axis, int sign, int slot) {
     }
   return 0;
 }
-__device__ __forceinline__ void tangential(int a, int& t1, int& t2) {
-  t1 = a == 0 ? 1 : 0;
-  t2 = a == 2 ? 1 : 2;
-}
+template <int A, int SIGN, int SLOT>
+struct EnterDir {
+  static constexpr int q = enter_dir(A, SIGN, SLOT);
+};
 
 // Once per step after the sweep (and after a state is loaded): the boundary
-// nodes beyond the open faces from the face cells' entries in `side` (the
-// moments of their collision, as the boundary rule asks).  A boundary node
-// one cell beyond face f at tangential position (g1, g2) feeds the face
-// cells around it, so its value goes into the ghost layer of every Block on
-// that face whose ghost layer, tangential ghost cells included, covers it:
-// the Block that owns the face cell, the face Blocks next to it, and on a
-// periodic tangential axis the Blocks that hold its periodic image.  In a
-// Block the node lies in the main arrays' ghost rows (y faces) or planes
-// (z faces) or, for x faces and past a Block's x ends, in the x-ghost plane
-// of the directions that pull from there.  One thread per node position
-// (g1, g2) in [-1, n1] x [-1, n2] of each face; nodes beyond a wall are left
-// to the sweep's bounce-back.  faceblk: per face the count of Blocks
-// touching it, then their ids (stride 1 + nblocks).
-template <int PREC>
-__global__ void __launch_bounds__(256) k_openfill(void* grid_, const BlockDev* __restrict__ blocks, int nblocks,
-                                                  const int* __restrict__ faceblk, GridGeom geo,
-                                                  const double* __restrict__ side) {
+// nodes beyond the open faces of axis A.  A boundary node one cell beyond face
+// f at tangential position (g1, g2) feeds the face cells around it, so its
+// value goes into the ghost layer of every Block on that face whose ghost
+// layer, tangential ghost cells included, covers it: the Block that owns the
+// face cell, the face Blocks next to it, and on a periodic tangential axis the
+// Blocks that hold its periodic image.  In a Block the node lies in the main
+// arrays' ghost rows (y faces) or planes (z faces) or, for x faces and past a
+// Block's x ends, in the x-ghost plane of the directions that pull from there.
+// One thread per node position (g1, g2) in [-1, n1] x [-1, n2] of each face;
+// nodes beyond a wall are left to the sweep's bounce-back.  faceblk: per face
+// the count of Blocks touching it, then their ids (stride 1 + nblocks).
+// SIDE: the face cells' moments and entering populations come from the side
+// buffer (x faces after a sweep, which keeps those of its collision).  Without,
+// they are rebuilt from the cell's 19 stored post-collision populations (drho =
+// sum f~, u = sum e f~ / rho0 - g/2: the collision invariants, so the moments of
+// its last collision up to rounding): y and z faces, and x faces of a state
+// loaded from outside.
+// Bound by latency: a chain of the Block list, a Block, the populations and
+// the stores, on few threads.  Rebuilding here instead of in a pass of its own
+// through the side buffer, with the directions resolved at compile time, took a
+// 257x126x93 duct in 8 Blocks from 15 + 21 to 7.5 us per step (149 -> 120 in all).
+template <int PREC, int A, int SIGN, bool SIDE>
+__device__ __forceinline__ void open_node(typename Stor<PREC>::T* grid, const BlockDev* __restrict__ blocks,
+                                          const int* __restrict__ list, const GridGeom& geo,
+                                          const double* __restrict__ side, int g1, int g2) {
   using T = typename Stor<PREC>::T;
-  T* grid = (T*)grid_;
-  const int a = geo.open_axis;
-  int t1, t2;
-  tangential(a, t1, t2);
+  constexpr int t1 = A == 0 ? 1 : 0, t2 = A == 2 ? 1 : 2, f = 2 * A + (SIGN > 0 ? 0 : 1);
+  constexpr int Q[5] = {EnterDir<A, SIGN, 0>::q, EnterDir<A, SIGN, 1>::q, EnterDir<A, SIGN, 2>::q,
+                        EnterDir<A, SIGN, 3>::q, EnterDir<A, SIGN, 4>::q};
   const int n1 = geo.n[t1], n2 = geo.n[t2];
-  const int per_face = (n1 + 2) * (n2 + 2);
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a < 0 || t >= 2 * per_face) return;
-  const int fs = t / per_face, r = t % per_face;
-  const int f = 2 * a + fs;
-  if (!geo.open[f]) return;
-  const int g1 = r % (n1 + 2) - 1, g2 = r / (n1 + 2) - 1;
-  if ((g1 < 0 || g1 >= n1) && geo.wall[t1]) return;
-  if ((g2 < 0 || g2 >= n2) && geo.wall[t2]) return;
   const int s1 = g1 < 0 ? g1 + n1 : (g1 >= n1 ? g1 - n1 : g1);
   const int s2 = g2 < 0 ? g2 + n2 : (g2 >= n2 ? g2 - n2 : g2);
-  const double* cs = side + 16 * ((long long)fs * n1 * n2 + (long long)s2 * n1 + s1);
-  const double d = cs[5], ux = cs[6], uy = cs[7], uz = cs[8];
-  const int sign = fs == 0 ? 1 : -1;
-  T v[5];
-  for (int slot = 0; slot < 5; ++slot) {
-    const int q = enter_dir(a, sign, slot);
-    v[slot] = from_c<PREC, double>(cs[slot] + open_corr(geo, f, q, geo.rho0, d, ux, uy, uz));
-  }
-  const int* list = faceblk + fs * (1 + nblocks);
-  for (int k = 0; k < list[0]; ++k) {
-    const BlockDev& M = blocks[list[1 + k]];
-    int l[3];
-    l[a] = fs == 0 ? -1 : M.dim[a];
-    l[t1] = g1 - M.org[t1];
-    l[t2] = g2 - M.org[t2];
-    if (l[t1] < -1 || l[t1] > M.dim[t1] || l[t2] < -1 || l[t2] > M.dim[t2]) continue;
-    for (int slot = 0; slot < 5; ++slot) {
-      const int q = enter_dir(a, sign, slot);
-      if (l[0] >= 0 && l[0] < M.dim[0])
-        grid[main_off(M, q, l[0], l[1], l[2])] = v[slot];
-      else if ((l[0] < 0 && kEx[q] == 1) || (l[0] >= M.dim[0] && kEx[q] == -1))
-        grid[xg_off(M, q, l[1], l[2])] = v[slot];
+  const int nlist = list[0];
+  double in[5], d, ux, uy, uz;
+  if constexpr (SIDE) {
+    const double* cs = side + 16 * ((long long)(SIGN > 0 ? 0 : 1) * n1 * n2 + (long long)s2 * n1 + s1);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) in[k] = cs[k];
+    d = cs[5], ux = cs[6], uy = cs[7], uz = cs[8];
+  } else {
+    double fi[kQ];
+    for (int k = 0; k < nlist; ++k) {
+      const BlockDev& B = blocks[list[1 + k]];
+      int l[3];
+      l[A] = SIGN > 0 ? 0 : B.dim[A] - 1;
+      l[t1] = s1 - B.org[t1];
+      l[t2] = s2 - B.org[t2];
+      if (l[t1] < 0 || l[t1] >= B.dim[t1] || l[t2] < 0 || l[t2] >= B.dim[t2]) continue;
+      const T* c = grid + main_off(B, 0, l[0], l[1], l[2]);
+      const long long Sf = B.Sf;
+#pragma unroll
+      for (int i = 0; i < kQ; ++i) fi[i] = (double)to_c<PREC, double>(c[i * Sf]);
+      break;
     }
-  }
-}
-
-// The face cells' entries of `side` rebuilt from their stored post-collision
-// populations (drho = sum f~, u = sum e f~ / rho0 - g/2: the collision
-// invariants, so the moments of their last collision up to rounding): after
-// every sweep for y and z faces, after a state is loaded for x faces (whose
-// entries the sweep writes itself).  One thread per face cell (FP64).
-template <int PREC>
-__global__ void __launch_bounds__(256) k_openside(const void* grid_, const BlockDev* __restrict__ blocks,
-                                                  int nblocks, const int* __restrict__ faceblk, GridGeom geo,
-                                                  double* __restrict__ side) {
-  using T = typename Stor<PREC>::T;
-  const T* grid = (const T*)grid_;
-  const int a = geo.open_axis;
-  int t1, t2;
-  tangential(a, t1, t2);
-  const int n1 = geo.n[t1], n2 = geo.n[t2];
-  const int per_face = n1 * n2;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a < 0 || t >= 2 * per_face) return;
-  const int fs = t / per_face, r = t % per_face;
-  if (!geo.open[2 * a + fs]) return;
-  const int g1 = r % n1, g2 = r / n1;
-  const int sign = fs == 0 ? 1 : -1;
-  const int* list = faceblk + fs * (1 + nblocks);
-  for (int k = 0; k < list[0]; ++k) {
-    const BlockDev& B = blocks[list[1 + k]];
-    int l[3];
-    l[a] = fs == 0 ? 0 : B.dim[a] - 1;
-    l[t1] = g1 - B.org[t1];
-    l[t2] = g2 - B.org[t2];
-    if (l[t1] < 0 || l[t1] >= B.dim[t1] || l[t2] < 0 || l[t2] >= B.dim[t2]) continue;
-    double fi[kQ], dr = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
+    double jx = 0.0, jy = 0.0, jz = 0.0;
+    d = 0.0;
+#pragma unroll
     for (int i = 0; i < kQ; ++i) {
-      fi[i] = (double)to_c<PREC, double>(grid[main_off(B, i, l[0], l[1], l[2])]);
-      dr += fi[i];
+      d += fi[i];
       jx += EXd(i) * fi[i];
       jy += EYd(i) * fi[i];
       jz += EZd(i) * fi[i];
     }
-    double* cs = side + 16 * ((long long)fs * per_face + r);
-    for (int slot = 0; slot < 5; ++slot) cs[slot] = fi[enter_dir(a, sign, slot)];
-    cs[5] = dr;
-    cs[6] = jx / geo.rho0 - geo.hg[0];
-    cs[7] = jy / geo.rho0 - geo.hg[1];
-    cs[8] = jz / geo.rho0 - geo.hg[2];
-    for (int j = 9; j < 16; ++j) cs[j] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) in[k] = fi[Q[k]];
+    ux = jx / geo.rho0 - geo.hg[0];
+    uy = jy / geo.rho0 - geo.hg[1];
+    uz = jz / geo.rho0 - geo.hg[2];
   }
+  T v[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) v[k] = from_c<PREC, double>(in[k] + open_corr(geo, f, Q[k], geo.rho0, d, ux, uy, uz));
+  for (int k = 0; k < nlist; ++k) {
+    const BlockDev& M = blocks[list[1 + k]];
+    int l[3];
+    l[A] = SIGN > 0 ? -1 : M.dim[A];
+    l[t1] = g1 - M.org[t1];
+    l[t2] = g2 - M.org[t2];
+    if (l[t1] < -1 || l[t1] > M.dim[t1] || l[t2] < -1 || l[t2] > M.dim[t2]) continue;
+    const bool lo = l[0] < 0, hi = l[0] >= M.dim[0];
+    const long long m0 = main_off(M, 0, l[0], l[1], l[2]), x0 = xg_off(M, 0, l[1], l[2]);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      if (!lo && !hi)
+        grid[m0 + Q[j] * M.Sf] = v[j];
+      else if ((lo && EXd(Q[j]) == 1) || (hi && EXd(Q[j]) == -1))
+        grid[x0 + Q[j] * M.Sf] = v[j];
+    }
+  }
+}
+
+template <int PREC, int A, bool SIDE>
+__global__ void __launch_bounds__(256) k_openfill(void* grid_, const BlockDev* __restrict__ blocks, int nblocks,
+                                                  const int* __restrict__ faceblk, GridGeom geo,
+                                                  const double* __restrict__ side) {
+  using T = typename Stor<PREC>::T;
+  constexpr int t1 = A == 0 ? 1 : 0, t2 = A == 2 ? 1 : 2;
+  const int n1 = geo.n[t1], n2 = geo.n[t2];
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  const int fs = blockIdx.y;  // low, high face
+  if (t >= (n1 + 2) * (n2 + 2) || !geo.open[2 * A + fs]) return;
+  const int g1 = t % (n1 + 2) - 1, g2 = t / (n1 + 2) - 1;
+  if ((g1 < 0 || g1 >= n1) && geo.wall[t1]) return;
+  if ((g2 < 0 || g2 >= n2) && geo.wall[t2]) return;
+  const int* list = faceblk + fs * (1 + nblocks);
+  if (fs == 0)
+    open_node<PREC, A, 1, SIDE>((T*)grid_, blocks, list, geo, side, g1, g2);
+  else
+    open_node<PREC, A, -1, SIDE>((T*)grid_, blocks, list, geo, side, g1, g2);
 }
 
 // f~ = feq~(rho - rho0, u) of Eq. (2) in FP64 (warm start), 0 in solid cells.
@@ -1634,37 +1637,31 @@ void launch_bbfill(int prec, bool f64math, void* grid, const CellArgs& a, const 
   }
 }
 
-// node positions (openfill) or face cells (openside) of both open faces
-static int open_threads(const GridGeom& geo, int ghost) {
-  const int a = geo.open_axis;
-  if (a < 0) return 0;
-  const int t1 = a == 0 ? 1 : 0, t2 = a == 2 ? 1 : 2;
-  return 2 * (geo.n[t1] + 2 * ghost) * (geo.n[t2] + 2 * ghost);
+template <int PREC>
+static void launch_openfill_t(void* grid, const BlockDev* blocks, int nblocks, const int* faceblk, const GridGeom& geo,
+                              const double* side, hipStream_t s) {
+  const int a = geo.open_axis, t1 = a == 0 ? 1 : 0, t2 = a == 2 ? 1 : 2;
+  const dim3 g(((geo.n[t1] + 2) * (geo.n[t2] + 2) + 255) / 256, 2), b(256);
+  if (a == 0 && side)
+    hipLaunchKernelGGL((k_openfill<PREC, 0, true>), g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side);
+  else if (a == 0)
+    hipLaunchKernelGGL((k_openfill<PREC, 0, false>), g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side);
+  else if (a == 1)
+    hipLaunchKernelGGL((k_openfill<PREC, 1, false>), g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side);
+  else
+    hipLaunchKernelGGL((k_openfill<PREC, 2, false>), g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side);
 }
 
+// side: the sweep's side buffer (open x faces after a sweep), or NULL to
+// rebuild the face cells' moments from their stored populations
 void launch_openfill(int prec, void* grid, const BlockDev* blocks, int nblocks, const int* faceblk,
                      const GridGeom& geo, const double* side, hipStream_t s) {
-  const int n = open_threads(geo, 1);
-  if (n == 0) return;
-  const dim3 g((n + 255) / 256), b(256);
+  if (geo.open_axis < 0) return;
   switch (prec) {
-    case 0: hipLaunchKernelGGL(k_openfill<0>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-    case 1: hipLaunchKernelGGL(k_openfill<1>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-    case 2: hipLaunchKernelGGL(k_openfill<2>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-    default: hipLaunchKernelGGL(k_openfill<3>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-  }
-}
-
-void launch_openside(int prec, const void* grid, const BlockDev* blocks, int nblocks, const int* faceblk,
-                     const GridGeom& geo, double* side, hipStream_t s) {
-  const int n = open_threads(geo, 0);
-  if (n == 0) return;
-  const dim3 g((n + 255) / 256), b(256);
-  switch (prec) {
-    case 0: hipLaunchKernelGGL(k_openside<0>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-    case 1: hipLaunchKernelGGL(k_openside<1>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-    case 2: hipLaunchKernelGGL(k_openside<2>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
-    default: hipLaunchKernelGGL(k_openside<3>, g, b, 0, s, grid, blocks, nblocks, faceblk, geo, side); break;
+    case 0: launch_openfill_t<0>(grid, blocks, nblocks, faceblk, geo, side, s); break;
+    case 1: launch_openfill_t<1>(grid, blocks, nblocks, faceblk, geo, side, s); break;
+    case 2: launch_openfill_t<2>(grid, blocks, nblocks, faceblk, geo, side, s); break;
+    default: launch_openfill_t<3>(grid, blocks, nblocks, faceblk, geo, side, s); break;
   }
 }
 

@@ -37,8 +37,6 @@ void launch_bbfill(int prec, bool f64math, void* grid, const CellArgs& a, const 
 void launch_linkmask(const uint8_t* solid, const CellArgs& a, uint32_t* mask, hipStream_t s);
 void launch_openfill(int prec, void* grid, const BlockDev* blocks, int nblocks, const int* faceblk,
                      const GridGeom& geo, const double* side, hipStream_t s);
-void launch_openside(int prec, const void* grid, const BlockDev* blocks, int nblocks, const int* faceblk,
-                     const GridGeom& geo, double* side, hipStream_t s);
 void launch_init_eq(int prec, void* grid, const CellArgs& a, double rho0, const double* rho, const double* u,
                     long long N, hipStream_t s);
 void launch_macro(int prec, const void* grid, const CellArgs& a, double rho0, const double hg[3], double* rho,
@@ -127,7 +125,7 @@ struct lbm_ctx {
   double* d_partial = nullptr;
   int nparts = 1024;
   double* d_red = nullptr;
-  double* d_side = nullptr;  // open faces: [face][s2][s1][16] over the two other axes (see k_openfill)
+  double* d_side = nullptr;  // open x faces: [face][z][y][16] (see k_openfill)
   int* d_faceblk = nullptr;  // open faces: per face the count of Blocks touching it, then their ids
   void* d_stage = nullptr;
   double* d_umark = nullptr;   // [rho | u_x | u_y | u_z] snapshot, FP64, 4 N
@@ -508,9 +506,7 @@ SweepArgs sweep_args(const lbm_ctx* c, int from) {
   a.items = c->d_items;
   a.mask = c->d_mask;
   a.ghost = c->d_ghost;
-  // the sweep writes the side entries of open x faces itself (y and z faces:
-  // k_openside after the sweep)
-  a.side = c->geo.open_axis == 0 ? c->d_side : nullptr;
+  a.side = c->d_side;  // open x faces: the sweep keeps its face cells' moments
   a.nitems = (int)c->items_h.size();
   a.geo = c->geo;
   if (hetero(c)) {
@@ -560,11 +556,8 @@ bool has_open(const lbm_ctx* c);
 // from outside the sweep (the nodes from the face cells' stored populations).
 void enqueue_slots(lbm_ctx* c, int g, hipStream_t s) {
   launch_bbfill(c->prec, c->f64math, c->grid[g], cell_args(c), c->phd, c->phf, s);
-  if (has_open(c)) {
-    const int nb = (int)c->bh.size();
-    launch_openside(c->prec, c->grid[g], c->d_blocks, nb, c->d_faceblk, c->geo, c->d_side, s);
-    launch_openfill(c->prec, c->grid[g], c->d_blocks, nb, c->d_faceblk, c->geo, c->d_side, s);
-  }
+  if (has_open(c))
+    launch_openfill(c->prec, c->grid[g], c->d_blocks, (int)c->bh.size(), c->d_faceblk, c->geo, nullptr, s);
 }
 
 // Ghost layers and bounce-back slots of a state written from outside the sweep.
@@ -603,12 +596,8 @@ bool has_open(const lbm_ctx* c) { return c->geo.open_axis >= 0; }
 // and the boundary nodes of open faces.
 void enqueue_post(lbm_ctx* c, int g, hipStream_t s) {
   if (c->sched.fused_exchange != 1) enqueue_exchange(c, g, s, c->sched.fused_exchange == 2);
-  if (has_open(c)) {
-    const int nb = (int)c->bh.size();
-    if (c->geo.open_axis != 0)
-      launch_openside(c->prec, c->grid[g], c->d_blocks, nb, c->d_faceblk, c->geo, c->d_side, s);
-    launch_openfill(c->prec, c->grid[g], c->d_blocks, nb, c->d_faceblk, c->geo, c->d_side, s);
-  }
+  if (has_open(c))
+    launch_openfill(c->prec, c->grid[g], c->d_blocks, (int)c->bh.size(), c->d_faceblk, c->geo, c->d_side, s);
 }
 
 void enqueue_step(lbm_ctx* c, int from, hipStream_t s) {
@@ -1358,13 +1347,10 @@ lbm_status lbm_create_blocks(const lbm_params* p, const lbm_aabb* blocks, int32_
   c->d_rim = (XchgTask*)dalloc(c, sizeof(XchgTask) * std::max<size_t>(1, c->rim_h.size()));
   c->d_partial = (double*)dalloc(c, sizeof(double) * 6 * c->nparts);
   c->d_red = (double*)dalloc(c, sizeof(double) * 8);
-  if (open_axis >= 0) {
-    const int t1 = open_axis == 0 ? 1 : 0, t2 = open_axis == 2 ? 1 : 2;
-    c->d_side = (double*)dalloc(c, sizeof(double) * 32 * (size_t)p->dims[t1] * p->dims[t2]);
-  }
-    c->d_faceblk = (int*)dalloc(c, sizeof(int) * 2 * (1 + (size_t)nblocks));
+  if (open_axis == 0) c->d_side = (double*)dalloc(c, sizeof(double) * 32 * (size_t)p->dims[1] * p->dims[2]);
+  c->d_faceblk = (int*)dalloc(c, sizeof(int) * 2 * (1 + (size_t)nblocks));
   if (!c->grid[0] || !c->grid[1] || !c->d_blocks || !c->d_nbr || !c->d_ghost || !c->d_tasks || !c->d_rim ||
-      !c->d_partial || !c->d_red || (open_axis >= 0 && (!c->d_side || !c->d_faceblk)))
+      !c->d_partial || !c->d_red || (open_axis == 0 && !c->d_side) || (open_axis >= 0 && !c->d_faceblk))
     return bail(LBM_ENOMEM, "device allocation failed");
   if (hipMemcpy(c->d_blocks, c->bh.data(), sizeof(BlockDev) * nblocks, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(c->d_nbr, c->nbh.data(), sizeof(NbrDev) * c->nbh.size(), hipMemcpyHostToDevice) != hipSuccess ||
