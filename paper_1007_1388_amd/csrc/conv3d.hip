@@ -1282,34 +1282,71 @@ __global__ void __launch_bounds__(256) k_weight_t(const float* __restrict__ w, i
     if ((int)(q % kpad_t) >= taps * cout) wt[q] = 0;
 }
 
+// Nearest-neighbour 2x upsampling and its adjoint.  A thread owns the 8
+// channels (16 bytes) of one coarse voxel: one load and eight stores, or eight
+// loads and one store; consecutive threads walk the channels, then w, so the
+// two fine voxels of a pair along w are written (read) as whole lines.  One
+// workgroup per 256 of a row's (w, channel group) pairs, rows by blockIdx.y
+// (strided past the grid limit), so the row's coordinates are uniform.  Bound
+// by HBM.  Measured on gfx950, batch 8, 64 channels to (from) 128x64x64, against
+// one fine voxel's chunk (adjoint: one channel) per thread: upsampling 165 ->
+// 109 us, adjoint 333 -> 112 us (5.4 TB/s).
+__device__ __forceinline__ void coarse_row(const Geo& g, int row, int& n, int& d, int& h) {
+  h = row % g.h;
+  const int r = row / g.h;
+  d = r % g.d;
+  n = r / g.d;
+}
+
 __global__ void __launch_bounds__(256) k_up2(const uint16_t* __restrict__ x, Geo gx, uint16_t* __restrict__ y,
                                              Geo gy) {
-  const long long V = (long long)gy.n * gy.d * gy.h * gy.w;
-  const int cv = gy.c / 8;
-  for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < V * cv; q += (long long)gridDim.x * blockDim.x) {
-    const long long v = q / cv;
-    const int c8 = (int)(q % cv) * 8;
-    int n, d, h, w;
-    unvox(gy, v, n, d, h, w);
-    *(u32x4*)(y + v * gy.ldc + c8) = *(const u32x4*)(x + vox(gx, n, d >> 1, h >> 1, w >> 1) * gx.ldc + c8);
+  const int cv = gx.c / 8, q = blockIdx.x * 256 + threadIdx.x;
+  if (q >= gx.w * cv) return;
+  const int w = q / cv, c8 = (q - w * cv) * 8;
+  const int rows = gx.n * gx.d * gx.h;
+  for (int row = blockIdx.y; row < rows; row += gridDim.y) {
+    int n, d, h;
+    coarse_row(gx, row, n, d, h);
+    const u32x4 v = *(const u32x4*)(x + ((long long)row * gx.w + w) * gx.ldc + c8);
+    uint16_t* o = y + vox(gy, n, 2 * d, 2 * h, 2 * w) * gy.ldc + c8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      *(u32x4*)(o + (((long long)(j >> 2) * gy.h + ((j >> 1) & 1)) * gy.w + (j & 1)) * gy.ldc) = v;
   }
 }
 
 __global__ void __launch_bounds__(256) k_up2_bwd(const uint16_t* __restrict__ dy, Geo gy, uint16_t* __restrict__ dx,
                                                  Geo gx, int accumulate) {
-  const long long V = (long long)gx.n * gx.d * gx.h * gx.w;
-  for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < V * gx.c; q += (long long)gridDim.x * blockDim.x) {
-    const long long v = q / gx.c;
-    const int c = (int)(q % gx.c);
-    int n, d, h, w;
-    unvox(gx, v, n, d, h, w);
-    float s = 0.f;
-    for (int j = 0; j < 8; ++j) {
-      const int dd = 2 * d + (j >> 2), hh = 2 * h + ((j >> 1) & 1), ww = 2 * w + (j & 1);
-      if (dd < gy.d && hh < gy.h && ww < gy.w) s += bf2f(dy[vox(gy, n, dd, hh, ww) * gy.ldc + c]);
+  const int cv = gx.c / 8, q = blockIdx.x * 256 + threadIdx.x;
+  if (q >= gx.w * cv) return;
+  const int w = q / cv, c8 = (q - w * cv) * 8;
+  const int rows = gx.n * gx.d * gx.h;
+  for (int row = blockIdx.y; row < rows; row += gridDim.y) {
+    int n, d, h;
+    coarse_row(gx, row, n, d, h);
+    const uint16_t* p = dy + vox(gy, n, 2 * d, 2 * h, 2 * w) * gy.ldc + c8;
+    u32x4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      v[j] = *(const u32x4*)(p + (((long long)(j >> 2) * gy.h + ((j >> 1) & 1)) * gy.w + (j & 1)) * gy.ldc);
+    u32x4* o = (u32x4*)(dx + ((long long)row * gx.w + w) * gx.ldc + c8);
+    u32x4 prev = u32x4{0u, 0u, 0u, 0u}, out;
+    if (accumulate) prev = *o;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float lo = 0.f, hi = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        lo += __uint_as_float(v[j][k] << 16);
+        hi += __uint_as_float(v[j][k] & 0xffff0000u);
+      }
+      if (accumulate) {
+        lo += __uint_as_float(prev[k] << 16);
+        hi += __uint_as_float(prev[k] & 0xffff0000u);
+      }
+      out[k] = (unsigned)f2bf(lo) | (unsigned)f2bf(hi) << 16;
     }
-    if (accumulate) s += bf2f(dx[v * gx.ldc + c]);
-    dx[v * gx.ldc + c] = f2bf(s);
+    *o = out;
   }
 }
 
@@ -1554,6 +1591,12 @@ void launch_wgrad_rows(const WArgs& a, hipStream_t s) {
     launch_wgrad_rows_t<S, BM, 8>(a, s);
 }
 
+// Rows (n, d, h) by y, (w, channel group) pairs by x.
+dim3 grid_rows(const lbm_tensor5* t) {
+  const long long rows = (long long)t->n * t->d * t->h;
+  return dim3((unsigned)(((long long)t->w * (t->c / 8) + 255) / 256), (unsigned)std::min<long long>(rows, 65535));
+}
+
 int grid1(long long n) {
   long long g = (n + 255) / 256;
   if (g > 65536) g = 65536;
@@ -1748,8 +1791,7 @@ lbm_status lbm_upsample2(const lbm_tensor5* x, const lbm_tensor5* y, void* strea
   if (!tensor_ok(x) || !tensor_ok(y) || y->n != x->n || y->c != x->c || y->d != 2 * x->d || y->h != 2 * x->h ||
       y->w != 2 * x->w)
     return LBM_EINVAL;
-  const long long n = (long long)y->n * y->d * y->h * y->w * (y->c / 8);
-  hipLaunchKernelGGL(k_up2, dim3(grid1(n)), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)x->ptr, geo_of(x),
+  hipLaunchKernelGGL(k_up2, grid_rows(x), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)x->ptr, geo_of(x),
                      (uint16_t*)y->ptr, geo_of(y));
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
@@ -1758,8 +1800,7 @@ lbm_status lbm_upsample2_bwd(const lbm_tensor5* dy, const lbm_tensor5* dx, int32
   if (!tensor_ok(dy) || !tensor_ok(dx) || dy->n != dx->n || dy->c != dx->c || dy->d != 2 * dx->d ||
       dy->h != 2 * dx->h || dy->w != 2 * dx->w)
     return LBM_EINVAL;
-  const long long n = (long long)dx->n * dx->d * dx->h * dx->w * dx->c;
-  hipLaunchKernelGGL(k_up2_bwd, dim3(grid1(n)), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)dy->ptr,
+  hipLaunchKernelGGL(k_up2_bwd, grid_rows(dx), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)dy->ptr,
                      geo_of(dy), (uint16_t*)dx->ptr, geo_of(dx), accumulate);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
