@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "../../include/lbm_surrogate.h"
 
@@ -824,6 +825,133 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
   }
 }
 
+// --------------------------------------------- fwd / bwd-data, 1x1x1 layers
+// The pointwise products (either direction: rows = voxels, K = the gathered
+// channels).  A wave takes 64 consecutive voxels (four 16-voxel operands) and
+// 32 columns; the operands are direct 16-byte loads, whole lines of the
+// channels-last rows, all of a chunk's issued before its MFMAs.  A wave's
+// weights of the chunk come from L1.  No LDS: no value is used twice.  Bound by
+// HBM.  Measured on gfx950 at 8 x 128x64x64: 32->8 forward 127 -> 70 us, its input
+// gradient 233 -> 104 (against the tap-major and the general kernel).
+__global__ void __launch_bounds__(256) k_conv_point(DArgs a) {
+  constexpr unsigned OOB = 0x80000000u;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int L = lane & 15, g = lane >> 4;
+  const Geo go = a.go;
+  const int V = go.n * go.d * go.h * go.w;
+  const int v0 = (blockIdx.x * 4 + wave) * 64 + L, n0 = blockIdx.y * 32;
+  const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.src, a.src_bytes);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wk, a.wk_bytes);
+  unsigned xo[4], wo[2];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) xo[f] = v0 + f * 16 < V ? (unsigned)((v0 + f * 16) * a.gs.ldc + g * 8) * 2u : OOB;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int col = n0 + (L >> 2) * 8 + j * 4 + (L & 3);  // weight rows as in k_conv_rows
+    wo[j] = col < go.c ? (unsigned)(col * a.kstride + g * 8) * 2u : OOB;
+  }
+  f32x4 acc[4][2];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) acc[f][0] = acc[f][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < a.C; c0 += 32) {
+    const unsigned dead = c0 + g * 8 < a.C ? 0u : OOB;
+    u32x4 x[4], w[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) w[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, wo[j] | dead, c0 * 2, 0);
+#pragma unroll
+    for (int f = 0; f < 4; ++f) x[f] = __builtin_amdgcn_raw_buffer_load_b128(rs, xo[f] | dead, c0 * 2, 0);
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]),
+                                                            __builtin_bit_cast(bf16x8, x[f]), acc[f][j], 0, 0, 0);
+  }
+  const int col = n0 + g * 8;
+  if (col >= go.c) return;
+#pragma unroll
+  for (int f = 0; f < 4; ++f)
+    if (v0 + f * 16 < V) store8(a, v0 + f * 16, col, acc[f][0], acc[f][1]);
+}
+
+// -------------------------------------- forward, stride 1, 3x3x3, 8 channels
+// The input layer.  K = tap * 8 + channel, four taps per MFMA (lane group g of
+// step s: tap 4 s + g; the 28th is zeros), seven steps in all, whose weights a
+// wave keeps in registers.  A workgroup owns 16 x 16 voxels of kPl planes and 32
+// output channels: it brings the kPl + 2 source planes' halos into LDS (16-byte
+// cells, LDS-direct loads) once; wave v takes rows 4 v .. 4 v + 3 of every plane.
+// A voxel operand is one LDS read per lane, at the lane's own tap.  Bound by the
+// stores of its 32 channels.  Measured on gfx950 at 8 x 128x64x64: 346 -> 110 us
+// against the general kernel, which gathered every tap from memory.
+__global__ void __launch_bounds__(256) k_conv_fwd_c8(DArgs a) {
+  constexpr int kPl = 4, HC = 18, HR = 18, CELLS = (kPl + 2) * HR * HC;
+  constexpr int NXI = (CELLS + 63) / 64, SX = (NXI + 3) / 4;
+  constexpr unsigned OOB = 0x80000000u;
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[NXI * 512 + 8];  // the last cell: zeros
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Geo gs = a.gs, go = a.go;
+  const int total = (int)gridDim.x, id0 = (int)blockIdx.x, q8 = total / 8 * 8;
+  int bx = id0 < q8 ? (id0 % 8) * (total / 8) + id0 / 8 : id0;
+  const int nct = (go.c + 31) / 32, nwb = (go.w + 15) / 16, nhb = (go.h + 15) / 16, ndb = (go.d + kPl - 1) / kPl;
+  const int n0 = bx % nct * 32;
+  bx /= nct;
+  const int w0 = bx % nwb * 16;
+  bx /= nwb;
+  const int h0 = bx % nhb * 16;
+  bx /= nhb;
+  const int d0 = bx % ndb * kPl, n = bx / ndb;
+  const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.src, a.src_bytes);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wk, a.wk_bytes);
+#pragma unroll
+  for (int i = 0; i < SX; ++i)
+    if (i * 4 + wave < NXI) {
+      const int cell = (i * 4 + wave) * 64 + lane;
+      const int p = cell / (HR * HC), r = cell / HC % HR, c = cell % HC;
+      const int ds = d0 - 1 + p, hs = h0 - 1 + r, ws = w0 - 1 + c;
+      const bool ok = cell < CELLS && ds >= 0 && ds < gs.d && hs >= 0 && hs < gs.h && ws >= 0 && ws < gs.w;
+      lds_dma16(rs, Xs + (i * 4 + wave) * 512,
+                ok ? (unsigned)((((n * gs.d + ds) * gs.h + hs) * gs.w + ws) * gs.ldc) * 2u : OOB, 0);
+    }
+  if (tid == 0) *(u32x4*)(Xs + NXI * 512) = u32x4{0u, 0u, 0u, 0u};
+  const int L = lane & 15, g = lane >> 4;
+  bf16x8 wf[7][2];
+#pragma unroll
+  for (int s = 0; s < 7; ++s)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + (L >> 2) * 8 + j * 4 + (L & 3);
+      const unsigned wo = col < go.c ? (unsigned)(col * a.kstride + s * 32 + g * 8) * 2u : OOB;
+      wf[s][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, wo, 0, 0));
+    }
+  int xo[7];  // cell of the lane's tap, relative to the output voxel's row and plane
+#pragma unroll
+  for (int s = 0; s < 7; ++s) {
+    const int t = 4 * s + g;
+    xo[s] = ((t / 9 * HR + t / 3 % 3) * HC + t % 3 + L) * 8;
+  }
+  const bool none = g == 3;  // tap 27 of the last step
+  __syncthreads();  // (waits for the loads)
+  const int w = w0 + L, col = n0 + g * 8;
+  for (int p = 0; p < kPl; ++p) {
+    if (d0 + p >= go.d) break;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int h = h0 + wave * 4 + r;
+      const int base = (p * HR + wave * 4 + r) * HC * 8;
+      f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int s = 0; s < 7; ++s) {
+        const int at = s == 6 && none ? NXI * 512 : base + xo[s];
+        const bf16x8 xf = *(const bf16x8*)(Xs + at);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][j], xf, acc[j], 0, 0, 0);
+      }
+      if (h < go.h && w < go.w && col < go.c)
+        store8(a, (((long long)n * go.d + d0 + p) * go.h + h) * go.w + w, col, acc[0], acc[1]);
+    }
+  }
+}
+
 // ------------------------------------------------------- bwd-weight operands
 struct WArgs {
   const uint16_t* x;
@@ -835,7 +963,6 @@ struct WArgs {
   float* dw;
   float* db;            // bias gradient, or nullptr
   int kpad;
-  int wp, r;            // k_conv_wgrad_c8: step shape, R rows of W' voxels
   int nhb, nwb;         // steps per column of rows / per row
   int steps, per_wg;    // total steps, steps per workgroup
   int nco, nci;         // output / input channel tiles
@@ -1067,167 +1194,227 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1
 
 // --------------------------------- bwd-weight, 3x3x3, 8 input channels
 // dw[co][tap*8 + ci] += sum_v dy[v][co] * x[src(v, tap)][ci] for the input
-// layer (8 channels, stride 1): all 27 taps of a 32-output-channel tile in
-// one workgroup, the 216 columns as 14 MFMA column tiles of two taps x 8
-// channels (the last holds tap 26 and zeros).  Per 32-voxel step (R rows of
-// W' voxels, as above) it stages the dy tile [32 voxels][32 channels] and the
-// x halo of the three source planes [3][R+2 rows][W'+2 columns][8 channels];
-// ds_read_b64_tr_b16 takes one address per lane, so each lane of a B
-// fragment points at the tap of its half of the tile's columns, and both
-// operands are transposing LDS reads.  Wave w owns output-channel tile w % 2
-// and column tiles w/2, w/2 + 2, ..., w/2 + 12 (seven MFMA tiles).  With db
-// given every workgroup also sums its dy tiles (each once per channel tile).
+// layer (8 channels, stride 1): all 27 taps of a 32-output-channel tile in one
+// workgroup, the 216 columns as 14 MFMA column tiles of two taps x 8 channels
+// (the last holds tap 26 and zeros).  Steps are rows of 32 voxels as in
+// k_conv_wgrad_rows; per step the dy tile [32 RR voxels][32 channels] and the x
+// halo of all source planes (16-byte cells) come into LDS by direct loads.
+// ds_read_b64_tr_b16 takes one address per lane, so each lane of an x operand
+// points at the tap of its half of the tile's columns.  Wave v owns both
+// 16-channel halves of dy and the column tiles v, v + 4, v + 8, v + 12: six reads
+// for eight MFMAs of a row.  With db given the dy tiles are summed from LDS
+// (each once per channel tile).  Bound by LDS reads, then by the atomics (see
+// wgrad_splits).  Measured on gfx950 at 8 x 128x64x64, 8->32: 384 -> 225 us
+// against steps of one row staged through registers.
+template <int WP>
 __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
-  constexpr int BC = 32;                 // output channels per tile
-  constexpr int PA = BC + 8;             // dy tile row pitch (bf16)
-  constexpr int PC = 8;                  // halo cell: 8 channels
-  constexpr int PLANE = 102;             // largest (R+2)(W'+2) over the step shapes
-  constexpr int CELLS = 3 * PLANE;
-  constexpr int ZERO = CELLS * PC;       // a cell of zeros (the missing 28th tap)
-  constexpr int NXP = (CELLS + 255) / 256;
+  constexpr int RR = 8, DP = 32 / WP;
+  constexpr int HR = RR + 2, HC = WP + 2, CELLS = (DP + 2) * HR * HC;
+  constexpr int NXI = (CELLS + 63) / 64, NAI = RR * 2;  // wave-wide 16-byte loads of x and dy
+  constexpr int SX = (NXI + 3) / 4, SA = NAI / 4;
+  constexpr int ZERO = NXI * 512;                       // a cell of zeros (the missing 28th tap)
   constexpr unsigned OOB = 0x80000000u;
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][32 * PA];
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][(CELLS + 1) * PC];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __attribute__((aligned(1024))) uint16_t As[NAI * 512];
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[NXI * 512 + 8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const Geo gx = a.gx, gy = a.gy;
   // XCD-aware work index (see k_conv_wgrad_rows)
-  const int total = (int)gridDim.x, L8 = (int)blockIdx.x;
-  const int q8 = total / 8 * 8;
+  const int total = (int)gridDim.x, L8 = (int)blockIdx.x, q8 = total / 8 * 8;
   const int idx = L8 < q8 ? (L8 % 8) * (total / 8) + L8 / 8 : L8;
-  const int co_t = idx % a.nco, split = idx / a.nco;
-  const int co0 = co_t * BC;
-  const int wp = a.wp, rr = a.r;
-  const int hc = wp + 2, hr = rr + 2, pcells = hr * hc, ncell = 3 * pcells;
-  if (tid < 2 * PC / 8) *(u32x4*)(&Xs[tid][ZERO]) = u32x4{0u, 0u, 0u, 0u};
+  const int co0 = idx % a.nco * 32, split = idx / a.nco;
+  if (tid == 0) *(u32x4*)(Xs + ZERO) = u32x4{0u, 0u, 0u, 0u};
 
-  // staging roles: dy chunk (voxel, 8-channel group), threads 0..127
-  const bool a_act = tid < 32 * BC / 8;
-  const int a_v = tid / (BC / 8), a_q = tid % (BC / 8);
-  const bool a_on = a_act && co0 + a_q * 8 < gy.c;
-  const int a_r = (a_v & 31) / wp, a_c = (a_v & 31) % wp;
-  // halo cell (plane, row, column)
-  int x_p[NXP], x_hr[NXP], x_hc[NXP];
-  bool x_on[NXP];
+  // load slots (row | column << 8 | plane << 16, -1: none)
+  int adl[SA], apos[SA], xdl[SX], xpos[SX];
 #pragma unroll
-  for (int i = 0; i < NXP; ++i) {
-    const int cell = tid + i * 256;
-    x_on[i] = cell < ncell;
-    x_p[i] = cell / pcells;
-    x_hr[i] = (cell % pcells) / hc;
-    x_hc[i] = cell % hc;
+  for (int i = 0; i < SA; ++i) {
+    const int id = (i * 4 + wave) * 64 + lane;
+    const int v = id >> 2, r = v / 32, c = v % WP, p = v % 32 / WP, ch = co0 + (id & 3) * 8;
+    apos[i] = ch < gy.c ? r | c << 8 | p << 16 : -1;
+    adl[i] = ((p * gy.h + r) * gy.w + c) * gy.ldc + ch;
   }
-  // operand read offsets (16-lane group g covers voxels 8g..8g+7, half h the
-  // rows 8g+4h..+3; lane L addresses row L/4, columns (L%4)*4..+3)
-  const int L = lane & 15, g = lane >> 4;
-  const int cot = wave & 1, kt0 = wave >> 1;
-  const int hi = (L & 3) >> 1, cio = (L & 1) * 4;
-  int aoff[2], xb[2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int v = 8 * g + 4 * h + (L >> 2);
-    aoff[h] = v * PA + cot * 16 + (L & 3) * 4;
-    xb[h] = ((v / wp) * hc + (v % wp)) * PC + cio;
+  for (int i = 0; i < SX; ++i) {
+    const int cell = (i * 4 + wave) * 64 + lane;
+    const int p = cell / (HR * HC), r = cell / HC % HR, c = cell % HC;
+    xpos[i] = cell < CELLS ? r | c << 8 | p << 16 : -1;
+    xdl[i] = ((p * gx.h + r) * gx.w + c) * gx.ldc;
   }
-  // per column tile j of this wave: the lane's tap and its halo offset
-  int toff[7];
-  bool tzero[7];
+  // operand reads (16-lane group g covers voxels 8 g .. 8 g + 7 of a row, half
+  // hh the voxels 8 g + 4 hh .. + 3; lane L addresses voxel L / 4, columns
+  // 4 (L % 4) .. + 3 of its 16)
+  const int L = lane & 15, g = lane >> 4, cio = (L & 1) * 4;
+  int aoff[2], xv[2];
 #pragma unroll
-  for (int j = 0; j < 7; ++j) {
-    const int t = 2 * (kt0 + 2 * j) + hi;
-    tzero[j] = t >= 27;
-    const int tt = tzero[j] ? 0 : t;
-    toff[j] = ((tt / 9) * pcells + ((tt / 3) % 3) * hc + tt % 3) * PC;
+  for (int hh = 0; hh < 2; ++hh) {
+    const int v = 8 * g + 4 * hh + (L >> 2);
+    aoff[hh] = v * 32 + (L & 3) * 4;
+    xv[hh] = (v / WP * HR * HC + v % WP) * 8 + cio;
+  }
+  int toff[4];  // the lane's tap of each column tile, -1: none
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int t = 2 * (wave + 4 * j) + ((L & 3) >> 1);
+    toff[j] = t < 27 ? ((t / 9 * HR + t / 3 % 3) * HC + t % 3) * 8 : -1;
   }
 
   const __amdgpu_buffer_rsrc_t rx = rsrc_of(a.x, a.x_bytes);
   const __amdgpu_buffer_rsrc_t rd = rsrc_of(a.dy, a.dy_bytes);
   const int s_begin = split * a.per_wg;
   const int s_end = s_begin + a.per_wg < a.steps ? s_begin + a.per_wg : a.steps;
-  int st = s_begin;
-  int wb = st % a.nwb, hb = (st / a.nwb) % a.nhb, pl = st / (a.nwb * a.nhb);
-  int nn = pl / gy.d, dd = pl % gy.d;
-  auto advance = [&]() {
-    ++wb;
-    const int c1 = wb == a.nwb;
-    wb = c1 ? 0 : wb;
-    hb += c1;
-    const int c2 = hb == a.nhb;
-    hb = c2 ? 0 : hb;
-    dd += c2;
-    const int c3 = dd == gy.d;
-    dd = c3 ? 0 : dd;
-    nn += c3;
-  };
-  u32x4 ar, xr[NXP];
-  auto load_step = [&](unsigned dead) {
-    const int h0 = hb * rr, w0 = wb * wp;
-    {
-      const int hh = h0 + a_r, ww = w0 + a_c;
-      const bool ok = a_on && hh < gy.h && ww < gy.w;
-      const unsigned vo =
-          (unsigned)((((nn * gy.d + dd) * gy.h + hh) * gy.w + ww) * gy.ldc + co0 + a_q * 8) * 2u | (ok ? 0u : OOB);
-      ar = __builtin_amdgcn_raw_buffer_load_b128(rd, vo | dead, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < NXP; ++i) {
-      const int zs = dd + x_p[i] - 1, ys = h0 - 1 + x_hr[i], xs = w0 - 1 + x_hc[i];
-      const bool ok = x_on[i] && zs >= 0 && zs < gx.d && ys >= 0 && ys < gx.h && xs >= 0 && xs < gx.w;
-      const unsigned vo = (unsigned)((((nn * gx.d + zs) * gx.h + ys) * gx.w + xs) * gx.ldc) * 2u | (ok ? 0u : OOB);
-      xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, vo | dead, 0, 0);
-    }
-  };
-  auto store_step = [&](int buf) {
-    if (a_act) *(u32x4*)(&As[buf][(a_v & 31) * PA + a_q * 8]) = ar;
-#pragma unroll
-    for (int i = 0; i < NXP; ++i)
-      if (x_on[i]) *(u32x4*)(&Xs[buf][(x_p[i] * pcells + x_hr[i] * hc + x_hc[i]) * PC]) = xr[i];
-  };
+  const int ndb = (gy.d + DP - 1) / DP;
+  int db = s_begin % ndb, pl = s_begin / ndb;
+  int wb = pl % a.nwb, hb = pl / a.nwb % a.nhb, nn = pl / (a.nwb * a.nhb);
 
-  f32x4 acc[7];
+  f32x4 acc[2][4];
 #pragma unroll
-  for (int j = 0; j < 7; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const bool do_bias = a.db != nullptr;
-  const int b_ch = tid % BC, b_v0 = (tid / BC) * 4;
   float bsum = 0.f;
 
-  if (s_begin < s_end) {
-    load_step(0u);
-    store_step(0);
-    __syncthreads();
-  }
-  int buf = 0;
-  for (; st < s_end; ++st) {
-    advance();
-    load_step(st + 1 < s_end ? 0u : OOB);
-    __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the MFMAs
-    const uint16_t* A = As[buf];
-    const uint16_t* X = Xs[buf];
-    const bf16x8 af = tr_load8(A, aoff[0], aoff[1]);
+  for (int st = s_begin; st < s_end; ++st) {
+    const int d0 = db * DP, h0 = hb * RR, w0 = wb * WP;
+    const int ab = ((nn * gy.d + d0) * gy.h + h0) * gy.w * gy.ldc + w0 * gy.ldc;
+    const int xb = ((nn * gx.d + d0 - 1) * gx.h + h0 - 1) * gx.w * gx.ldc + (w0 - 1) * gx.ldc;
+    __syncthreads();  // the previous step's readers are done
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-      const bf16x8 bfr = tr_load8(X, tzero[j] ? ZERO + cio : xb[0] + toff[j], tzero[j] ? ZERO + cio : xb[1] + toff[j]);
-      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc[j], 0, 0, 0);
+    for (int i = 0; i < SA; ++i) {
+      const int r = apos[i] & 255, c = apos[i] >> 8 & 255, p = apos[i] >> 16;
+      const bool ok = apos[i] >= 0 && h0 + r < gy.h && w0 + c < gy.w && d0 + p < gy.d;
+      lds_dma16(rd, As + (i * 4 + wave) * 512, ok ? (unsigned)(ab + adl[i]) * 2u : OOB, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < SX; ++i)
+      if (i * 4 + wave < NXI) {
+        const int r = xpos[i] & 255, c = xpos[i] >> 8 & 255, p = xpos[i] >> 16;
+        const bool ok = xpos[i] >= 0 && (unsigned)(h0 - 1 + r) < (unsigned)gx.h &&
+                        (unsigned)(w0 - 1 + c) < (unsigned)gx.w && (unsigned)(d0 - 1 + p) < (unsigned)gx.d;
+        lds_dma16(rx, Xs + (i * 4 + wave) * 512, ok ? (unsigned)(xb + xdl[i]) * 2u : OOB, 0);
+      }
+    ++db;
+    const int c1 = db == ndb;
+    db = c1 ? 0 : db;
+    wb += c1;
+    const int c2 = wb == a.nwb;
+    wb = c2 ? 0 : wb;
+    hb += c2;
+    const int c3 = hb == a.nhb;
+    hb = c3 ? 0 : hb;
+    nn += c3;
+    __syncthreads();  // (waits for the loads)
+#pragma unroll
+    for (int r = 0; r < RR; ++r) {
+      bf16x8 af[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) af[i] = tr_load8(As, aoff[0] + r * 1024 + i * 16, aoff[1] + r * 1024 + i * 16);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j == 3 && wave >= 2) continue;  // 14 column tiles
+        const int t = toff[j] + r * HC * 8;
+        const bf16x8 bfr = tr_load8(Xs, toff[j] < 0 ? ZERO + cio : xv[0] + t, toff[j] < 0 ? ZERO + cio : xv[1] + t);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr, acc[i][j], 0, 0, 0);
+      }
     }
     if (do_bias) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bsum += __uint_as_float((unsigned)A[(b_v0 + j) * PA + b_ch] << 16);
-    }
-    store_step(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
-  }
-  // lane holds D[(lane/16)*4 + q][lane%16] of each tile: rows co, columns k
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int co = co0 + cot * 16 + g * 4 + q;
-    if (co >= gy.c) continue;
-#pragma unroll
-    for (int j = 0; j < 7; ++j) {
-      const int k = (kt0 + 2 * j) * 16 + L;
-      if (k < 216) atomicAdd(a.dw + (long long)co * a.kpad + k, acc[j][q]);
+#pragma unroll 8
+      for (int j = 0; j < RR * 4; ++j) bsum += bf2f(As[(tid / 32 * (RR * 4) + j) * 32 + tid % 32]);
     }
   }
-  if (do_bias && co0 + b_ch < gy.c) atomicAdd(a.db + co0 + b_ch, bsum);
+  // lane holds D[4 g + q][L] of each tile: rows co, columns k
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int co = co0 + i * 16 + g * 4 + q;
+      if (co >= gy.c) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = (wave + 4 * j) * 16 + L;
+        if (k < 216) atomicAdd(a.dw + (long long)co * a.kpad + k, acc[i][j][q]);
+      }
+    }
+  if (do_bias && co0 + tid % 32 < gy.c) atomicAdd(a.db + co0 + tid % 32, bsum);
+}
+
+// ------------------------------------------------------- bwd-weight, 1x1x1
+// dw[co][ci] += sum_v dy[v][co] * x[v][ci] and db[co] += sum_v dy[v][co]: a
+// workgroup owns 32 output and 32 input channels and walks steps of 512
+// voxels, both tiles brought into LDS by direct loads (64-byte cells, zeros
+// past the channels); wave v multiplies voxels 64 v .. + 63, and the eight waves'
+// sums meet in LDS.  Bound by HBM (the channels are read once per tile of the
+// other side) and the atomics' queue at its few addresses.  Measured on gfx950 at 8 x 128x64x64, 32->8: 239 -> 142 us with
+// the bias, against the general kernel, which transposes by hand, and a bias
+// pass of its own.
+__global__ void __launch_bounds__(512) k_conv_wgrad_point(WArgs a) {
+  constexpr unsigned OOB = 0x80000000u;
+  __shared__ __attribute__((aligned(1024))) uint16_t As[512 * 32], Xs[512 * 32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Geo gx = a.gx, gy = a.gy;
+  const int V = gy.n * gy.d * gy.h * gy.w;
+  const int ntiles = a.nci * a.nco, split = blockIdx.x / ntiles, tile = blockIdx.x % ntiles;
+  const int co0 = tile % a.nco * 32, ci0 = tile / a.nco * 32;
+  const __amdgpu_buffer_rsrc_t rx = rsrc_of(a.x, a.x_bytes);
+  const __amdgpu_buffer_rsrc_t rd = rsrc_of(a.dy, a.dy_bytes);
+  const int q = (lane & 3) * 8;
+  const bool aok = co0 + q < gy.c, xok = ci0 + q < gx.c;
+  const int L = lane & 15, g = lane >> 4;
+  int off[2];
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) off[hh] = (wave * 64 + 8 * g + 4 * hh + (L >> 2)) * 32 + (L & 3) * 4;
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool do_bias = a.db != nullptr && ci0 == 0;
+  float bsum = 0.f;
+  const int s_end = (split + 1) * a.per_wg < a.steps ? (split + 1) * a.per_wg : a.steps;
+  for (int st = split * a.per_wg; st < s_end; ++st) {
+    __syncthreads();  // the previous step's readers are done
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int slot = i * 8 + wave, v = st * 512 + slot * 16 + (lane >> 2);
+      lds_dma16(rd, As + slot * 512, aok && v < V ? (unsigned)(v * gy.ldc + co0 + q) * 2u : OOB, 0);
+      lds_dma16(rx, Xs + slot * 512, xok && v < V ? (unsigned)(v * gx.ldc + ci0 + q) * 2u : OOB, 0);
+    }
+    __syncthreads();  // (waits for the loads)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      bf16x8 af[2], bx[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        af[i] = tr_load8(As, off[0] + c * 1024 + i * 16, off[1] + c * 1024 + i * 16);
+        bx[i] = tr_load8(Xs, off[0] + c * 1024 + i * 16, off[1] + c * 1024 + i * 16);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bx[j], acc[i][j], 0, 0, 0);
+    }
+    if (do_bias) {
+#pragma unroll 8
+      for (int j = 0; j < 32; ++j) bsum += bf2f(As[(tid / 32 * 32 + j) * 32 + tid % 32]);
+    }
+  }
+  float* T = (float*)Xs;  // [wave][32 co][32 ci]
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) T[(wave * 32 + i * 16 + g * 4 + k) * 32 + j * 16 + L] = acc[i][j][k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int e = k * 512 + tid, co = co0 + e / 32, ci = ci0 + e % 32;
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) t += T[w * 1024 + e];
+    if (co < gy.c && ci < gx.c) atomicAdd(a.dw + (long long)co * a.kpad + ci, t);
+  }
+  if (do_bias && co0 + tid % 32 < gy.c) atomicAdd(a.db + co0 + tid % 32, bsum);
 }
 
 // dbias[co] += sum_v dy[v][co]: a thread sums 8 channels (one 16-byte load
@@ -1519,6 +1706,18 @@ bool launch_plane(const DArgs& a, hipStream_t s) {
   return false;
 }
 
+// 1x1x1 layers onto at most 32 channels, or with channels off 32s; onto more,
+// the tap-major kernel's wider column tiles read the input fewer times (8 x
+// 32x16x16 256->128: 25.9 against 28.2 us).
+bool point_fits(int ksize, const lbm_tensor5* src, const lbm_tensor5* out) {
+  return ksize == 1 && (out->c <= 32 || src->c % 32 != 0);
+}
+
+void launch_point(const DArgs& a, hipStream_t s) {
+  const long long V = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
+  hipLaunchKernelGGL(k_conv_point, dim3((unsigned)((V + 255) / 256), (unsigned)((a.go.c + 31) / 32)), dim3(256), 0, s, a);
+}
+
 // Workgroups of the row-tile kernel with R rows per wave.
 template <int R>
 long long row_tiles(const Geo& go) {
@@ -1541,6 +1740,12 @@ template <int MODE>
 bool launch_rows(const DArgs& a, hipStream_t s) {
   const long long big = row_tiles<4>(a.go), small = row_tiles<2>(a.go);
   const long long vox = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
+  if (MODE == 0 && a.C == 8) {
+    const long long g = (long long)((a.go.w + 15) / 16) * ((a.go.h + 15) / 16) * ((a.go.d + 3) / 4) * a.go.n *
+                        ((a.go.c + 31) / 32);
+    hipLaunchKernelGGL(k_conv_fwd_c8, dim3((unsigned)g), dim3(256), 0, s, a);
+    return true;
+  }
   if ((a.go.w % 32 != 0 || a.go.c > 64) && launch_plane<MODE>(a, s)) return true;
   if (a.C % 32 == 0 && small * 128 > 4 * vox * ((a.go.c + 31) / 32)) return false;
   const bool four = big >= 256 && big * 2 <= small * 1.22, tail = a.C % 32 != 0;
@@ -1556,9 +1761,21 @@ bool launch_rows(const DArgs& a, hipStream_t s) {
   return true;
 }
 
+// Workgroups that share one tile of a weight gradient: at most `slots` in the
+// grid, c sqrt(steps) and a tenth of the steps per tile.  Each ends with one
+// atomic per value of the tile, and the memory side takes the atomics of one
+// address one after the other, about 0.16 us each: N of them cost a step's time
+// times steps / N plus 0.16 us times N (a 1x1x1 layer, 256 addresses in all:
+// 85 us with 512 workgroups, 44 with 113; batch 1 128x64x64 32->32: 129 us with
+// 342, 76 with 90).  Short of ten steps the tile's set-up and atomics outweigh
+// the MFMAs (batch 1 16x8x8 256->256, eight steps: 22 us undivided, 50 in eight).
+long long wgrad_splits(long long steps, long long tiles, long long slots, double c) {
+  const long long most = std::min<long long>((long long)(c * std::sqrt((double)steps)), steps / 10);
+  return std::max<long long>(1, std::min(slots / tiles, most));
+}
+
 // Weight gradients of 3x3x3 layers by row steps: the grid holds about 768
-// workgroups (three per compute unit, see the kernel), each at least 12 x 128
-// voxels.
+// workgroups (three per compute unit, see the kernel).
 template <int S, int BM, int WP>
 void launch_wgrad_rows_t(WArgs a, hipStream_t s) {
   constexpr int RR = BM == 32 ? 8 : 4, DP = 32 / WP;
@@ -1568,27 +1785,66 @@ void launch_wgrad_rows_t(WArgs a, hipStream_t s) {
   a.nco = (a.gy.c + BM - 1) / BM;
   a.nci = (a.gx.c + 31) / 32;
   const long long tiles = 3ll * a.nci * a.nco;
-  const long long per = std::max<long long>((steps * tiles + 767) / 768, 12 * 4 / RR);
+  const long long n = wgrad_splits(steps, tiles, 768, 2.0), per = (steps + n - 1) / n;
   a.steps = (int)steps;
   a.per_wg = (int)per;
   hipLaunchKernelGGL((k_conv_wgrad_rows<S, BM, WP>), dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(256), 0, s,
                      a);
 }
 
+// Voxels of a 32-voxel row along w: what pads the volume least, the longest of
+// equals.
+int row_voxels(const Geo& g) {
+  int best = 32;
+  long long least = -1;
+  for (int wp = 32; wp >= 8; wp /= 2) {
+    const int dp = 32 / wp;
+    const long long p = (long long)((g.w + wp - 1) / wp) * wp * ((g.d + dp - 1) / dp) * dp;
+    if (least < 0 || p < least) least = p, best = wp;
+  }
+  return best;
+}
+
 template <int S, int BM>
 void launch_wgrad_rows(const WArgs& a, hipStream_t s) {
-  // voxels of a row along w: what pads the volume least, the longest of equals
-  auto padded = [&](int wp) {
-    const int dp = 32 / wp;
-    return (long long)((a.gy.w + wp - 1) / wp) * wp * ((a.gy.d + dp - 1) / dp) * dp;
-  };
-  const long long p32 = padded(32), p16 = padded(16), p8 = padded(8);
-  if (p32 <= p16 && p32 <= p8)
-    launch_wgrad_rows_t<S, BM, 32>(a, s);
-  else if (p16 <= p8)
-    launch_wgrad_rows_t<S, BM, 16>(a, s);
-  else
-    launch_wgrad_rows_t<S, BM, 8>(a, s);
+  switch (row_voxels(a.gy)) {
+    case 32: launch_wgrad_rows_t<S, BM, 32>(a, s); break;
+    case 16: launch_wgrad_rows_t<S, BM, 16>(a, s); break;
+    default: launch_wgrad_rows_t<S, BM, 8>(a, s); break;
+  }
+}
+
+template <int WP>
+void launch_wgrad_c8_t(WArgs a, hipStream_t s) {
+  constexpr int DP = 32 / WP;
+  a.nhb = (a.gy.h + 7) / 8;
+  a.nwb = (a.gy.w + WP - 1) / WP;
+  const long long steps = (long long)a.gy.n * ((a.gy.d + DP - 1) / DP) * a.nhb * a.nwb;
+  a.nco = (a.gy.c + 31) / 32;
+  const long long n = wgrad_splits(steps, a.nco, 512, 2.0), per = (steps + n - 1) / n;
+  a.steps = (int)steps;
+  a.per_wg = (int)per;
+  hipLaunchKernelGGL(k_conv_wgrad_c8<WP>, dim3((unsigned)((steps + per - 1) / per * a.nco)), dim3(256), 0, s, a);
+}
+
+void launch_wgrad_c8(const WArgs& a, hipStream_t s) {
+  switch (row_voxels(a.gy)) {
+    case 32: launch_wgrad_c8_t<32>(a, s); break;
+    case 16: launch_wgrad_c8_t<16>(a, s); break;
+    default: launch_wgrad_c8_t<8>(a, s); break;
+  }
+}
+
+// 1x1x1: steps of 512 voxels.
+void launch_wgrad_point(WArgs a, hipStream_t s) {
+  const long long V = (long long)a.gy.n * a.gy.d * a.gy.h * a.gy.w, steps = (V + 511) / 512;
+  a.nco = (a.gy.c + 31) / 32;
+  a.nci = (a.gx.c + 31) / 32;
+  const long long tiles = (long long)a.nco * a.nci;
+  const long long n = wgrad_splits(steps, tiles, 512, 2.5), per = (steps + n - 1) / n;
+  a.steps = (int)steps;
+  a.per_wg = (int)per;
+  hipLaunchKernelGGL(k_conv_wgrad_point, dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(512), 0, s, a);
 }
 
 // Rows (n, d, h) by y, (w, channel group) pairs by x.
@@ -1622,12 +1878,15 @@ lbm_status lbm_conv3d_fwd(const lbm_tensor5* x, const uint16_t* w, const float* 
   hipStream_t s = (hipStream_t)stream;
   const Geo gs = geo_of(x), go = geo_of(y);
   const dim3 b(256);
-  const bool rows = ksize == 3 && stride == 1 && x->c != 8;
-  if ((x->c % 32 == 0 || rows) && tap_fits(x) && tap_fits(y) && (long long)y->c * kpad < (1ll << 30)) {
+  const bool rows = ksize == 3 && stride == 1, point = point_fits(ksize, x, y);
+  if ((x->c % 32 == 0 || rows || point) && tap_fits(x) && tap_fits(y) && (long long)y->c * kpad < (1ll << 30)) {
     const DArgs a{(const uint16_t*)x->ptr, gs, (unsigned)view_bytes(x), w, kpad,
                   (unsigned)((long long)y->c * kpad * 2), bias, (uint16_t*)y->ptr, go, nullptr, 0, ksize, stride,
                   relu, 0, x->c};
-    if (!rows || !launch_rows<0>(a, s)) launch_tap_cols<0, false>(a, M, 1, s);
+    if (point)
+      launch_point(a, s);
+    else if (!rows || !launch_rows<0>(a, s))
+      launch_tap_cols<0, false>(a, M, 1, s);
   } else if (y->c <= 16) {
     dim3 g((unsigned)((M + BM - 1) / BM), (y->c + 15) / 16);
     hipLaunchKernelGGL((k_conv_gemm<0, 16>), g, b, 0, s, (const uint16_t*)x->ptr, gs, w, kpad, bias,
@@ -1664,12 +1923,14 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
   const uint16_t* ap = act ? (const uint16_t*)act->ptr : nullptr;
   const int aldc = act ? act->ldc : 0;
   const dim3 b(256);
-  const bool rows = ksize == 3 && stride == 1;
-  if ((dy->c % 32 == 0 || rows) && tap_fits(dy) && tap_fits(dx) && (long long)dx->c * kpad < (1ll << 30)) {
+  const bool rows = ksize == 3 && stride == 1, point = point_fits(ksize, dy, dx);
+  if ((dy->c % 32 == 0 || rows || point) && tap_fits(dy) && tap_fits(dx) && (long long)dx->c * kpad < (1ll << 30)) {
     const DArgs a{(const uint16_t*)dy->ptr, gs, (unsigned)view_bytes(dy), w_t, kpad,
                   (unsigned)((long long)dx->c * kpad * 2), nullptr, (uint16_t*)dx->ptr, go, ap, aldc, ksize, stride,
                   0, accumulate, dy->c};
-    if (stride == 2) {
+    if (point) {
+      launch_point(a, s);
+    } else if (stride == 2) {
       // rows of the largest parity class; smaller classes mask their tail
       const long long rows = (long long)dx->n * ((dx->d + 1) / 2) * ((dx->h + 1) / 2) * ((dx->w + 1) / 2);
       launch_tap_cols<1, true>(a, rows, 8, s);
@@ -1705,9 +1966,8 @@ lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, fl
   const long long V = (long long)dy->n * dy->d * dy->h * dy->w;
   hipStream_t s = (hipStream_t)stream;
   const dim3 b(256);
-  const bool wfit = dy->w >= 32 ? true : (32 % dy->w) == 0;
   const bool fits = tap_fits(x) && tap_fits(dy) && V < (1ll << 31);
-  if (ksize == 3 && fits && !(stride == 1 && x->c == 8 && wfit)) {
+  if (fits) {
     WArgs a{};
     a.x = (const uint16_t*)x->ptr;
     a.gx = geo_of(x);
@@ -1721,40 +1981,16 @@ lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, fl
     // 32-channel output tiles where 64 would be half empty; stride 2, whose
     // halos leave one workgroup per compute unit with them, always takes 64
     const bool half = dy->c % 64 > 0 && dy->c % 64 <= 32;
-    if (stride == 2)
+    if (ksize == 1)
+      launch_wgrad_point(a, s);
+    else if (stride == 2)
       launch_wgrad_rows<2, 64>(a, s);
+    else if (x->c == 8)
+      launch_wgrad_c8(a, s);
     else if (half)
       launch_wgrad_rows<1, 32>(a, s);
     else
       launch_wgrad_rows<1, 64>(a, s);
-    return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
-  }
-  if (ksize == 3 && fits) {
-    WArgs a{};
-    a.x = (const uint16_t*)x->ptr;
-    a.gx = geo_of(x);
-    a.x_bytes = (unsigned)view_bytes(x);
-    a.dy = (const uint16_t*)dy->ptr;
-    a.gy = geo_of(dy);
-    a.dy_bytes = (unsigned)view_bytes(dy);
-    a.dw = dw;
-    a.db = dbias;
-    a.kpad = kpad;
-    a.wp = dy->w >= 32 ? 32 : dy->w;
-    a.r = 32 / a.wp;
-    a.nhb = (dy->h + a.r - 1) / a.r;
-    a.nwb = (dy->w + a.wp - 1) / a.wp;
-    const long long steps = (long long)dy->n * dy->d * a.nhb * a.nwb;
-    a.nco = (dy->c + 31) / 32;
-    a.nci = 1;
-    // about 1024 workgroups, at least 48 steps each (each ends with 32 x 216
-    // FP32 atomics)
-    long long per = (steps * a.nco + 1023) / 1024;
-    if (per < 48) per = 48;
-    const long long splits = (steps + per - 1) / per;
-    a.steps = (int)steps;
-    a.per_wg = (int)per;
-    hipLaunchKernelGGL(k_conv_wgrad_c8, dim3((unsigned)(splits * a.nco)), b, 0, s, a);
     return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
   }
   const int gm = (dy->c + BM - 1) / BM, gn = (kpad + 63) / 64;

@@ -74,6 +74,10 @@ ROWS = [
 ]
 
 
+# the 8-channel forward: partial tiles along every axis (four planes per tile)
+ROWS += [dict(n=2, d=5, h=17, w=17, ci=8, co=40), dict(n=1, d=9, h=15, w=16, ci=8, co=32)]
+
+
 @pytest.mark.parametrize("case", range(len(ROWS)))
 def test_stride1_row_tiles(case):
     _check(ROWS[case], 100 + case)
@@ -128,17 +132,38 @@ WGRADS = [
 ]
 
 
+# the 8-channel layer's weight gradient alike, and pointwise layers: voxel counts
+# off the 64- and 256-voxel pieces, channels on and off 32
+WGRADS += [
+    dict(n=1, d=2, h=9, w=33, ci=8, co=40),
+    dict(n=2, d=3, h=4, w=17, ci=8, co=8),
+    dict(n=1, d=7, h=19, w=5, ci=8, co=32),
+    dict(n=1, d=1, h=1, w=1, ci=8, co=8, k=1),
+    dict(n=2, d=5, h=9, w=13, ci=40, co=72, k=1),
+    dict(n=1, d=16, h=32, w=33, ci=32, co=8, k=1),
+]
+
+
 @pytest.mark.parametrize("case", range(len(WGRADS)))
 def test_weight_gradient_row_steps(case):
     from paper_1007_1388_amd import surrogate as S
     c = WGRADS[case]
-    s = c.get("s", 1)
+    k, s = c.get("k", 3), c.get("s", 1)
     x, w, b, dy = _operands(c, 300 + case)
-    layer = S.Conv(c["ci"], c["co"], stride=s)
+    layer = S.Conv(c["ci"], c["co"], k=k, stride=s)
     layer.zero_grad()
     layer.backward(_sliced(S, x, 8, 16), _sliced(S, dy, 16, 24), None)
-    dw, db = conv.conv3d_bwd_weight(x, dy, 3, s)
-    gw = layer.gw.cpu().numpy()
-    assert np.abs(gw[:, :27 * c["ci"]].reshape(dw.shape) - dw).max() <= 1e-5 * np.abs(dw).max()
-    assert np.all(gw[:, 27 * c["ci"]:] == 0)
+    dw, db = conv.conv3d_bwd_weight(x, dy, k, s)
+    gw, K = layer.gw.cpu().numpy(), k ** 3 * c["ci"]
+    assert np.abs(gw[:, :K].reshape(dw.shape) - dw).max() <= 1e-5 * np.abs(dw).max()
+    assert np.all(gw[:, K:] == 0)
     assert np.abs(layer.gb.cpu().numpy() - db).max() <= 1e-5 * np.abs(db).max()
+
+
+POINTS = [dict(n=1, d=1, h=1, w=1, ci=8, co=8, k=1), dict(n=2, d=5, h=9, w=13, ci=40, co=72, k=1),
+          dict(n=1, d=4, h=8, w=8, ci=64, co=24, k=1), dict(n=1, d=7, h=5, w=11, ci=8, co=32, k=1)]
+
+
+@pytest.mark.parametrize("case", range(len(POINTS)))
+def test_pointwise(case):
+    _check(POINTS[case], 400 + case)
