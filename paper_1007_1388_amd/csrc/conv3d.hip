@@ -1013,8 +1013,9 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 // atomics and, at full resolution, by HBM; the rest by LDS reads and MFMAs.
 template <int S, int BM, int WP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1 && WP > 8 ? 4 : 2))) k_conv_wgrad_rows(WArgs a) {
-  constexpr int KS = BM == 32 ? 2 : 1;             // waves that share a dw tile, each with 4 of a step's rows
-  constexpr int RW = 4, RR = RW * KS;              // rows per wave, per step
+  constexpr int KS = BM == 32 ? 2 : 1;             // waves that share a dw tile, each with RW of a step's rows
+  constexpr int RW = S == 2 && BM == 32 ? 2 : 4;   // (eight rows of stride 2 would leave one workgroup per compute unit)
+  constexpr int RR = RW * KS;
   constexpr int DP = 32 / WP;                      // planes of a 32-voxel row
   constexpr int HR = (RR - 1) * S + 3, HC = (WP - 1) * S + 3;
   constexpr int CELLS = DP * HR * HC;
@@ -1658,11 +1659,9 @@ void launch_tap_cols(const DArgs& a, long long rows, int nz, hipStream_t s) {
     launch_tap<MODE, CLS, 2, 8>(a, rows, nz, s);
 }
 
-// One shape of the plane kernel: its workgroups, and an estimate of its time
-// in units of one (WF = 8, R = 2, WN = 1) workgroup alone on a compute unit:
-// rounds of workgroups (as many per unit as LDS holds) times a workgroup's
-// time, which measured 0.8 : 1 : 1.4 for R WN = 1, 2, 4 (18.5, 23.3 and 31.7 us
-// at 256 channels).
+// One shape of the plane kernel: its workgroups, and an estimate of its time in
+// us: rounds of workgroups (as many per compute unit as LDS holds) times a
+// round's measured time.
 template <int MODE, int NC, int WF, int R, int WN>
 struct PlaneTile {
   static constexpr int DP = 16 / WF;
@@ -1671,39 +1670,55 @@ struct PlaneTile {
     return (long long)((go.w + WF - 1) / WF) * ((go.h + 4 * R - 1) / (4 * R)) * ((go.d + DP - 1) / DP) * go.n *
            ((go.c + 32 * WN - 1) / (32 * WN));
   }
-  static double cost(const Geo& go) {
+  static double us(const Geo& go) {
+    constexpr double small = NC == 8 ? 18.5 : (NC == 4 ? 16.0 : 12.0), mid = NC == 8 ? 23.3 : (NC == 4 ? 16.4 : 18.0),
+                     big = NC == 8 ? 31.7 : (NC == 4 ? 28.0 : 18.0);
     const long long slots = 256 * (160 * 1024 / kLds);
-    return (double)((groups(go) + slots - 1) / slots) * (0.6 + 0.2 * R * WN);
+    return (double)((groups(go) + slots - 1) / slots) * (R * WN == 1 ? small : (R * WN == 2 ? mid : big));
   }
   static void launch(const DArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((k_conv_plane<MODE, NC, WF, R, WN>), dim3((unsigned)groups(a.go)), dim3(256 * WN), 0, s, a);
   }
 };
 
+// The tap-major kernel's time alike: rounds of 512 workgroups, 0.75 us per K
+// step of a 128 x 128 tile, half with 64 columns (launch_tap_cols).
+double tap_us(const DArgs& a) {
+  const long long rows = ((long long)a.go.n * a.go.d * a.go.h * a.go.w + 127) / 128;
+  const int steps = a.ksize * a.ksize * a.ksize * (a.C / 32);
+  const long long wide = rows * ((a.go.c + 127) / 128);
+  if (a.go.c > 64 && wide >= 512) return (double)((wide + 511) / 512) * 0.75 * steps;
+  return (double)((rows * ((a.go.c + 63) / 64) + 511) / 512) * 0.37 * steps;
+}
+
+// false: the tap-major kernel, whose result is the same, is the faster one
+// (widths that fill the tiles badly: 42x37x19 at batch 4, 128->256, 312 against
+// 366 us on plane tiles, its input gradient 335 against 468)
 template <int MODE, int NC>
-void launch_plane_c(const DArgs& a, hipStream_t s) {
+bool launch_plane_c(const DArgs& a, hipStream_t s) {
   using Small = PlaneTile<MODE, NC, 8, 1, 1>;
   using Mid = PlaneTile<MODE, NC, 8, 2, 1>;
   using Big = PlaneTile<MODE, NC, 16, 2, 2>;
-  const double cs = Small::cost(a.go), cm = Mid::cost(a.go), cb = Big::cost(a.go);
+  const double cs = Small::us(a.go), cm = Mid::us(a.go), cb = Big::us(a.go);
+  if (tap_us(a) < std::min(cs, std::min(cm, cb))) return false;
   if (cb < cm && cb < cs)
     Big::launch(a, s);
   else if (cm <= cs)
     Mid::launch(a, s);
   else
     Small::launch(a, s);
+  return true;
 }
 
-// The products that keep the tap-by-tap order of their sums (see
-// launch_rows), for the channel counts the plane kernel holds in LDS.
+// The products that keep the tap-by-tap order of their sums (see launch_rows),
+// for the channel counts the plane kernel holds in LDS.
 template <int MODE>
 bool launch_plane(const DArgs& a, hipStream_t s) {
   switch (a.C) {
-    case 64: launch_plane_c<MODE, 2>(a, s); return true;
-    case 128: launch_plane_c<MODE, 4>(a, s); return true;
-    case 256: launch_plane_c<MODE, 8>(a, s); return true;
+    case 64: return launch_plane_c<MODE, 2>(a, s);
+    case 128: return launch_plane_c<MODE, 4>(a, s);
+    default: return launch_plane_c<MODE, 8>(a, s);
   }
-  return false;
 }
 
 // 1x1x1 layers onto at most 32 channels, or with channels off 32s; onto more,
@@ -1746,7 +1761,7 @@ bool launch_rows(const DArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_conv_fwd_c8, dim3((unsigned)g), dim3(256), 0, s, a);
     return true;
   }
-  if ((a.go.w % 32 != 0 || a.go.c > 64) && launch_plane<MODE>(a, s)) return true;
+  if ((a.go.w % 32 != 0 || a.go.c > 64) && (a.C == 64 || a.C == 128 || a.C == 256)) return launch_plane<MODE>(a, s);
   if (a.C % 32 == 0 && small * 128 > 4 * vox * ((a.go.c + 31) / 32)) return false;
   const bool four = big >= 256 && big * 2 <= small * 1.22, tail = a.C % 32 != 0;
   const dim3 g((unsigned)(four ? big : small)), b(256);
@@ -1761,31 +1776,32 @@ bool launch_rows(const DArgs& a, hipStream_t s) {
   return true;
 }
 
-// Workgroups that share one tile of a weight gradient: at most `slots` in the
-// grid, c sqrt(steps) and a tenth of the steps per tile.  Each ends with one
-// atomic per value of the tile, and the memory side takes the atomics of one
-// address one after the other, about 0.16 us each: N of them cost a step's time
-// times steps / N plus 0.16 us times N (a 1x1x1 layer, 256 addresses in all:
-// 85 us with 512 workgroups, 44 with 113; batch 1 128x64x64 32->32: 129 us with
-// 342, 76 with 90).  Short of ten steps the tile's set-up and atomics outweigh
-// the MFMAs (batch 1 16x8x8 256->256, eight steps: 22 us undivided, 50 in eight).
-long long wgrad_splits(long long steps, long long tiles, long long slots, double c) {
-  const long long most = std::min<long long>((long long)(c * std::sqrt((double)steps)), steps / 10);
-  return std::max<long long>(1, std::min(slots / tiles, most));
+// Workgroups N that share one tile of a weight gradient, at most `slots` in the
+// grid.  Each ends with one atomic per value of the tile: the memory side takes
+// the atomics of one address one after the other, about 0.16 us each, and about
+// 95 G/s in all, so N cost a step's time (us) times steps / N plus N times
+// (0.16 + tiles * values / 95000) us; N is where the two are equal.  Measured:
+// a 1x1x1 layer (256 addresses) 85 us with 512 workgroups, 44 with 80; batch 1
+// 128x64x64 32->32 129 us with 342, 76 with 90; batch 1 16x8x8 256->256 (96 tiles,
+// eight steps) 22 us undivided, 50 in eight.
+long long wgrad_splits(long long steps, long long tiles, long long values, long long slots, double step_us) {
+  const double each = 0.16 + (double)(tiles * values) / 95000.0;
+  const long long n = (long long)std::sqrt(step_us * (double)steps / each);
+  return std::max<long long>(1, std::min(std::min(slots / tiles, steps), n));
 }
 
 // Weight gradients of 3x3x3 layers by row steps: the grid holds about 768
 // workgroups (three per compute unit, see the kernel).
 template <int S, int BM, int WP>
 void launch_wgrad_rows_t(WArgs a, hipStream_t s) {
-  constexpr int RR = BM == 32 ? 8 : 4, DP = 32 / WP;
+  constexpr int RR = S == 1 && BM == 32 ? 8 : 4, DP = 32 / WP;
   a.nhb = (a.gy.h + RR - 1) / RR;
   a.nwb = (a.gy.w + WP - 1) / WP;
   const long long steps = (long long)a.gy.n * ((a.gy.d + DP - 1) / DP) * a.nhb * a.nwb;
   a.nco = (a.gy.c + BM - 1) / BM;
   a.nci = (a.gx.c + 31) / 32;
   const long long tiles = 3ll * a.nci * a.nco;
-  const long long n = wgrad_splits(steps, tiles, 768, 2.0), per = (steps + n - 1) / n;
+  const long long n = wgrad_splits(steps, tiles, BM * 288, 768, 3.0), per = (steps + n - 1) / n;
   a.steps = (int)steps;
   a.per_wg = (int)per;
   hipLaunchKernelGGL((k_conv_wgrad_rows<S, BM, WP>), dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(256), 0, s,
@@ -1821,7 +1837,7 @@ void launch_wgrad_c8_t(WArgs a, hipStream_t s) {
   a.nwb = (a.gy.w + WP - 1) / WP;
   const long long steps = (long long)a.gy.n * ((a.gy.d + DP - 1) / DP) * a.nhb * a.nwb;
   a.nco = (a.gy.c + 31) / 32;
-  const long long n = wgrad_splits(steps, a.nco, 512, 2.0), per = (steps + n - 1) / n;
+  const long long n = wgrad_splits(steps, a.nco, 32 * 216, 512, 2.5), per = (steps + n - 1) / n;
   a.steps = (int)steps;
   a.per_wg = (int)per;
   hipLaunchKernelGGL(k_conv_wgrad_c8<WP>, dim3((unsigned)((steps + per - 1) / per * a.nco)), dim3(256), 0, s, a);
@@ -1841,7 +1857,7 @@ void launch_wgrad_point(WArgs a, hipStream_t s) {
   a.nco = (a.gy.c + 31) / 32;
   a.nci = (a.gx.c + 31) / 32;
   const long long tiles = (long long)a.nco * a.nci;
-  const long long n = wgrad_splits(steps, tiles, 512, 2.5), per = (steps + n - 1) / n;
+  const long long n = wgrad_splits(steps, tiles, 1024, 512, 1.0), per = (steps + n - 1) / n;
   a.steps = (int)steps;
   a.per_wg = (int)per;
   hipLaunchKernelGGL(k_conv_wgrad_point, dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(512), 0, s, a);
@@ -1967,7 +1983,15 @@ lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, fl
   hipStream_t s = (hipStream_t)stream;
   const dim3 b(256);
   const bool fits = tap_fits(x) && tap_fits(dy) && V < (1ll << 31);
-  if (fits) {
+  // (1x1x1: the general kernel's wider tiles read the channels of large layers
+  // fewer times: 6 x 107x68x49 64->64 232 against 369 us; 8 x 32x16x16 256->128
+  // 114 against 56)
+  const long long tiles1 = (long long)((x->c + 31) / 32) * ((dy->c + 31) / 32);
+  const bool wide1 = ksize == 1 && tiles1 >= 4 && V * tiles1 > 3000000;
+  // (a handful of stride-2 steps on channels off 32s: 6 x 4x13x6 24->64 8 us on
+  // the general kernel against 12)
+  const bool tiny = stride == 2 && x->c % 32 != 0 && V < 4096;
+  if (fits && !wide1 && !tiny) {
     WArgs a{};
     a.x = (const uint16_t*)x->ptr;
     a.gx = geo_of(x);
@@ -1978,11 +2002,12 @@ lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, fl
     a.dw = dw;
     a.db = dbias;
     a.kpad = kpad;
-    // 32-channel output tiles where 64 would be half empty; stride 2, whose
-    // halos leave one workgroup per compute unit with them, always takes 64
+    // 32-channel output tiles where 64 would be half empty
     const bool half = dy->c % 64 > 0 && dy->c % 64 <= 32;
     if (ksize == 1)
       launch_wgrad_point(a, s);
+    else if (stride == 2 && half)
+      launch_wgrad_rows<2, 32>(a, s);
     else if (stride == 2)
       launch_wgrad_rows<2, 64>(a, s);
     else if (x->c == 8)

@@ -126,6 +126,7 @@ WGRADS = [
     dict(n=1, d=7, h=3, w=7, ci=32, co=72),
     dict(n=2, d=4, h=17, w=33, ci=32, co=32),
     dict(n=1, d=5, h=7, w=9, ci=40, co=24, s=2),
+    dict(n=3, d=13, h=21, w=43, ci=40, co=24, s=2),
     dict(n=1, d=9, h=6, w=33, ci=32, co=72, s=2),
     dict(n=1, d=3, h=9, w=65, ci=16, co=64, s=2),
     dict(n=2, d=16, h=32, w=32, ci=32, co=32),
