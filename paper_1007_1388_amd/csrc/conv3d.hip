@@ -825,6 +825,134 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
   }
 }
 
+// ------------------------------------- bwd-data, stride 2, 3x3x3, all parities
+// The stride-2 input gradients of 32 or 64 channels (NC chunks).  An input
+// voxel i = 2 j + p receives, per axis, from dy voxel j through tap 1 (p = 0), or
+// from j + 1 through tap 0 and j through tap 2 (p = 1).  The tap-major kernel runs
+// the eight parities as separate grids, each gathering dy and writing every
+// other voxel of a line; here a workgroup owns 4 R rows of 16 dy voxels of one
+// plane, i.e. their 2 x 8 R x 32 input voxels, and 32 channels: dy and its next
+// plane, row and column come into LDS once, all chunks, and the weights pass
+// through two LDS buffers in nine stages of three kw taps, grouped by the parity
+// of plane and row.  Both parities along w are finished together, so a lane
+// writes two neighbouring voxels.  Cells, weight rows and stores as in
+// k_conv_rows; the order of the sums is the tap-major kernel's (kd, kh, kw,
+// chunk), bit for bit.  Bound by HBM (the mask and the accumulated gradient).
+// Measured on gfx950, batch 8: 128x64x64 32 <- 64 channels 478 us before, 186
+// now (312 TFLOP/s); batch 4, 100x60x52 32 <- 64: 125 before, 63 now.
+template <int NC, int R>
+__global__ void __launch_bounds__(256) k_conv_up(DArgs a) {
+  constexpr int TH = 4 * R, HC = 17, HR = TH + 1, CELLS = 2 * HR * HC;
+  constexpr int NXI = (CELLS * 4 + 63) / 64, NWI = 6 * NC;  // wave-wide 16-byte loads: a chunk's halo, a stage's weights
+  constexpr int SX = (NXI + 3) / 4, SW = (NWI + 3) / 4;
+  constexpr int C = NC * 32;
+  constexpr unsigned OOB = 0x80000000u;
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[NC][NXI * 512];
+  __shared__ __attribute__((aligned(1024))) uint16_t Ws[2][NWI * 512];  // [kw][chunk][32 columns][32]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Geo gs = a.gs, go = a.go;
+  const int total = (int)gridDim.x, id0 = (int)blockIdx.x, q8 = total / 8 * 8;
+  int bx = id0 < q8 ? (id0 % 8) * (total / 8) + id0 / 8 : id0;
+  const int nct = (go.c + 31) / 32, nwb = (gs.w + 15) / 16, nhb = (gs.h + TH - 1) / TH;
+  const int n0 = bx % nct * 32;
+  bx /= nct;
+  const int w0 = bx % nwb * 16;
+  bx /= nwb;
+  const int h0 = bx % nhb * TH;
+  bx /= nhb;
+  const int jd0 = bx % gs.d, n = bx / gs.d;
+  const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.src, a.src_bytes);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wk, a.wk_bytes);
+  unsigned woff[SW];
+#pragma unroll
+  for (int i = 0; i < SW; ++i) {
+    const int id = (i * 4 + wave) * 64 + lane;
+    const int kw = id / (NC * 128), ck = id / 128 % NC, col = id % 128 >> 2, q = (id & 3) ^ ((col >> 3) & 3);
+    woff[i] = n0 + col < go.c ? (unsigned)((n0 + col) * a.kstride + kw * C + ck * 32 + q * 8) * 2u : OOB;
+  }
+  // stage s: parities (pd, ph) of plane and row, and which of their one or two
+  // taps along each (jd, jh)
+  auto stage = [](int s, int& pd, int& ph, int& jd, int& jh) {
+    constexpr int PD[9] = {0, 0, 0, 1, 1, 1, 1, 1, 1}, PH[9] = {0, 1, 1, 0, 0, 1, 1, 1, 1};
+    constexpr int JD[9] = {0, 0, 0, 0, 1, 0, 0, 1, 1}, JH[9] = {0, 0, 1, 0, 0, 0, 1, 0, 1};
+    pd = PD[s], ph = PH[s], jd = JD[s], jh = JH[s];
+  };
+  auto load_w = [&](int s) {
+    int pd, ph, jd, jh;
+    stage(s, pd, ph, jd, jh);
+    const int kd = pd ? 2 * jd : 1, kh = ph ? 2 * jh : 1;
+#pragma unroll
+    for (int i = 0; i < SW; ++i)
+      if (i * 4 + wave < NWI)
+        lds_dma16(rw, Ws[s & 1] + (i * 4 + wave) * 512, woff[i], (unsigned)((kd * 3 + kh) * 3 * C) * 2u);
+  };
+  load_w(0);
+#pragma unroll
+  for (int i = 0; i < SX; ++i)
+    if (i * 4 + wave < NXI) {
+      const int id = (i * 4 + wave) * 64 + lane;
+      const int cell = id >> 2, p = cell / (HR * HC), r = cell / HC % HR, c = cell % HC;
+      const int q = (id & 3) ^ ((c >> 1) & 3);
+      const bool ok = cell < CELLS && jd0 + p < gs.d && h0 + r < gs.h && w0 + c < gs.w;
+      const unsigned vo =
+          ok ? (unsigned)((((n * gs.d + jd0 + p) * gs.h + h0 + r) * gs.w + w0 + c) * gs.ldc + q * 8) * 2u : OOB;
+#pragma unroll
+      for (int k = 0; k < NC; ++k) lds_dma16(rs, Xs[k] + (i * 4 + wave) * 512, vo, (unsigned)k * 64u);
+    }
+  const int L = lane & 15, g = lane >> 4;
+  int xb[2];
+#pragma unroll
+  for (int o = 0; o < 2; ++o) xb[o] = (wave * R * HC + L + o) * 32 + ((g ^ (((L + o) >> 1) & 3)) * 8);
+  const int wb = ((L >> 2) * 8 + (L & 3)) * 32 + ((g ^ (L >> 2)) * 8);
+  __syncthreads();  // (waits for the loads)
+
+  const int col = n0 + g * 8, w = 2 * (w0 + L);
+  f32x4 acc[R][2][2];  // [row][parity along w][column fragment]
+#pragma unroll
+  for (int s = 0; s < 9; ++s) {
+    int pd, ph, jd, jh;
+    stage(s, pd, ph, jd, jh);
+    if (s < 8) load_w(s + 1);  // in flight while this stage runs
+    if (jd == 0 && jh == 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int o = 0; o < 2; ++o) acc[r][o][0] = acc[r][o][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int xo = ((pd - jd) * HR + ph - jh) * HC * 32;  // source plane and row
+    // kw = 1 (even voxels, dy column j), 0 (odd, j + 1), 2 (odd, j)
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int kw = t == 0 ? 1 : (t == 1 ? 0 : 2), odd = t == 0 ? 0 : 1, o = t == 1 ? 1 : 0;
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        bf16x8 wf[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) wf[j] = *(const bf16x8*)(&Ws[s & 1][wb + ((kw * NC + k) * 32 + j * 4) * 32]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const bf16x8 xf = *(const bf16x8*)(&Xs[k][xb[o] + xo + r * HC * 32]);
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[r][odd][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf, acc[r][odd][j], 0, 0, 0);
+        }
+      }
+    }
+    if (jd == pd && jh == ph) {  // the parity's last stage
+      const int d = 2 * jd0 + pd;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int h = 2 * (h0 + wave * R + r) + ph;
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+          if (d < go.d && h < go.h && w + o < go.w && col < go.c)
+            store8(a, (((long long)n * go.d + d) * go.h + h) * go.w + w + o, col, acc[r][o][0], acc[r][o][1]);
+      }
+    }
+    __syncthreads();  // this stage's weights are read, the next one's have arrived
+  }
+}
+
 // --------------------------------------------- fwd / bwd-data, 1x1x1 layers
 // The pointwise products (either direction: rows = voxels, K = the gathered
 // channels).  A wave takes 64 consecutive voxels (four 16-voxel operands) and
@@ -1721,6 +1849,28 @@ bool launch_plane(const DArgs& a, hipStream_t s) {
   }
 }
 
+template <int NC, int R>
+void launch_up_t(const DArgs& a, hipStream_t s) {
+  const long long g = (long long)((a.gs.w + 15) / 16) * ((a.gs.h + 4 * R - 1) / (4 * R)) * a.gs.d * a.gs.n *
+                      ((a.go.c + 31) / 32);
+  hipLaunchKernelGGL((k_conv_up<NC, R>), dim3((unsigned)g), dim3(256), 0, s, a);
+}
+
+// Stride-2 input gradients of 32 or 64 channels, where the 16 x 8 tiles are at
+// least half filled.  Below that the tap-major kernel's flat rows win (100x100x8
+// 32 <- 64: 86 us against 64; 100x100x22, 0.6 filled: 90 against 172).  128
+// channels take the LDS to one workgroup a CU: 80 us against 104 on 64x32x32
+// 64 <- 128, but 621 against 549 on 40x40x64 256 <- 128.
+bool launch_up(const DArgs& a, hipStream_t s) {
+  const long long full = (long long)((a.gs.w + 15) / 16 * 16) * ((a.gs.h + 7) / 8 * 8);
+  if ((a.C != 32 && a.C != 64) || 2 * (long long)a.gs.w * a.gs.h < full) return false;
+  if (a.C == 32)
+    launch_up_t<1, 2>(a, s);
+  else
+    launch_up_t<2, 2>(a, s);
+  return true;
+}
+
 // 1x1x1 layers onto at most 32 channels, or with channels off 32s; onto more,
 // the tap-major kernel's wider column tiles read the input fewer times (8 x
 // 32x16x16 256->128: 25.9 against 28.2 us).
@@ -1947,9 +2097,11 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
     if (point) {
       launch_point(a, s);
     } else if (stride == 2) {
-      // rows of the largest parity class; smaller classes mask their tail
-      const long long rows = (long long)dx->n * ((dx->d + 1) / 2) * ((dx->h + 1) / 2) * ((dx->w + 1) / 2);
-      launch_tap_cols<1, true>(a, rows, 8, s);
+      if (!launch_up(a, s)) {
+        // rows of the largest parity class; smaller classes mask their tail
+        const long long rows = (long long)dx->n * ((dx->d + 1) / 2) * ((dx->h + 1) / 2) * ((dx->w + 1) / 2);
+        launch_tap_cols<1, true>(a, rows, 8, s);
+      }
     } else if (!rows || !launch_rows<1>(a, s)) {
       launch_tap_cols<1, false>(a, M, 1, s);
     }

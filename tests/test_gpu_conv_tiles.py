@@ -168,3 +168,21 @@ POINTS = [dict(n=1, d=1, h=1, w=1, ci=8, co=8, k=1), dict(n=2, d=5, h=9, w=13, c
 @pytest.mark.parametrize("case", range(len(POINTS)))
 def test_pointwise(case):
     _check(POINTS[case], 400 + case)
+
+
+# stride-2 input gradients of 32 and 64 channels: odd and even extents (the last
+# odd voxel missing), partial tiles of 16 columns and 8 rows, partial columns;
+# the last two stay with the tap-major kernel (tiles badly filled, 128 channels)
+UPS = [
+    dict(n=1, d=1, h=9, w=17, ci=8, co=32, s=2),
+    dict(n=2, d=4, h=32, w=34, ci=40, co=32, s=2),
+    dict(n=1, d=5, h=15, w=64, ci=24, co=64, s=2),
+    dict(n=3, d=3, h=25, w=31, ci=72, co=64, s=2),
+    dict(n=1, d=6, h=18, w=7, ci=32, co=64, s=2),
+    dict(n=1, d=3, h=16, w=32, ci=72, co=128, s=2),
+]
+
+
+@pytest.mark.parametrize("case", range(len(UPS)))
+def test_stride2_input_gradient(case):
+    _check(UPS[case], 500 + case)
