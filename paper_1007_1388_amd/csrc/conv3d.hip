@@ -5,10 +5,15 @@
 //   forward      C[voxel][co]      = sum_k  patch(x)[voxel][k] * w[co][k]
 //   bwd-data     C[voxel_in][ci]   = sum_k  patch^T(dy)[voxel_in][k] * wt[ci][k]
 //   bwd-weight   C[co][k]          = sum_v  dy[v][co] * patch(x)[v][k]      (split over voxels)
-// with k = tap * Cin + ci.  A workgroup (4 waves) computes a 128 x BN tile;
-// each wave owns 32 rows (two 16-row MFMA tiles) and all BN columns.  The
-// operand tiles are staged through LDS with K fastest, so every MFMA operand
-// is one 16-byte LDS read per lane.
+// with k = tap * Cin + ci.  By shape (the launch_ functions below):
+//   3x3x3, stride 1        k_conv_rows, k_conv_plane: source halos in LDS by direct loads
+//   3x3x3, 8 channels      k_conv_fwd_c8, k_conv_wgrad_c8
+//   stride-2 bwd-data      k_conv_up (all parities of a tile in one workgroup)
+//   1x1x1                  k_conv_point, k_conv_wgrad_point
+//   3x3x3 bwd-weight       k_conv_wgrad_rows
+//   forward of stride 2 and what those leave, channels a multiple of 32: k_conv_tap
+//   the rest               k_conv_gemm, k_conv_wgrad: a 128 x BN tile per workgroup
+//                          (4 waves of 32 rows), operands staged in LDS with K fastest
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
