@@ -338,12 +338,17 @@ void order_items_by_xcd(lbm_ctx* c) {
 //    which half-size values outrun: 256^3 cavity FP16S 273 -> 263, 128^3 38.7
 //    -> 36.9, 256^3 in 8 Blocks 358 -> 318 (64^3, one per unit, 19.4
 //    against 23.8).
+//  * The fully fused exchange keeps the target: a wave spends more on looking
+//    up its rows' ghost targets, once per item (384^3 FP32 in 64 Blocks 1806
+//    against 1982 halved, in 216 Blocks 1742 against 1841, FP64 in 27 Blocks
+//    3421 against 3724; the other way by up to 4 % on 128^3 FP64).
 bool few_items(const lbm_ctx* c) {
   return c->n_cells / std::max(1, c->sched.item_cells) < 3 * c->cu_count;
 }
 int item_target(const lbm_ctx* c) {
   const int t = std::max(1, c->sched.item_cells);
   if (c->sched.persistent > 0) return t;  // workgroups loop over the items anyway
+  if (c->sched.fused_exchange == 1) return t;
   if (c->prec >= 2) return c->n_cells / t >= 12 * c->cu_count ? 2 * t : t;
   const bool streams = c->prec == 0 || (!c->has_mask && c->sched.fused_exchange != 2);
   return streams || few_items(c) ? std::max(1, t / 2) : t;
