@@ -120,8 +120,8 @@ typedef struct {
                               ghost layers itself; 2 = the sweep writes the x-face ghost
                               planes for rows off the y/z faces, the copy kernel the rest */
   int32_t item_cells;      /* target cells per work item (whole x-rows), >= 1; sweeps bound by
-                              memory take half of it, 16-bit storage on large grids twice
-                              (neither with fused_exchange = 1) */
+                              memory take half of it, 16-bit storage on large grids
+                              without obstacles twice (neither with fused_exchange = 1) */
   int32_t wg_size;         /* threads per workgroup: 64, 128 or 256 */
   int32_t persistent;      /* 0: one workgroup per item; k > 0: k workgroups per
                               compute unit loop over the item list */

@@ -333,11 +333,14 @@ void order_items_by_xcd(lbm_ctx* c) {
 //  * Fewer than three items per compute unit: half, whatever the variant, to
 //    occupy the chip: 32^3 FP64 cavity 12.8 -> 8.7, 64^3 FP32 in 8 Blocks
 //    22.9 -> 21.3 (64x64x128 porous, four per unit, 18.7 against 19.1).
-//  * 16-bit storage with at least six items per compute unit left: double,
+//  * 16-bit storage without obstacles, with at least eight items per compute
+//    unit left: double,
 //    four tasks per wave.  The dispatcher starts about 240 workgroups per us,
 //    which half-size values outrun: 256^3 cavity FP16S 273 -> 263, 128^3 38.7
 //    -> 36.9, 256^3 in 8 Blocks 358 -> 318 (64^3, one per unit, 19.4
-//    against 23.8).
+//    against 23.8; 321x137x38 in 8 Blocks, six per unit, 54.9 against 57.8).  With
+//    obstacles whole items: 53x95x391 in 8 Blocks 101 against 135 doubled, 24x211x357
+//    85 against 93, 138x212x144 in 12 Blocks 153 against 161.
 //  * The fully fused exchange keeps the target: a wave spends more on looking
 //    up its rows' ghost targets, once per item (384^3 FP32 in 64 Blocks 1806
 //    against 1982 halved, in 216 Blocks 1742 against 1841, FP64 in 27 Blocks
@@ -349,7 +352,7 @@ int item_target(const lbm_ctx* c) {
   const int t = std::max(1, c->sched.item_cells);
   if (c->sched.persistent > 0) return t;  // workgroups loop over the items anyway
   if (c->sched.fused_exchange == 1) return t;
-  if (c->prec >= 2) return c->n_cells / t >= 12 * c->cu_count ? 2 * t : t;
+  if (c->prec >= 2) return !c->has_mask && c->n_cells / t >= 16 * c->cu_count ? 2 * t : t;
   const bool streams = c->prec == 0 || (!c->has_mask && c->sched.fused_exchange != 2);
   return streams || few_items(c) ? std::max(1, t / 2) : t;
 }
