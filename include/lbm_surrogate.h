@@ -61,6 +61,18 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
 lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* dbias,
                                  int32_t ksize, int32_t stride, void* stream);
 
+/* The same gradient with its sums in a fixed order, so that a repeated call on
+ * the same values gives the same bits: the workgroups store partial sums in
+ * `scratch` (device memory, 16-byte aligned, at least the bytes that
+ * lbm_conv3d_bwd_weight_scratch names for these shapes; 0: none needed, NULL
+ * will do; -1: bad shapes), and a second kernel adds them in FP64.  The scratch
+ * memory is the call's own until its work on `stream` is done; its contents
+ * before do not matter.  LBM_EINVAL too if it is missing, short or unaligned. */
+int64_t lbm_conv3d_bwd_weight_scratch(const lbm_tensor5* x, const lbm_tensor5* dy, int32_t ksize, int32_t stride);
+lbm_status lbm_conv3d_bwd_weight_ordered(const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* dbias,
+                                         int32_t ksize, int32_t stride, void* scratch, int64_t scratch_bytes,
+                                         void* stream);
+
 /* Transposed weight for lbm_conv3d_bwd_data: wt[ci][t*Cout + co] (padded to
  * lbm_conv_kpad(taps, cout)) from w[co][t*Cin + ci]; FP32 master -> BF16. */
 lbm_status lbm_conv3d_weight_t(const float* w_master, int32_t taps, int32_t cin, int32_t cout,

@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "../../include/lbm_surrogate.h"
 
@@ -457,7 +458,8 @@ __global__ void __launch_bounds__(256) k_conv_tap(DArgs a) {
 // (BN = 64), K loop over 32-voxel chunks of this workgroup's voxel range.
 __global__ void __launch_bounds__(256) k_conv_wgrad(const uint16_t* __restrict__ x, Geo gx,
                                                     const uint16_t* __restrict__ dy, Geo gy, float* __restrict__ dw,
-                                                    int kpad, int kin, int ksize, int stride, long long vox_per_wg) {
+                                                    float* __restrict__ part, int kpad, int kin, int ksize, int stride,
+                                                    long long vox_per_wg) {
   constexpr int BN = 64;
   __shared__ __attribute__((aligned(16))) uint16_t As[BM * LDK];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * LDK];
@@ -527,7 +529,12 @@ __global__ void __launch_bounds__(256) k_conv_wgrad(const uint16_t* __restrict__
 #pragma unroll
       for (int j = 0; j < BN / 16; ++j) {
         const int k = k0c + j * 16 + (lane & 15);
-        if (k < kpad) atomicAdd(dw + (long long)co * kpad + k, acc[i][j][r]);
+        if (k >= kpad) continue;
+        const long long e = (long long)co * kpad + k;
+        if (part)
+          part[(long long)blockIdx.z * cout * kpad + e] = acc[i][j][r];
+        else
+          atomicAdd(dw + e, acc[i][j][r]);
       }
     }
 }
@@ -1099,7 +1106,40 @@ struct WArgs {
   int nhb, nwb;         // steps per column of rows / per row
   int steps, per_wg;    // total steps, steps per workgroup
   int nco, nci;         // output / input channel tiles
+  float* part;          // the splits' sums [split][Cout][kpad], or nullptr: atomics into dw, db
+  float* part_b;        // ... of the bias gradient [split][Cout]
 };
+
+// Where a workgroup's sums of dw go: their split's part, stored for k_wgrad_sum,
+// or dw itself, added.
+__device__ __forceinline__ float* dw_of(const WArgs& a, int split) {
+  return a.part ? a.part + (long long)split * a.gy.c * a.kpad : a.dw;
+}
+template <bool ADD>
+__device__ __forceinline__ void put(float* p, float v) {
+  if constexpr (ADD)
+    atomicAdd(p, v);
+  else
+    *p = v;
+}
+
+// The bias gradient of a split from NG partial sums per channel of a CH-channel
+// tile (thread tid: group tid / CH, channel tid % CH), added up through LDS in a
+// fixed order.  The caller's waves are past their last reads of `red`.
+template <int CH, int NG>
+__device__ __forceinline__ void put_db(const WArgs& a, int split, int co0, int tid, float v, float* red) {
+  red[tid] = v;
+  __syncthreads();
+  if (tid < CH && co0 + tid < a.gy.c) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < NG; ++k) t += red[k * CH + tid];
+    if (a.part_b)
+      a.part_b[(long long)split * a.gy.c + co0 + tid] = t;
+    else
+      atomicAdd(a.db + co0 + tid, t);
+  }
+}
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
@@ -1133,19 +1173,21 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 //    three steps, in their L2 (going along the rows first read x three times
 //    from memory: 128x64x64 32->32 290 against 267 us at batch 8, 64->32 512
 //    against 460).
-//  * 768 workgroups in all: every one ends with BM x 288 FP32 atomics, of which
-//    the card takes about 95 G/s (memory side, whatever their order or the
-//    width of their runs), so more workgroups cost more than they fill
-//    (64x32x32 64->64: 128 us with 768, 143 with 1024, 176 with 2048).
+//  * About 768 workgroups, one round (wgrad_splits).  Every one ends with BM x 288
+//    values, stored as its split's part and added up in a fixed order by
+//    k_wgrad_sum: against FP32 atomics into dw, of which the card takes about 95
+//    G/s, the sums repeat bit for bit and are nearer the exact ones (batch 8
+//    128x64x64 32->32: dw off by 4.7e-7 of its norm, 5.5e-7 before; db 6e-8, 9e-7
+//    before), and small layers may be split further (batch 1 128x64x64 32->32 77
+//    -> 49 us).
 // Channels in 8s: the part of a tile past Cin or Cout loads zeros.
-// Measured on gfx950 at batch 8, us, against the tap-by-tap kernel: 128x64x64
-// 32->32 349 -> 267, 64->32 583 -> 460; 64x32x32 64->64 189 -> 128, 128->64 248 ->
-// 207 (1120 TFLOP/s); 32x16x16 128->128 113 -> 84, 256->128 187 -> 120; 16x8x8
-// 256->256 69 -> 60; stride 2 128x64x64 32->64 145 -> 140; 4 x 100x60x52 32->64
-// 138 (general kernel) -> 67; batch 1 128x64x64 32->32 129 -> 103.  Bound by the
-// atomics and, at full resolution, by HBM; the rest by LDS reads and MFMAs.
+// Measured on gfx950 at batch 8, us with the sum and the bias, against the
+// tap-by-tap kernel with atomics: 128x64x64 32->32 349 -> 235; 64x32x32 64->64
+// 190 -> 114; 32x16x16 256->128 182 -> 119; 16x8x8 256->256 69 -> 44; stride 2
+// 128x64x64 32->64 141 -> 126; batch 1 128x64x64 32->32 136 -> 49.  Bound by HBM at
+// full resolution, by LDS reads and MFMAs otherwise.
 template <int S, int BM, int WP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1 && WP > 8 ? 4 : 2))) k_conv_wgrad_rows(WArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2 || WP == 8 ? 2 : (BM == 64 && WP == 32 ? 3 : 4)))) k_conv_wgrad_rows(WArgs a) {
   constexpr int KS = BM == 32 ? 2 : 1;             // waves that share a dw tile, each with RW of a step's rows
   constexpr int RW = S == 2 && BM == 32 ? 2 : 4;   // (eight rows of stride 2 would leave one workgroup per compute unit)
   constexpr int RR = RW * KS;
@@ -1220,16 +1262,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1
   int db = s_begin % ndb, pl = s_begin / ndb;
   int wb = pl % a.nwb, hb = pl / a.nwb % a.nhb, nn = pl / (a.nwb * a.nhb);
 
+  constexpr int BG = 256 / BM;
+  const bool do_bias = a.db != nullptr && kd == 0 && ci0 == 0;
+  const int b_ch = tid % BM, b_v0 = tid / BM * (RR * 32 / BG);
+
   f32x4 acc[2][9];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr int BG = 256 / BM;
-  const bool do_bias = a.db != nullptr && kd == 0 && ci0 == 0;
-  const int b_ch = tid % BM, b_v0 = tid / BM * (RR * 32 / BG);
   float bsum = 0.f;
-
   for (int st = s_begin; st < s_end; ++st) {
     const int d0 = db * DP, h0 = hb * RR, w0 = wb * WP;
     const int ab = ((nn * gy.d + d0) * gy.h + h0) * gy.w * gy.ldc + w0 * gy.ldc;
@@ -1286,9 +1328,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1
       }
     }
     if (do_bias) {
+      float t = 0.f;
 #pragma unroll 8
       for (int j = 0; j < RR * 32 / BG; ++j)
-        bsum += bf2f(As[((b_ch >> 5) * (RR * 32) + b_v0 + j) * 32 + (b_ch & 31)]);
+        t += bf2f(As[((b_ch >> 5) * (RR * 32) + b_v0 + j) * 32 + (b_ch & 31)]);
+      bsum += t;
     }
   }
   if constexpr (KS == 2) {
@@ -1312,7 +1356,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1
   }
   // lane holds D[4 g + q][L] of each tile: rows co, columns ci
   const int cin = gx.c, ci = ci0 + jsub * 16 + L;
-  if ((KS == 1 || wave < 2) && ci < cin) {
+  float* const dw = dw_of(a, split);
+  auto finish = [&](auto add) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -1320,10 +1365,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1
         const int co = co0 + (cs * 2 + i) * 16 + g * 4 + q;
         if (co >= gy.c) continue;
 #pragma unroll
-        for (int t = 0; t < 9; ++t) atomicAdd(a.dw + (long long)co * a.kpad + (kd * 9 + t) * cin + ci, acc[i][t][q]);
+        for (int t = 0; t < 9; ++t)
+          put<add.value>(dw + (unsigned)(co * a.kpad + (kd * 9 + t) * cin + ci), acc[i][t][q]);
       }
+  };
+  if ((KS == 1 || wave < 2) && ci < cin) {
+    if (a.part)
+      finish(std::false_type{});
+    else
+      finish(std::true_type{});
   }
-  if (do_bias && co0 + b_ch < gy.c) atomicAdd(a.db + co0 + b_ch, bsum);
+  if (do_bias) {
+    __syncthreads();  // the last readers of LDS are done
+    put_db<BM, BG>(a, split, co0, tid, bsum, (float*)Xs);
+  }
 }
 
 // --------------------------------- bwd-weight, 3x3x3, 8 input channels
@@ -1337,9 +1392,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 1
 // points at the tap of its half of the tile's columns.  Wave v owns both
 // 16-channel halves of dy and the column tiles v, v + 4, v + 8, v + 12: six reads
 // for eight MFMAs of a row.  With db given the dy tiles are summed from LDS
-// (each once per channel tile).  Bound by LDS reads, then by the atomics (see
-// wgrad_splits).  Measured on gfx950 at 8 x 128x64x64, 8->32: 384 -> 225 us
-// against steps of one row staged through registers.
+// (each once per channel tile), one value per channel and workgroup.  Bound by LDS
+// reads.  Measured on gfx950 at 8 x 128x64x64, 8->32: 121 us with the sum and the
+// bias (384 with steps of one row staged through registers; 213 with eight
+// atomics per channel and workgroup for the bias, which queued at 32 addresses).
 template <int WP>
 __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
   constexpr int RR = 8, DP = 32 / WP;
@@ -1400,14 +1456,14 @@ __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
   int db = s_begin % ndb, pl = s_begin / ndb;
   int wb = pl % a.nwb, hb = pl / a.nwb % a.nhb, nn = pl / (a.nwb * a.nhb);
 
+  const bool do_bias = a.db != nullptr;
+
   f32x4 acc[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bool do_bias = a.db != nullptr;
   float bsum = 0.f;
-
   for (int st = s_begin; st < s_end; ++st) {
     const int d0 = db * DP, h0 = hb * RR, w0 = wb * WP;
     const int ab = ((nn * gy.d + d0) * gy.h + h0) * gy.w * gy.ldc + w0 * gy.ldc;
@@ -1453,24 +1509,36 @@ __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
       }
     }
     if (do_bias) {
+      float t = 0.f;
 #pragma unroll 8
-      for (int j = 0; j < RR * 4; ++j) bsum += bf2f(As[(tid / 32 * (RR * 4) + j) * 32 + tid % 32]);
+      for (int j = 0; j < RR * 4; ++j) t += bf2f(As[(tid / 32 * (RR * 4) + j) * 32 + tid % 32]);
+      bsum += t;
     }
   }
   // lane holds D[4 g + q][L] of each tile: rows co, columns k
+  float* const dw = dw_of(a, split);
+  auto finish = [&](auto add) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int co = co0 + i * 16 + g * 4 + q;
-      if (co >= gy.c) continue;
+      for (int q = 0; q < 4; ++q) {
+        const int co = co0 + i * 16 + g * 4 + q;
+        if (co >= gy.c) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = (wave + 4 * j) * 16 + L;
-        if (k < 216) atomicAdd(a.dw + (long long)co * a.kpad + k, acc[i][j][q]);
+        for (int j = 0; j < 4; ++j) {
+          const int k = (wave + 4 * j) * 16 + L;
+          if (k < 216) put<add.value>(dw + (unsigned)(co * a.kpad + k), acc[i][j][q]);
+        }
       }
-    }
-  if (do_bias && co0 + tid % 32 < gy.c) atomicAdd(a.db + co0 + tid % 32, bsum);
+  };
+  if (a.part)
+    finish(std::false_type{});
+  else
+    finish(std::true_type{});
+  if (do_bias) {
+    __syncthreads();  // the last readers of LDS are done
+    put_db<32, 8>(a, split, co0, tid, bsum, (float*)As);
+  }
 }
 
 // ------------------------------------------------------- bwd-weight, 1x1x1
@@ -1479,9 +1547,9 @@ __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
 // voxels, both tiles brought into LDS by direct loads (64-byte cells, zeros
 // past the channels); wave v multiplies voxels 64 v .. + 63, and the eight waves'
 // sums meet in LDS.  Bound by HBM (the channels are read once per tile of the
-// other side) and the atomics' queue at its few addresses.  Measured on gfx950 at 8 x 128x64x64, 32->8: 239 -> 142 us with
-// the bias, against the general kernel, which transposes by hand, and a bias
-// pass of its own.
+// other side).  Measured on gfx950 at 8 x 128x64x64, 32->8, with the sum and the
+// bias: 239 -> 78 us, against the general kernel, which transposes by hand, and a
+// bias pass of its own (140 with the splits' values as atomics).
 __global__ void __launch_bounds__(512) k_conv_wgrad_point(WArgs a) {
   constexpr unsigned OOB = 0x80000000u;
   __shared__ __attribute__((aligned(1024))) uint16_t As[512 * 32], Xs[512 * 32];
@@ -1498,13 +1566,13 @@ __global__ void __launch_bounds__(512) k_conv_wgrad_point(WArgs a) {
   int off[2];
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) off[hh] = (wave * 64 + 8 * g + 4 * hh + (L >> 2)) * 32 + (L & 3) * 4;
+  const bool do_bias = a.db != nullptr && ci0 == 0;
+  const int s_begin = split * a.per_wg, s_end = s_begin + a.per_wg < a.steps ? s_begin + a.per_wg : a.steps;
   f32x4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bool do_bias = a.db != nullptr && ci0 == 0;
   float bsum = 0.f;
-  const int s_end = (split + 1) * a.per_wg < a.steps ? (split + 1) * a.per_wg : a.steps;
-  for (int st = split * a.per_wg; st < s_end; ++st) {
+  for (int st = s_begin; st < s_end; ++st) {
     __syncthreads();  // the previous step's readers are done
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1527,8 +1595,10 @@ __global__ void __launch_bounds__(512) k_conv_wgrad_point(WArgs a) {
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bx[j], acc[i][j], 0, 0, 0);
     }
     if (do_bias) {
+      float t = 0.f;
 #pragma unroll 8
-      for (int j = 0; j < 32; ++j) bsum += bf2f(As[(tid / 32 * 32 + j) * 32 + tid % 32]);
+      for (int j = 0; j < 32; ++j) t += bf2f(As[(tid / 32 * 32 + j) * 32 + tid % 32]);
+      bsum += t;
     }
   }
   float* T = (float*)Xs;  // [wave][32 co][32 ci]
@@ -1546,17 +1616,22 @@ __global__ void __launch_bounds__(512) k_conv_wgrad_point(WArgs a) {
     float t = 0.f;
 #pragma unroll
     for (int w = 0; w < 8; ++w) t += T[w * 1024 + e];
-    if (co < gy.c && ci < gx.c) atomicAdd(a.dw + (long long)co * a.kpad + ci, t);
+    if (co >= gy.c || ci >= gx.c) continue;
+    float* const p = dw_of(a, split) + (unsigned)(co * a.kpad + ci);
+    if (a.part)
+      put<false>(p, t);
+    else
+      put<true>(p, t);
   }
-  if (do_bias && co0 + tid % 32 < gy.c) atomicAdd(a.db + co0 + tid % 32, bsum);
+  if (do_bias) put_db<32, 16>(a, split, co0, tid, bsum, (float*)As);  // (As is free since the sums met in Xs)
 }
 
 // dbias[co] += sum_v dy[v][co]: a thread sums 8 channels (one 16-byte load
 // per voxel) over every (256 / groups)-th voxel of the workgroup's range; the
 // partial sums meet in LDS and each channel takes one atomic per workgroup.
 __global__ void __launch_bounds__(256) k_bias_grad(const uint16_t* __restrict__ dy, Geo gy, float* __restrict__ db,
-                                                   long long vox_per_wg) {
-  __shared__ float part[256 * 8];
+                                                   float* __restrict__ part, long long vox_per_wg) {
+  __shared__ float sums[256 * 8];
   const long long V = (long long)gy.n * gy.d * gy.h * gy.w;
   const long long vbeg = (long long)blockIdx.x * vox_per_wg;
   const long long vend = vbeg + vox_per_wg < V ? vbeg + vox_per_wg : V;
@@ -1574,13 +1649,67 @@ __global__ void __launch_bounds__(256) k_bias_grad(const uint16_t* __restrict__ 
       }
     }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) part[tid * 8 + j] = s8[j];
+  for (int j = 0; j < 8; ++j) sums[tid * 8 + j] = s8[j];
   __syncthreads();
   for (int c = tid; c < gy.c; c += 256) {
     const int g = c / 8, j = c % 8;
     float t = 0.f;
-    for (int k = 0; k < vl; ++k) t += part[(k * groups + g) * 8 + j];
-    atomicAdd(db + c, t);
+    for (int k = 0; k < vl; ++k) t += sums[(k * groups + g) * 8 + j];
+    if (part)
+      part[(long long)blockIdx.x * gy.c + c] = t;
+    else
+      atomicAdd(db + c, t);
+  }
+}
+
+// dw[co][k] += the sum of its splits' parts, and db alike, in a fixed order
+// and in FP64 (one rounding), so that a repeated gradient repeats bit for bit.
+// Four neighbouring values per thread; where there are many splits the block's
+// eight groups of 32 threads take every eighth part each and meet in LDS (few
+// values and many parts would otherwise be one long chain of loads).  Bound by
+// reading the parts once, from the memory-side cache for most layers.
+struct WSum {
+  const float *part, *part_b;
+  float *dw, *db;
+  int splits, splits_b;
+  int cout, kpad, kuse;  // (the K padding of dw stays as it is)
+};
+
+template <int G>
+__global__ void __launch_bounds__(256) k_wgrad_sum(WSum a) {
+  constexpr int T = 256 / G;
+  __shared__ double red[G > 1 ? G * T * 4 : 1];
+  const int tid = threadIdx.x, g = tid / T;
+  const long long nw = (long long)a.cout * a.kpad, q = ((long long)blockIdx.x * T + tid % T) * 4;
+  const bool bias = q >= nw;
+  const bool on = q < nw + (a.db ? a.cout : 0);
+  const float* p = bias ? a.part_b + (q - nw) : a.part + q;
+  const long long stride = bias ? a.cout : nw;
+  const int n = !on ? 0 : (bias ? a.splits_b : a.splits);
+  double t[4] = {0., 0., 0., 0.};
+#pragma unroll 4
+  for (int k = g; k < n; k += G) {
+    const f32x4 v = *(const f32x4*)(p + k * stride);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] += (double)v[j];
+  }
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[tid * 4 + j] = t[j];
+    __syncthreads();
+    if (g > 0) return;
+#pragma unroll
+    for (int k = 1; k < G; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t[j] += red[(k * T + tid) * 4 + j];
+  }
+  if (!on) return;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (bias)
+      a.db[q - nw + j] += (float)t[j];
+    else if ((int)(q % a.kpad) + j < a.kuse)
+      a.dw[q + j] += (float)t[j];
   }
 }
 
@@ -1760,6 +1889,8 @@ bool tensor_ok(const lbm_tensor5* t) {
          (t->ldc % 8) == 0 && t->ldc >= t->c && (((uintptr_t)t->ptr) & 15) == 0;
 }
 
+constexpr long long kBiasVoxels = 2048;  // voxels of a workgroup of k_bias_grad
+
 int outdim(int in, int stride) { return (in + stride - 1) / stride; }
 
 // bytes spanned by a channels-last view (last voxel's last channel included)
@@ -1931,37 +2062,16 @@ bool launch_rows(const DArgs& a, hipStream_t s) {
   return true;
 }
 
-// Workgroups N that share one tile of a weight gradient, at most `slots` in the
-// grid.  Each ends with one atomic per value of the tile: the memory side takes
-// the atomics of one address one after the other, about 0.16 us each, and about
-// 95 G/s in all, so N cost a step's time (us) times steps / N plus N times
-// (0.16 + tiles * values / 95000) us; N is where the two are equal.  Measured:
-// a 1x1x1 layer (256 addresses) 85 us with 512 workgroups, 44 with 80; batch 1
-// 128x64x64 32->32 129 us with 342, 76 with 90; batch 1 16x8x8 256->256 (96 tiles,
-// eight steps) 22 us undivided, 50 in eight.
-long long wgrad_splits(long long steps, long long tiles, long long values, long long slots, double step_us) {
-  const double each = 0.16 + (double)(tiles * values) / 95000.0;
-  const long long n = (long long)std::sqrt(step_us * (double)steps / each);
-  return std::max<long long>(1, std::min(std::min(slots / tiles, steps), n));
-}
-
-// Weight gradients of 3x3x3 layers by row steps: the grid holds about 768
-// workgroups (three per compute unit, see the kernel).
-template <int S, int BM, int WP>
-void launch_wgrad_rows_t(WArgs a, hipStream_t s) {
-  constexpr int RR = S == 1 && BM == 32 ? 8 : 4, DP = 32 / WP;
-  a.nhb = (a.gy.h + RR - 1) / RR;
-  a.nwb = (a.gy.w + WP - 1) / WP;
-  const long long steps = (long long)a.gy.n * ((a.gy.d + DP - 1) / DP) * a.nhb * a.nwb;
-  a.nco = (a.gy.c + BM - 1) / BM;
-  a.nci = (a.gx.c + 31) / 32;
-  const long long tiles = 3ll * a.nci * a.nco;
-  const long long n = wgrad_splits(steps, tiles, BM * 288, 768, 3.0), per = (steps + n - 1) / n;
-  a.steps = (int)steps;
-  a.per_wg = (int)per;
-  hipLaunchKernelGGL((k_conv_wgrad_rows<S, BM, WP>), dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(256), 0, s,
-                     a);
-}
+// How a weight gradient runs: its kernel and tile, its steps (kGeneral: voxels),
+// how many of them a workgroup takes, and the workgroups that so share a tile.
+struct WPlan {
+  enum Kind { kRows, kC8, kPoint, kGeneral } kind;
+  int bm = 0, wp = 0;        // kRows: output channels of a tile, voxels of a row along w (kC8 too)
+  int nhb = 0, nwb = 0, nco = 0, nci = 0;
+  long long steps = 0, tiles = 0, per_wg = 0;
+  long long splits = 0, splits_b = 0;  // (of the bias gradient)
+  long long floats(const Geo& gy, int kpad) const { return (splits * kpad + splits_b) * gy.c; }
+};
 
 // Voxels of a 32-voxel row along w: what pads the volume least, the longest of
 // equals.
@@ -1976,46 +2086,160 @@ int row_voxels(const Geo& g) {
   return best;
 }
 
+// Workgroups that share one tile of a weight gradient.  N of them cost a step's
+// time (us) times steps / N plus N times the end of each, and N is where the two
+// are equal, as long as one round (`slots` workgroups) holds them:
+//  * with a workspace (parts) the end is a store of the tile's values and their
+//    later sum, 8 bytes a value at about 4 TB/s;
+//  * without, one atomic per value: the memory side takes the atomics of one
+//    address one after the other, about 0.16 us each, and about 95 G/s in all.
+//    (A 1x1x1 layer, 256 addresses, 85 us with 512 workgroups, 44 with 80; batch
+//    1 128x64x64 32->32 129 us with 342, 76 with 90.)
+// A sum of n products one after the other is off by about sqrt(n / 2) * 2^-24, so
+// N also keeps the chains short (per_step products a step; V voxels, 32 a
+// product): with parts, which are added in FP64, to 24 + V / 3072 products; with
+// atomics, which go on in FP32, chain and adds together to 48 + V / 1536.
+void wgrad_splits(WPlan& p, long long V, int per_step, long long values, long long slots, double step_us, bool parts) {
+  const long long v32 = (V + 31) / 32, sum = p.steps * per_step;
+  const double each = (double)(p.tiles * values) * (parts ? 2e-6 : 1.0 / 95000.0) + (parts ? 0.0 : 0.16);
+  long long n = (long long)std::sqrt(step_us * (double)p.steps / each);
+  n = std::max<long long>(1, std::min(slots / p.tiles, n));
+  if (parts)
+    n = std::max(n, sum / (24 + v32 / 96));
+  else if (sum / n + n > 48 + v32 / 48)
+    n = std::max(n, std::min(v32 / 48, 2048 / p.tiles));
+  n = std::min(n, p.steps);
+  p.per_wg = (p.steps + n - 1) / n;
+  p.splits = p.splits_b = (p.steps + p.per_wg - 1) / p.per_wg;
+}
+
+template <int S, int BM, int WP>
+void launch_wgrad_rows_t(const WArgs& a, unsigned grid, hipStream_t s) {
+  hipLaunchKernelGGL((k_conv_wgrad_rows<S, BM, WP>), dim3(grid), dim3(256), 0, s, a);
+}
+
 template <int S, int BM>
-void launch_wgrad_rows(const WArgs& a, hipStream_t s) {
-  switch (row_voxels(a.gy)) {
-    case 32: launch_wgrad_rows_t<S, BM, 32>(a, s); break;
-    case 16: launch_wgrad_rows_t<S, BM, 16>(a, s); break;
-    default: launch_wgrad_rows_t<S, BM, 8>(a, s); break;
+void launch_wgrad_rows(const WArgs& a, int wp, unsigned grid, hipStream_t s) {
+  switch (wp) {
+    case 32: launch_wgrad_rows_t<S, BM, 32>(a, grid, s); break;
+    case 16: launch_wgrad_rows_t<S, BM, 16>(a, grid, s); break;
+    default: launch_wgrad_rows_t<S, BM, 8>(a, grid, s); break;
   }
 }
 
-template <int WP>
-void launch_wgrad_c8_t(WArgs a, hipStream_t s) {
-  constexpr int DP = 32 / WP;
-  a.nhb = (a.gy.h + 7) / 8;
-  a.nwb = (a.gy.w + WP - 1) / WP;
-  const long long steps = (long long)a.gy.n * ((a.gy.d + DP - 1) / DP) * a.nhb * a.nwb;
-  a.nco = (a.gy.c + 31) / 32;
-  const long long n = wgrad_splits(steps, a.nco, 32 * 216, 512, 2.5), per = (steps + n - 1) / n;
-  a.steps = (int)steps;
-  a.per_wg = (int)per;
-  hipLaunchKernelGGL(k_conv_wgrad_c8<WP>, dim3((unsigned)((steps + per - 1) / per * a.nco)), dim3(256), 0, s, a);
-}
-
-void launch_wgrad_c8(const WArgs& a, hipStream_t s) {
-  switch (row_voxels(a.gy)) {
-    case 32: launch_wgrad_c8_t<32>(a, s); break;
-    case 16: launch_wgrad_c8_t<16>(a, s); break;
-    default: launch_wgrad_c8_t<8>(a, s); break;
+WPlan wgrad_plan(const lbm_tensor5* x, const lbm_tensor5* dy, int ksize, int stride, bool parts) {
+  const Geo gx = geo_of(x), gy = geo_of(dy);
+  const long long V = (long long)gy.n * gy.d * gy.h * gy.w;
+  WPlan p;
+  // (1x1x1: the general kernel's wider tiles read the channels of large layers
+  // fewer times: 6 x 107x68x49 64->64 232 against 369 us; 8 x 32x16x16 256->128
+  // 114 against 56)
+  const long long tiles1 = (long long)((gx.c + 31) / 32) * ((gy.c + 31) / 32);
+  const bool wide1 = ksize == 1 && tiles1 >= 4 && V * tiles1 > 3000000;
+  // (a handful of stride-2 steps on channels off 32s: 6 x 4x13x6 24->64 8 us on
+  // the general kernel against 12)
+  const bool tiny = stride == 2 && gx.c % 32 != 0 && V < 4096;
+  const int kpad = lbm_conv_kpad(ksize * ksize * ksize, gx.c);
+  if (!tap_fits(x) || !tap_fits(dy) || V >= (1ll << 31) || (long long)gy.c * kpad >= (1ll << 30) || wide1 || tiny) {
+    p.kind = WPlan::kGeneral;
+    p.nco = (gy.c + BM - 1) / BM;
+    p.nci = (kpad + 63) / 64;
+    p.tiles = (long long)p.nco * p.nci;
+    // split the voxel range so that the grid holds about 2048 workgroups
+    p.per_wg = (V + std::max<long long>(1, 2048 / p.tiles) - 1) / std::max<long long>(1, 2048 / p.tiles);
+    p.per_wg = (p.per_wg + BK - 1) / BK * BK;
+    p.splits = (V + p.per_wg - 1) / p.per_wg;
+    p.splits_b = (V + kBiasVoxels - 1) / kBiasVoxels;
+    return p;
   }
+  if (ksize == 1) {
+    p.kind = WPlan::kPoint;
+    p.steps = (V + 511) / 512;  // steps of 512 voxels
+    p.nco = (gy.c + 31) / 32;
+    p.nci = (gx.c + 31) / 32;
+    p.tiles = (long long)p.nco * p.nci;
+    wgrad_splits(p, V, 2, 1024, 512, 1.0, parts);
+    return p;
+  }
+  const bool c8 = stride == 1 && gx.c == 8;
+  p.kind = c8 ? WPlan::kC8 : WPlan::kRows;
+  // 32-channel output tiles where 64 would be half empty
+  p.bm = c8 || (gy.c % 64 > 0 && gy.c % 64 <= 32) ? 32 : 64;
+  p.wp = row_voxels(gy);
+  const int rr = c8 || (stride == 1 && p.bm == 32) ? 8 : 4, dp = 32 / p.wp;
+  p.nhb = (gy.h + rr - 1) / rr;
+  p.nwb = (gy.w + p.wp - 1) / p.wp;
+  p.steps = (long long)gy.n * ((gy.d + dp - 1) / dp) * p.nhb * p.nwb;
+  p.nco = (gy.c + p.bm - 1) / p.bm;
+  p.nci = c8 ? 1 : (gx.c + 31) / 32;
+  p.tiles = (c8 ? 1ll : 3ll) * p.nci * p.nco;
+  if (c8)
+    wgrad_splits(p, V, 8, 32 * 216, 512, 2.5, parts);
+  else
+    wgrad_splits(p, V, stride == 2 && p.bm == 32 ? 2 : 4, p.bm * 288, 768, 3.0, parts);
+  return p;
 }
 
-// 1x1x1: steps of 512 voxels.
-void launch_wgrad_point(WArgs a, hipStream_t s) {
-  const long long V = (long long)a.gy.n * a.gy.d * a.gy.h * a.gy.w, steps = (V + 511) / 512;
-  a.nco = (a.gy.c + 31) / 32;
-  a.nci = (a.gx.c + 31) / 32;
-  const long long tiles = (long long)a.nco * a.nci;
-  const long long n = wgrad_splits(steps, tiles, 1024, 512, 1.0), per = (steps + n - 1) / n;
-  a.steps = (int)steps;
-  a.per_wg = (int)per;
-  hipLaunchKernelGGL(k_conv_wgrad_point, dim3((unsigned)((steps + per - 1) / per * tiles)), dim3(512), 0, s, a);
+// Floats of workspace that make the sums independent of the workgroups' order
+// (none where every value has one workgroup anyway).
+long long wgrad_floats(const WPlan& p, const Geo& gy, int kpad) {
+  return p.splits > 1 || p.splits_b > 1 ? p.floats(gy, kpad) : 0;
+}
+
+void launch_wgrad(const WPlan& p, const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* db, int ksize,
+                  int stride, float* part, hipStream_t s) {
+  WArgs a{};
+  a.x = (const uint16_t*)x->ptr;
+  a.gx = geo_of(x);
+  a.dy = (const uint16_t*)dy->ptr;
+  a.gy = geo_of(dy);
+  a.dw = dw;
+  a.db = db;
+  a.kpad = lbm_conv_kpad(ksize * ksize * ksize, x->c);
+  a.part = part;
+  a.part_b = part && db ? part + p.splits * a.kpad * a.gy.c : nullptr;
+  if (p.kind == WPlan::kGeneral) {
+    const dim3 g(p.nco, p.nci, (unsigned)p.splits);
+    hipLaunchKernelGGL(k_conv_wgrad, g, dim3(256), 0, s, a.x, a.gx, a.dy, a.gy, dw, part, a.kpad, x->c, ksize, stride,
+                       p.per_wg);
+    if (db)
+      hipLaunchKernelGGL(k_bias_grad, dim3((unsigned)p.splits_b), dim3(256), 0, s, a.dy, a.gy, db, a.part_b,
+                         kBiasVoxels);
+  } else {
+    a.x_bytes = (unsigned)view_bytes(x);
+    a.dy_bytes = (unsigned)view_bytes(dy);
+    a.nhb = p.nhb;
+    a.nwb = p.nwb;
+    a.nco = p.nco;
+    a.nci = p.nci;
+    a.steps = (int)p.steps;
+    a.per_wg = (int)p.per_wg;
+    const unsigned grid = (unsigned)(p.splits * p.tiles);
+    if (p.kind == WPlan::kPoint)
+      hipLaunchKernelGGL(k_conv_wgrad_point, dim3(grid), dim3(512), 0, s, a);
+    else if (p.kind == WPlan::kC8 && p.wp == 32)
+      hipLaunchKernelGGL(k_conv_wgrad_c8<32>, dim3(grid), dim3(256), 0, s, a);
+    else if (p.kind == WPlan::kC8 && p.wp == 16)
+      hipLaunchKernelGGL(k_conv_wgrad_c8<16>, dim3(grid), dim3(256), 0, s, a);
+    else if (p.kind == WPlan::kC8)
+      hipLaunchKernelGGL(k_conv_wgrad_c8<8>, dim3(grid), dim3(256), 0, s, a);
+    else if (stride == 2 && p.bm == 32)
+      launch_wgrad_rows<2, 32>(a, p.wp, grid, s);
+    else if (stride == 2)
+      launch_wgrad_rows<2, 64>(a, p.wp, grid, s);
+    else if (p.bm == 32)
+      launch_wgrad_rows<1, 32>(a, p.wp, grid, s);
+    else
+      launch_wgrad_rows<1, 64>(a, p.wp, grid, s);
+  }
+  if (!part) return;
+  const WSum w{part, a.part_b, dw, db, (int)p.splits, (int)p.splits_b, a.gy.c, a.kpad, ksize * ksize * ksize * x->c};
+  const long long q = ((long long)a.gy.c * a.kpad + a.gy.c) / 4;  // values in fours
+  // (sixteen parts or more: eight groups a block, see the kernel)
+  if (std::max(p.splits, p.splits_b) >= 16)
+    hipLaunchKernelGGL(k_wgrad_sum<8>, dim3((unsigned)((q + 31) / 32)), dim3(256), 0, s, w);
+  else
+    hipLaunchKernelGGL(k_wgrad_sum<1>, dim3((unsigned)((q + 255) / 256)), dim3(256), 0, s, w);
 }
 
 // Rows (n, d, h) by y, (w, channel group) pairs by x.
@@ -2126,70 +2350,36 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
+static bool wgrad_ok(const lbm_tensor5* x, const lbm_tensor5* dy, int32_t ksize, int32_t stride) {
+  if (!tensor_ok(x) || !tensor_ok(dy) || (ksize != 1 && ksize != 3) || (stride != 1 && stride != 2) ||
+      (ksize == 1 && stride != 1))
+    return false;
+  return dy->n == x->n && dy->d == outdim(x->d, stride) && dy->h == outdim(x->h, stride) &&
+         dy->w == outdim(x->w, stride);
+}
+
 lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* dbias,
                                  int32_t ksize, int32_t stride, void* stream) {
-  if (!tensor_ok(x) || !tensor_ok(dy) || !dw || (ksize != 1 && ksize != 3) || (stride != 1 && stride != 2) ||
-      (ksize == 1 && stride != 1))
-    return LBM_EINVAL;
-  if (dy->n != x->n || dy->d != outdim(x->d, stride) || dy->h != outdim(x->h, stride) || dy->w != outdim(x->w, stride))
-    return LBM_EINVAL;
-  if (dbias && dy->c > 2048) return LBM_EINVAL;
-  const int taps = ksize * ksize * ksize;
-  const int kpad = lbm_conv_kpad(taps, x->c);
-  const long long V = (long long)dy->n * dy->d * dy->h * dy->w;
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 b(256);
-  const bool fits = tap_fits(x) && tap_fits(dy) && V < (1ll << 31);
-  // (1x1x1: the general kernel's wider tiles read the channels of large layers
-  // fewer times: 6 x 107x68x49 64->64 232 against 369 us; 8 x 32x16x16 256->128
-  // 114 against 56)
-  const long long tiles1 = (long long)((x->c + 31) / 32) * ((dy->c + 31) / 32);
-  const bool wide1 = ksize == 1 && tiles1 >= 4 && V * tiles1 > 3000000;
-  // (a handful of stride-2 steps on channels off 32s: 6 x 4x13x6 24->64 8 us on
-  // the general kernel against 12)
-  const bool tiny = stride == 2 && x->c % 32 != 0 && V < 4096;
-  if (fits && !wide1 && !tiny) {
-    WArgs a{};
-    a.x = (const uint16_t*)x->ptr;
-    a.gx = geo_of(x);
-    a.x_bytes = (unsigned)view_bytes(x);
-    a.dy = (const uint16_t*)dy->ptr;
-    a.gy = geo_of(dy);
-    a.dy_bytes = (unsigned)view_bytes(dy);
-    a.dw = dw;
-    a.db = dbias;
-    a.kpad = kpad;
-    // 32-channel output tiles where 64 would be half empty
-    const bool half = dy->c % 64 > 0 && dy->c % 64 <= 32;
-    if (ksize == 1)
-      launch_wgrad_point(a, s);
-    else if (stride == 2 && half)
-      launch_wgrad_rows<2, 32>(a, s);
-    else if (stride == 2)
-      launch_wgrad_rows<2, 64>(a, s);
-    else if (x->c == 8)
-      launch_wgrad_c8(a, s);
-    else if (half)
-      launch_wgrad_rows<1, 32>(a, s);
-    else
-      launch_wgrad_rows<1, 64>(a, s);
-    return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
-  }
-  const int gm = (dy->c + BM - 1) / BM, gn = (kpad + 63) / 64;
-  // split the voxel range so that the grid holds about 2048 workgroups
-  long long splits = 2048 / (gm * gn);
-  if (splits < 1) splits = 1;
-  long long per = (V + splits - 1) / splits;
-  per = ((per + BK - 1) / BK) * BK;
-  splits = (V + per - 1) / per;
-  dim3 g(gm, gn, (unsigned)splits);
-  hipLaunchKernelGGL(k_conv_wgrad, g, b, 0, s, (const uint16_t*)x->ptr, geo_of(x), (const uint16_t*)dy->ptr,
-                     geo_of(dy), dw, kpad, x->c, ksize, stride, per);
-  if (dbias) {
-    const long long pb = 2048;
-    hipLaunchKernelGGL(k_bias_grad, dim3((unsigned)((V + pb - 1) / pb)), b, 0, s, (const uint16_t*)dy->ptr,
-                       geo_of(dy), dbias, pb);
-  }
+  if (!wgrad_ok(x, dy, ksize, stride) || !dw || (dbias && dy->c > 2048)) return LBM_EINVAL;
+  launch_wgrad(wgrad_plan(x, dy, ksize, stride, false), x, dy, dw, dbias, ksize, stride, nullptr,
+               (hipStream_t)stream);
+  return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
+}
+
+int64_t lbm_conv3d_bwd_weight_scratch(const lbm_tensor5* x, const lbm_tensor5* dy, int32_t ksize, int32_t stride) {
+  if (!wgrad_ok(x, dy, ksize, stride)) return -1;
+  return 4 * wgrad_floats(wgrad_plan(x, dy, ksize, stride, true), geo_of(dy),
+                          lbm_conv_kpad(ksize * ksize * ksize, x->c));
+}
+
+lbm_status lbm_conv3d_bwd_weight_ordered(const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* dbias,
+                                         int32_t ksize, int32_t stride, void* scratch, int64_t scratch_bytes,
+                                         void* stream) {
+  if (!wgrad_ok(x, dy, ksize, stride) || !dw || (dbias && dy->c > 2048)) return LBM_EINVAL;
+  const WPlan p = wgrad_plan(x, dy, ksize, stride, true);
+  const int64_t need = 4 * wgrad_floats(p, geo_of(dy), lbm_conv_kpad(ksize * ksize * ksize, x->c));
+  if (need > 0 && (!scratch || scratch_bytes < need || ((uintptr_t)scratch & 15))) return LBM_EINVAL;
+  launch_wgrad(p, x, dy, dw, dbias, ksize, stride, need > 0 ? (float*)scratch : nullptr, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 

@@ -16,6 +16,7 @@ concatenation, ReLU, and a 1x1x1 head.
 """
 import ctypes
 import math
+import threading
 
 import numpy as np
 
@@ -31,7 +32,7 @@ class lbm_tensor5(ctypes.Structure):
 
 
 SYMBOLS = ["lbm_conv_kpad", "lbm_conv3d_fwd", "lbm_conv3d_bwd_data", "lbm_conv3d_bwd_weight",
-           "lbm_conv3d_weight_t", "lbm_upsample2", "lbm_upsample2_bwd", "lbm_mse_loss", "lbm_adam_step",
+           "lbm_conv3d_bwd_weight_scratch", "lbm_conv3d_bwd_weight_ordered", "lbm_conv3d_weight_t", "lbm_upsample2", "lbm_upsample2_bwd", "lbm_mse_loss", "lbm_adam_step",
            "lbm_surrogate_input", "lbm_surrogate_target", "lbm_surrogate_fields"]
 
 
@@ -48,6 +49,7 @@ def lib():
             "lbm_conv3d_fwd": [T, P, P, T, i32, i32, i32, P],
             "lbm_conv3d_bwd_data": [T, P, T, T, i32, i32, i32, P],
             "lbm_conv3d_bwd_weight": [T, T, P, P, i32, i32, P],
+            "lbm_conv3d_bwd_weight_ordered": [T, T, P, P, i32, i32, P, ctypes.c_int64, P],
             "lbm_conv3d_weight_t": [P, i32, i32, i32, P, P, P],
             "lbm_upsample2": [T, T, P],
             "lbm_upsample2_bwd": [T, T, i32, P],
@@ -63,6 +65,8 @@ def lib():
             fn.restype = ctypes.c_int
         L.lbm_conv_kpad.argtypes = [i32, i32]
         L.lbm_conv_kpad.restype = i32
+        L.lbm_conv3d_bwd_weight_scratch.argtypes = [T, T, i32, i32]
+        L.lbm_conv3d_bwd_weight_scratch.restype = ctypes.c_int64
         _sig_done = True
     return L
 
@@ -118,6 +122,42 @@ def from_numpy(a):
     return t
 
 
+class Scratch:
+    """Device memory for the partial sums of weight gradients: one buffer per
+    stream (so that streams do not share one), grown to the largest request and
+    kept until this object goes; at most four streams' buffers at a time.
+    Allocated on the stream that uses it, so the allocator hands a dropped
+    buffer's memory on only in that stream's order.  Hold ``lock`` from ``get``
+    until the work that uses the buffer is enqueued."""
+
+    STREAMS = 4
+
+    def __init__(self):
+        self.lock = threading.Lock()
+        self._bufs = {}
+
+    def __reduce__(self):   # a copy starts with no buffers
+        return (Scratch, ())
+
+    def get(self, nbytes, stream):
+        """A buffer of at least nbytes for work on `stream` (a raw handle, None: the
+        null stream), or None while that stream is being captured and the buffer
+        at hand is too small (a capture allocates nothing)."""
+        import torch
+        key = (torch.cuda.current_device(), int(stream or 0))
+        buf = self._bufs.get(key)
+        if buf is None or buf.numel() < nbytes:
+            on = torch.cuda.ExternalStream(key[1]) if key[1] else torch.cuda.default_stream()
+            with torch.cuda.stream(on):
+                if torch.cuda.is_current_stream_capturing():
+                    return None
+                self._bufs.pop(key, None)
+                while len(self._bufs) >= self.STREAMS:
+                    self._bufs.pop(next(iter(self._bufs)))
+                buf = self._bufs[key] = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        return buf
+
+
 class Conv:
     """One convolution layer: FP32 master weights w[co][kpad] (K-major,
     k = tap*cin + ci), FP32 bias, BF16 forward and transposed copies, grads and
@@ -143,6 +183,7 @@ class Conv:
         self.gb = torch.zeros_like(self.b)
         self.mw, self.vw = torch.zeros_like(self.w), torch.zeros_like(self.w)
         self.mb, self.vb = torch.zeros_like(self.b), torch.zeros_like(self.b)
+        self.scratch = Scratch()   # (layers that run one after the other may share one)
         self.refresh()
 
     def set_weights(self, w_co_t_ci, b):
@@ -164,10 +205,21 @@ class Conv:
 
     def backward(self, x, dy, dx, x_act=True, accumulate=False, stream=None):
         """Accumulate weight grads; write (or add) dx masked by ReLU'(x) when x
-        came out of a ReLU layer (x_act)."""
+        came out of a ReLU layer (x_act).  The weight grads' sums have a fixed
+        order, so that a repeated step repeats bit for bit; only in a capture that
+        finds no scratch memory from an earlier call are they atomics' sums."""
         L = lib()
-        _ck(L.lbm_conv3d_bwd_weight(x.ref, dy.ref, self.gw.data_ptr(), self.gb.data_ptr(), self.k, self.stride,
-                                    stream), "lbm_conv3d_bwd_weight")
+        need = L.lbm_conv3d_bwd_weight_scratch(x.ref, dy.ref, self.k, self.stride)
+        with self.scratch.lock:
+            buf = self.scratch.get(need, stream) if need > 0 else None
+            if need > 0 and buf is None:
+                st = L.lbm_conv3d_bwd_weight(x.ref, dy.ref, self.gw.data_ptr(), self.gb.data_ptr(), self.k,
+                                             self.stride, stream)
+            else:
+                st = L.lbm_conv3d_bwd_weight_ordered(x.ref, dy.ref, self.gw.data_ptr(), self.gb.data_ptr(), self.k,
+                                                     self.stride, buf.data_ptr() if need > 0 else None,
+                                                     need if need > 0 else 0, stream)
+        _ck(st, "lbm_conv3d_bwd_weight")
         if dx is not None:
             _ck(L.lbm_conv3d_bwd_data(dy.ref, self.wt.data_ptr(), dx.ref, x.ref if x_act else None, self.k,
                                       self.stride, 1 if accumulate else 0, stream), "lbm_conv3d_bwd_data")
@@ -212,6 +264,9 @@ class UNet:
         self.layers = [self.e0a, self.e0b, self.dn0, self.e1a, self.e1b, self.dn1, self.e2a, self.e2b, self.dn2,
                        self.e3a, self.e3b, self.up2, self.d2a, self.d2b, self.up1, self.d1a, self.d1b, self.up0,
                        self.d0a, self.d0b, self.head]
+        scratch = Scratch()   # one for all: a pass runs layer after layer
+        for layer in self.layers:
+            layer.scratch = scratch
         self._alloc()
         self.t = 0
 
