@@ -73,6 +73,16 @@ lbm_status lbm_conv3d_bwd_weight_ordered(const lbm_tensor5* x, const lbm_tensor5
                                          int32_t ksize, int32_t stride, void* scratch, int64_t scratch_bytes,
                                          void* stream);
 
+/* The kernel that a call on these shapes runs (for tests and studies; chosen by
+ * shape alone): pass 0 forward (x, y), 1 input gradient (dx, dy), 2 weight
+ * gradient (x, dy).  -1: bad shapes. */
+enum {
+  LBM_CONV_GENERAL = 0, LBM_CONV_TAP = 1, LBM_CONV_POINT = 2, LBM_CONV_C8 = 3, LBM_CONV_ROWS2 = 4,
+  LBM_CONV_ROWS4 = 5, LBM_CONV_PLANE_SMALL = 6, LBM_CONV_PLANE_MID = 7, LBM_CONV_PLANE_BIG = 8, LBM_CONV_UP = 9,
+  LBM_WGRAD_GENERAL = 16, LBM_WGRAD_POINT = 17, LBM_WGRAD_C8 = 18, LBM_WGRAD_ROWS32 = 19, LBM_WGRAD_ROWS64 = 20
+};
+int32_t lbm_conv3d_kernel(int32_t pass, const lbm_tensor5* x, const lbm_tensor5* y, int32_t ksize, int32_t stride);
+
 /* Transposed weight for lbm_conv3d_bwd_data: wt[ci][t*Cout + co] (padded to
  * lbm_conv_kpad(taps, cout)) from w[co][t*Cin + ci]; FP32 master -> BF16. */
 lbm_status lbm_conv3d_weight_t(const float* w_master, int32_t taps, int32_t cin, int32_t cout,

@@ -1157,8 +1157,8 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 // in LDS, by the workgroups of kernel plane 0 and input-channel tile 0 (each
 // dy tile once).  A workgroup owns one kernel plane kd, 32 input channels and
 // BM output channels, i.e. a BM x (9 taps x 32) block of dw, and walks steps of
-// RR rows of 32 voxels of dy (a row: 32 along w, or 16 or 8 along w of two or
-// four planes, whichever pads the volume least).  Per step it brings the dy
+// RR rows of 32 voxels of dy (a row: 32 along w, or WP along w of 32 / WP planes,
+// whichever pads the volume least).  Per step it brings the dy
 // tile and the x halo of plane d S + kd - 1, the sources of all nine (kh, kw)
 // taps, into LDS by 16-byte buffer loads that write LDS directly; both MFMA
 // operands (voxels as K) are then transposing reads (ds_read_b64_tr_b16: a
@@ -1187,7 +1187,7 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 // 128x64x64 32->64 141 -> 126; batch 1 128x64x64 32->32 136 -> 49.  Bound by HBM at
 // full resolution, by LDS reads and MFMAs otherwise.
 template <int S, int BM, int WP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2 || WP == 8 ? 2 : (BM == 64 && WP == 32 ? 3 : 4)))) k_conv_wgrad_rows(WArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2 || WP <= 8 ? 2 : (BM == 64 && WP == 32 ? 3 : 4)))) k_conv_wgrad_rows(WArgs a) {
   constexpr int KS = BM == 32 ? 2 : 1;             // waves that share a dw tile, each with RW of a step's rows
   constexpr int RW = S == 2 && BM == 32 ? 2 : 4;   // (eight rows of stride 2 would leave one workgroup per compute unit)
   constexpr int RR = RW * KS;
@@ -1225,7 +1225,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2
     const int v = (id >> 2) % (RR * 32), hf = (id >> 2) / (RR * 32), r = v / 32, c = v % WP, p = v % 32 / WP;
     const int ch = co0 + hf * 32 + (id & 3) * 8;
     apos[i] = ch < gy.c ? r | c << 8 | p << 16 : -1;
-    adl[i] = ((p * gy.h + r) * gy.w + c) * gy.ldc + ch;
+    adl[i] = (int)((((unsigned)p * gy.h + r) * gy.w + c) * gy.ldc + ch);  // (may wrap past the volume)
   }
 #pragma unroll
   for (int i = 0; i < SX; ++i) {
@@ -1234,7 +1234,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2
     const int q = S == 1 ? id & 3 : (id & 3) ^ (((c >> 2) & 1) << 1);
     const int ch = ci0 + q * 8;
     xpos[i] = cell < CELLS && ch < gx.c ? r | c << 8 | p << 16 : -1;
-    xdl[i] = ((p * S * gx.h + r) * gx.w + c) * gx.ldc + ch;
+    xdl[i] = (int)((((unsigned)p * S * gx.h + r) * gx.w + c) * gx.ldc + ch);
   }
   // operand reads: 16-lane group g covers voxels 8 g .. 8 g + 7 of a row, half
   // hh the voxels 8 g + 4 hh .. + 3; lane L addresses voxel L / 4, channels
@@ -1947,42 +1947,35 @@ struct PlaneTile {
 
 // The tap-major kernel's time alike: rounds of 512 workgroups, 0.75 us per K
 // step of a 128 x 128 tile, half with 64 columns (launch_tap_cols).
-double tap_us(const DArgs& a) {
-  const long long rows = ((long long)a.go.n * a.go.d * a.go.h * a.go.w + 127) / 128;
-  const int steps = a.ksize * a.ksize * a.ksize * (a.C / 32);
-  const long long wide = rows * ((a.go.c + 127) / 128);
-  if (a.go.c > 64 && wide >= 512) return (double)((wide + 511) / 512) * 0.75 * steps;
-  return (double)((rows * ((a.go.c + 63) / 64) + 511) / 512) * 0.37 * steps;
+double tap_us(const Geo& go, int ksize, int C) {
+  const long long rows = ((long long)go.n * go.d * go.h * go.w + 127) / 128;
+  const int steps = ksize * ksize * ksize * (C / 32);
+  const long long wide = rows * ((go.c + 127) / 128);
+  if (go.c > 64 && wide >= 512) return (double)((wide + 511) / 512) * 0.75 * steps;
+  return (double)((rows * ((go.c + 63) / 64) + 511) / 512) * 0.37 * steps;
 }
 
-// false: the tap-major kernel, whose result is the same, is the faster one
+// The products that keep the tap-by-tap order of their sums (see pick_rows),
+// for the channel counts the plane kernel holds in LDS: its fastest shape, or
+// the tap-major kernel, whose result is the same, where that is the faster one
 // (widths that fill the tiles badly: 42x37x19 at batch 4, 128->256, 312 against
-// 366 us on plane tiles, its input gradient 335 against 468)
-template <int MODE, int NC>
-bool launch_plane_c(const DArgs& a, hipStream_t s) {
-  using Small = PlaneTile<MODE, NC, 8, 1, 1>;
-  using Mid = PlaneTile<MODE, NC, 8, 2, 1>;
-  using Big = PlaneTile<MODE, NC, 16, 2, 2>;
-  const double cs = Small::us(a.go), cm = Mid::us(a.go), cb = Big::us(a.go);
-  if (tap_us(a) < std::min(cs, std::min(cm, cb))) return false;
-  if (cb < cm && cb < cs)
-    Big::launch(a, s);
-  else if (cm <= cs)
-    Mid::launch(a, s);
-  else
-    Small::launch(a, s);
-  return true;
+// 366 us on plane tiles, its input gradient 335 against 468).
+template <int NC>
+int32_t pick_plane(const Geo& go) {
+  const double cs = PlaneTile<0, NC, 8, 1, 1>::us(go), cm = PlaneTile<0, NC, 8, 2, 1>::us(go),
+               cb = PlaneTile<0, NC, 16, 2, 2>::us(go);
+  if (tap_us(go, 3, NC * 32) < std::min(cs, std::min(cm, cb))) return LBM_CONV_TAP;
+  return cb < cm && cb < cs ? LBM_CONV_PLANE_BIG : (cm <= cs ? LBM_CONV_PLANE_MID : LBM_CONV_PLANE_SMALL);
 }
 
-// The products that keep the tap-by-tap order of their sums (see launch_rows),
-// for the channel counts the plane kernel holds in LDS.
-template <int MODE>
-bool launch_plane(const DArgs& a, hipStream_t s) {
-  switch (a.C) {
-    case 64: return launch_plane_c<MODE, 2>(a, s);
-    case 128: return launch_plane_c<MODE, 4>(a, s);
-    default: return launch_plane_c<MODE, 8>(a, s);
-  }
+template <int MODE, int NC>
+void launch_plane(const DArgs& a, int32_t k, hipStream_t s) {
+  if (k == LBM_CONV_PLANE_BIG)
+    PlaneTile<MODE, NC, 16, 2, 2>::launch(a, s);
+  else if (k == LBM_CONV_PLANE_MID)
+    PlaneTile<MODE, NC, 8, 2, 1>::launch(a, s);
+  else
+    PlaneTile<MODE, NC, 8, 1, 1>::launch(a, s);
 }
 
 template <int NC, int R>
@@ -1997,21 +1990,16 @@ void launch_up_t(const DArgs& a, hipStream_t s) {
 // 32 <- 64: 86 us against 64; 100x100x22, 0.6 filled: 90 against 172).  128
 // channels take the LDS to one workgroup a CU: 80 us against 104 on 64x32x32
 // 64 <- 128, but 621 against 549 on 40x40x64 256 <- 128.
-bool launch_up(const DArgs& a, hipStream_t s) {
-  const long long full = (long long)((a.gs.w + 15) / 16 * 16) * ((a.gs.h + 7) / 8 * 8);
-  if ((a.C != 32 && a.C != 64) || 2 * (long long)a.gs.w * a.gs.h < full) return false;
-  if (a.C == 32)
-    launch_up_t<1, 2>(a, s);
-  else
-    launch_up_t<2, 2>(a, s);
-  return true;
+bool up_fits(const Geo& gs) {
+  const long long full = (long long)((gs.w + 15) / 16 * 16) * ((gs.h + 7) / 8 * 8);
+  return (gs.c == 32 || gs.c == 64) && 2 * (long long)gs.w * gs.h >= full;
 }
 
 // 1x1x1 layers onto at most 32 channels, or with channels off 32s; onto more,
 // the tap-major kernel's wider column tiles read the input fewer times (8 x
 // 32x16x16 256->128: 25.9 against 28.2 us).
-bool point_fits(int ksize, const lbm_tensor5* src, const lbm_tensor5* out) {
-  return ksize == 1 && (out->c <= 32 || src->c % 32 != 0);
+bool point_fits(int ksize, const Geo& src, const Geo& out) {
+  return ksize == 1 && (out.c <= 32 || src.c % 32 != 0);
 }
 
 void launch_point(const DArgs& a, hipStream_t s) {
@@ -2019,7 +2007,12 @@ void launch_point(const DArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_conv_point, dim3((unsigned)((V + 255) / 256), (unsigned)((a.go.c + 31) / 32)), dim3(256), 0, s, a);
 }
 
-// Workgroups of the row-tile kernel with R rows per wave.
+// Workgroups of the 8-channel forward, and of the row-tile kernel with R rows
+// per wave.
+long long c8_tiles(const Geo& go) {
+  return (long long)((go.w + 15) / 16) * ((go.h + 15) / 16) * ((go.d + 3) / 4) * go.n * ((go.c + 31) / 32);
+}
+
 template <int R>
 long long row_tiles(const Geo& go) {
   return (long long)((go.w + 15) / 16) * ((go.h + 4 * R - 1) / (4 * R)) * go.d * go.n * ((go.c + 31) / 32);
@@ -2029,43 +2022,123 @@ long long row_tiles(const Geo& go) {
 // would leave compute units without a workgroup (batch 1, 32x16x16 128->128:
 // 18.6 -> 16.7 us on 128 tiles) or pad the rows enough to lose what the
 // smaller ones lose in operand reuse (1180 against 1000 TFLOP/s at 64x32x32
-// 64->64).  Very narrow volumes, where even the small tiles are mostly padding
-// (at half, 16x8x8, they still take 52 against 89 us), keep the tap-major
-// kernel, which takes voxels in any shape but channels in 32s.  Products of 64,
-// 128 or 256 channels off rows of whole 32s or onto more than 64 channels go to
-// the plane kernel, whose sums run tap by tap over all chunks: results rounded
-// otherwise would flip ReLU masks all through a network's passes, so the order
-// of those sums is kept (the input gradient of 32x16x16 256->128 at batch 8
-// takes 112 us there against 91 on row tiles, 64x32x32 128->64 234 against 222).
+// 64->64).  Where even the small tiles are less than a quarter filled, and those
+// of the 8-channel forward less than an eighth, the volume goes to the kernels
+// that take voxels in any shape: the tap-major one, or, with channels off 32s,
+// the general one (1 x 65536x1x1 40->48 forward 40 us there against 1150 on row
+// tiles, 1 x 4096x4x4, an eighth filled, 48 against 85, 1 x 682x4x24, three
+// eighths, 48 against 36; 8->32 forward at a sixteenth 13.7 against 17.5, at
+// 3/16 14.0 against 13.0).  Products of 64, 128 or 256 channels off rows of whole
+// 32s or onto more than 64 channels go to the plane kernel, whose sums run tap
+// by tap over all chunks.  That line is one of rounding, not of speed: it is
+// where a layer's sums have always changed their order, and results rounded
+// otherwise would flip ReLU masks all through a trained network's passes (row
+// tiles would take the input gradient of 32x16x16 256->128 at batch 8 from 116 to
+// about 91 us).  So the order depends on whether the width is a multiple of 32.
 template <int MODE>
-bool launch_rows(const DArgs& a, hipStream_t s) {
-  const long long big = row_tiles<4>(a.go), small = row_tiles<2>(a.go);
-  const long long vox = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
-  if (MODE == 0 && a.C == 8) {
-    const long long g = (long long)((a.go.w + 15) / 16) * ((a.go.h + 15) / 16) * ((a.go.d + 3) / 4) * a.go.n *
-                        ((a.go.c + 31) / 32);
-    hipLaunchKernelGGL(k_conv_fwd_c8, dim3((unsigned)g), dim3(256), 0, s, a);
-    return true;
+int32_t pick_rows(const Geo& gs, const Geo& go) {
+  const long long big = row_tiles<4>(go), small = row_tiles<2>(go);
+  const long long vox = (long long)go.n * go.d * go.h * go.w, nct = (go.c + 31) / 32;
+  const int C = gs.c;
+  if (MODE == 0 && C == 8) return c8_tiles(go) * 1024 > 8 * vox * nct ? LBM_CONV_GENERAL : LBM_CONV_C8;
+  if (go.w % 32 != 0 || go.c > 64) {
+    if (C == 64) return pick_plane<2>(go);
+    if (C == 128) return pick_plane<4>(go);
+    if (C == 256) return pick_plane<8>(go);
   }
-  if ((a.go.w % 32 != 0 || a.go.c > 64) && (a.C == 64 || a.C == 128 || a.C == 256)) return launch_plane<MODE>(a, s);
-  if (a.C % 32 == 0 && small * 128 > 4 * vox * ((a.go.c + 31) / 32)) return false;
-  const bool four = big >= 256 && big * 2 <= small * 1.22, tail = a.C % 32 != 0;
-  const dim3 g((unsigned)(four ? big : small)), b(256);
-  if (four && tail)
-    hipLaunchKernelGGL((k_conv_rows<MODE, 4, true>), g, b, 0, s, a);
-  else if (four)
-    hipLaunchKernelGGL((k_conv_rows<MODE, 4, false>), g, b, 0, s, a);
-  else if (tail)
-    hipLaunchKernelGGL((k_conv_rows<MODE, 2, true>), g, b, 0, s, a);
-  else
-    hipLaunchKernelGGL((k_conv_rows<MODE, 2, false>), g, b, 0, s, a);
-  return true;
+  if (small * 128 > 4 * vox * nct) return C % 32 == 0 ? LBM_CONV_TAP : LBM_CONV_GENERAL;
+  return big >= 256 && big * 2 <= small * 1.22 ? LBM_CONV_ROWS4 : LBM_CONV_ROWS2;
+}
+
+// The kernel of a forward (MODE 0: gs = x, go = y) or input-gradient (gs = dy,
+// go = dx) product.
+template <int MODE>
+int32_t pick_conv(const Geo& gs, const Geo& go, int ksize, int stride, bool fits) {
+  if (!fits) return LBM_CONV_GENERAL;
+  if (point_fits(ksize, gs, go)) return LBM_CONV_POINT;
+  if (ksize == 3 && stride == 1) return pick_rows<MODE>(gs, go);
+  if (gs.c % 32 != 0) return LBM_CONV_GENERAL;
+  return MODE == 1 && stride == 2 && up_fits(gs) ? LBM_CONV_UP : LBM_CONV_TAP;
+}
+
+template <int MODE, int BN>
+void launch_gemm(const DArgs& a, hipStream_t s) {
+  const long long M = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
+  const dim3 g((unsigned)((M + BM - 1) / BM), (a.go.c + BN - 1) / BN);
+  hipLaunchKernelGGL((k_conv_gemm<MODE, BN>), g, dim3(256), 0, s, a.src, a.gs, a.wk, a.kstride, a.bias, a.out, a.go,
+                     a.act, a.act_ldc, a.ksize, a.stride, a.relu, a.accumulate, a.C);
+}
+
+template <int MODE>
+void launch_conv(const DArgs& a, int32_t k, hipStream_t s) {
+  const long long M = (long long)a.go.n * a.go.d * a.go.h * a.go.w;
+  const bool tail = a.C % 32 != 0;
+  const dim3 b(256);
+  switch (k) {
+    case LBM_CONV_GENERAL:
+      if (a.go.c <= 16)
+        launch_gemm<MODE, 16>(a, s);
+      else if (a.go.c <= 32)
+        launch_gemm<MODE, 32>(a, s);
+      else
+        launch_gemm<MODE, 64>(a, s);
+      break;
+    case LBM_CONV_POINT: launch_point(a, s); break;
+    case LBM_CONV_C8:
+      if constexpr (MODE == 0) hipLaunchKernelGGL(k_conv_fwd_c8, dim3((unsigned)c8_tiles(a.go)), b, 0, s, a);
+      break;
+    case LBM_CONV_ROWS2:
+    case LBM_CONV_ROWS4: {
+      const bool four = k == LBM_CONV_ROWS4;
+      const dim3 g((unsigned)(four ? row_tiles<4>(a.go) : row_tiles<2>(a.go)));
+      if (four && tail)
+        hipLaunchKernelGGL((k_conv_rows<MODE, 4, true>), g, b, 0, s, a);
+      else if (four)
+        hipLaunchKernelGGL((k_conv_rows<MODE, 4, false>), g, b, 0, s, a);
+      else if (tail)
+        hipLaunchKernelGGL((k_conv_rows<MODE, 2, true>), g, b, 0, s, a);
+      else
+        hipLaunchKernelGGL((k_conv_rows<MODE, 2, false>), g, b, 0, s, a);
+      break;
+    }
+    case LBM_CONV_PLANE_SMALL:
+    case LBM_CONV_PLANE_MID:
+    case LBM_CONV_PLANE_BIG:
+      if (a.C == 64)
+        launch_plane<MODE, 2>(a, k, s);
+      else if (a.C == 128)
+        launch_plane<MODE, 4>(a, k, s);
+      else
+        launch_plane<MODE, 8>(a, k, s);
+      break;
+    case LBM_CONV_UP:
+      if constexpr (MODE == 1) {
+        if (a.C == 32)
+          launch_up_t<1, 2>(a, s);
+        else
+          launch_up_t<2, 2>(a, s);
+      }
+      break;
+    default:
+      if (MODE == 1 && a.stride == 2) {
+        // rows of the largest parity class; smaller classes mask their tail
+        const long long rows = (long long)a.go.n * ((a.go.d + 1) / 2) * ((a.go.h + 1) / 2) * ((a.go.w + 1) / 2);
+        launch_tap_cols<MODE, MODE == 1>(a, rows, 8, s);
+      } else {
+        launch_tap_cols<MODE, false>(a, M, 1, s);
+      }
+  }
+}
+
+// Whether the kernels that index in 32 bits take the call.
+bool conv_fits(const lbm_tensor5* src, const lbm_tensor5* out, int kpad) {
+  return tap_fits(src) && tap_fits(out) && (long long)out->c * kpad < (1ll << 30);
 }
 
 // How a weight gradient runs: its kernel and tile, its steps (kGeneral: voxels),
 // how many of them a workgroup takes, and the workgroups that so share a tile.
 struct WPlan {
-  enum Kind { kRows, kC8, kPoint, kGeneral } kind;
+  enum Kind { kRows, kC8, kPoint, kGeneral } kind = kGeneral;
   int bm = 0, wp = 0;        // kRows: output channels of a tile, voxels of a row along w (kC8 too)
   int nhb = 0, nwb = 0, nco = 0, nci = 0;
   long long steps = 0, tiles = 0, per_wg = 0;
@@ -2074,14 +2147,16 @@ struct WPlan {
 };
 
 // Voxels of a 32-voxel row along w: what pads the volume least, the longest of
-// equals.
-int row_voxels(const Geo& g) {
+// equals.  Rows under 8 long, whose halo has up to three cells a voxel, only
+// where they save a third (64->64, 1 x 1024x64x1 34 us, 118 on rows of 8; 1 x
+// 4096x4x4 31 against 42).
+int row_voxels(const Geo& g, int shortest) {
   int best = 32;
   long long least = -1;
-  for (int wp = 32; wp >= 8; wp /= 2) {
+  for (int wp = 32; wp >= shortest; wp /= 2) {
     const int dp = 32 / wp;
     const long long p = (long long)((g.w + wp - 1) / wp) * wp * ((g.d + dp - 1) / dp) * dp;
-    if (least < 0 || p < least) least = p, best = wp;
+    if (least < 0 || (wp < 8 ? 3 * p < 2 * least : p < least)) least = p, best = wp;
   }
   return best;
 }
@@ -2123,7 +2198,10 @@ void launch_wgrad_rows(const WArgs& a, int wp, unsigned grid, hipStream_t s) {
   switch (wp) {
     case 32: launch_wgrad_rows_t<S, BM, 32>(a, grid, s); break;
     case 16: launch_wgrad_rows_t<S, BM, 16>(a, grid, s); break;
-    default: launch_wgrad_rows_t<S, BM, 8>(a, grid, s); break;
+    case 8: launch_wgrad_rows_t<S, BM, 8>(a, grid, s); break;
+    case 4: launch_wgrad_rows_t<S, BM, 4>(a, grid, s); break;
+    case 2: launch_wgrad_rows_t<S, BM, 2>(a, grid, s); break;
+    default: launch_wgrad_rows_t<S, BM, 1>(a, grid, s); break;
   }
 }
 
@@ -2140,7 +2218,32 @@ WPlan wgrad_plan(const lbm_tensor5* x, const lbm_tensor5* dy, int ksize, int str
   // the general kernel against 12)
   const bool tiny = stride == 2 && gx.c % 32 != 0 && V < 4096;
   const int kpad = lbm_conv_kpad(ksize * ksize * ksize, gx.c);
-  if (!tap_fits(x) || !tap_fits(dy) || V >= (1ll << 31) || (long long)gy.c * kpad >= (1ll << 30) || wide1 || tiny) {
+  const long long gtiles = (long long)((gy.c + BM - 1) / BM) * ((kpad + 63) / 64);
+  if (ksize == 3) {
+    const bool c8 = stride == 1 && gx.c == 8;
+    p.kind = c8 ? WPlan::kC8 : WPlan::kRows;
+    // 32-channel output tiles where 64 would be half empty
+    p.bm = c8 || (gy.c % 64 > 0 && gy.c % 64 <= 32) ? 32 : 64;
+    p.wp = row_voxels(gy, c8 ? 8 : 1);
+    const int rr = c8 || (stride == 1 && p.bm == 32) ? 8 : 4, dp = 32 / p.wp;
+    p.nhb = (gy.h + rr - 1) / rr;
+    p.nwb = (gy.w + p.wp - 1) / p.wp;
+    p.steps = (long long)gy.n * ((gy.d + dp - 1) / dp) * p.nhb * p.nwb;
+    p.nco = (gy.c + p.bm - 1) / p.bm;
+    p.nci = c8 ? 1 : (gx.c + 31) / 32;
+    p.tiles = (c8 ? 1ll : 3ll) * p.nci * p.nco;
+  }
+  // Volumes so narrow that the steps are mostly padding: the general kernel takes
+  // its voxels in any shape, at 2.1 ns per chunk of 32 and tile, against 4.3 ns
+  // per step and tile of 64 channels, 5.4 of 32 (12 on rows of one or two), 8 of
+  // the 8-channel layer (1 x 65536x1x1 24->32 60 us against 80, 8->32 54 against 159;
+  // 1 x 16384x2x2 24->32 61 against 50, 4096x4x4 8->32 about 55 against 32).
+  const double step_ns = p.kind == WPlan::kC8 ? 8.0 : (p.bm == 64 ? 4.3 : (p.wp > 2 ? 5.4 : 12.0));
+  const bool narrow =
+      ksize == 3 && 2.1 * (double)((V + 31) / 32) * (double)gtiles < step_ns * (double)(p.steps * p.tiles);
+  const bool fits = tap_fits(x) && tap_fits(dy) && V < (1ll << 31) && (long long)gy.c * kpad < (1ll << 30);
+  if (!fits || narrow || wide1 || tiny) {
+    p = WPlan{};
     p.kind = WPlan::kGeneral;
     p.nco = (gy.c + BM - 1) / BM;
     p.nci = (kpad + 63) / 64;
@@ -2161,19 +2264,7 @@ WPlan wgrad_plan(const lbm_tensor5* x, const lbm_tensor5* dy, int ksize, int str
     wgrad_splits(p, V, 2, 1024, 512, 1.0, parts);
     return p;
   }
-  const bool c8 = stride == 1 && gx.c == 8;
-  p.kind = c8 ? WPlan::kC8 : WPlan::kRows;
-  // 32-channel output tiles where 64 would be half empty
-  p.bm = c8 || (gy.c % 64 > 0 && gy.c % 64 <= 32) ? 32 : 64;
-  p.wp = row_voxels(gy);
-  const int rr = c8 || (stride == 1 && p.bm == 32) ? 8 : 4, dp = 32 / p.wp;
-  p.nhb = (gy.h + rr - 1) / rr;
-  p.nwb = (gy.w + p.wp - 1) / p.wp;
-  p.steps = (long long)gy.n * ((gy.d + dp - 1) / dp) * p.nhb * p.nwb;
-  p.nco = (gy.c + p.bm - 1) / p.bm;
-  p.nci = c8 ? 1 : (gx.c + 31) / 32;
-  p.tiles = (c8 ? 1ll : 3ll) * p.nci * p.nco;
-  if (c8)
+  if (p.kind == WPlan::kC8)
     wgrad_splits(p, V, 8, 32 * 216, 512, 2.5, parts);
   else
     wgrad_splits(p, V, stride == 2 && p.bm == 32 ? 2 : 4, p.bm * 288, 768, 3.0, parts);
@@ -2260,114 +2351,66 @@ extern "C" {
 
 int32_t lbm_conv_kpad(int32_t taps, int32_t cin) { return ((taps * cin + 31) / 32) * 32; }
 
+// Shapes of a convolution from x to y.
+static bool conv_ok(const lbm_tensor5* x, const lbm_tensor5* y, int32_t ksize, int32_t stride) {
+  if (!tensor_ok(x) || !tensor_ok(y) || (ksize != 1 && ksize != 3) || (stride != 1 && stride != 2) ||
+      (ksize == 1 && stride != 1))
+    return false;
+  return y->n == x->n && y->d == outdim(x->d, stride) && y->h == outdim(x->h, stride) && y->w == outdim(x->w, stride);
+}
+
 lbm_status lbm_conv3d_fwd(const lbm_tensor5* x, const uint16_t* w, const float* bias, const lbm_tensor5* y,
                           int32_t ksize, int32_t stride, int32_t relu, void* stream) {
-  if (!tensor_ok(x) || !tensor_ok(y) || !w || (ksize != 1 && ksize != 3) || (stride != 1 && stride != 2) ||
-      (ksize == 1 && stride != 1))
-    return LBM_EINVAL;
-  if (y->n != x->n || y->d != outdim(x->d, stride) || y->h != outdim(x->h, stride) || y->w != outdim(x->w, stride))
-    return LBM_EINVAL;
-  const int taps = ksize * ksize * ksize;
-  const int kpad = lbm_conv_kpad(taps, x->c);
-  const long long M = (long long)y->n * y->d * y->h * y->w;
-  hipStream_t s = (hipStream_t)stream;
-  const Geo gs = geo_of(x), go = geo_of(y);
-  const dim3 b(256);
-  const bool rows = ksize == 3 && stride == 1, point = point_fits(ksize, x, y);
-  if ((x->c % 32 == 0 || rows || point) && tap_fits(x) && tap_fits(y) && (long long)y->c * kpad < (1ll << 30)) {
-    const DArgs a{(const uint16_t*)x->ptr, gs, (unsigned)view_bytes(x), w, kpad,
-                  (unsigned)((long long)y->c * kpad * 2), bias, (uint16_t*)y->ptr, go, nullptr, 0, ksize, stride,
-                  relu, 0, x->c};
-    if (point)
-      launch_point(a, s);
-    else if (!rows || !launch_rows<0>(a, s))
-      launch_tap_cols<0, false>(a, M, 1, s);
-  } else if (y->c <= 16) {
-    dim3 g((unsigned)((M + BM - 1) / BM), (y->c + 15) / 16);
-    hipLaunchKernelGGL((k_conv_gemm<0, 16>), g, b, 0, s, (const uint16_t*)x->ptr, gs, w, kpad, bias,
-                       (uint16_t*)y->ptr, go, (const uint16_t*)nullptr, 0, ksize, stride, relu, 0, x->c);
-  } else if (y->c <= 32) {
-    dim3 g((unsigned)((M + BM - 1) / BM), 1);
-    hipLaunchKernelGGL((k_conv_gemm<0, 32>), g, b, 0, s, (const uint16_t*)x->ptr, gs, w, kpad, bias,
-                       (uint16_t*)y->ptr, go, (const uint16_t*)nullptr, 0, ksize, stride, relu, 0, x->c);
-  } else {
-    dim3 g((unsigned)((M + BM - 1) / BM), (y->c + 63) / 64);
-    hipLaunchKernelGGL((k_conv_gemm<0, 64>), g, b, 0, s, (const uint16_t*)x->ptr, gs, w, kpad, bias,
-                       (uint16_t*)y->ptr, go, (const uint16_t*)nullptr, 0, ksize, stride, relu, 0, x->c);
-  }
+  if (!conv_ok(x, y, ksize, stride) || !w) return LBM_EINVAL;
+  const int kpad = lbm_conv_kpad(ksize * ksize * ksize, x->c);
+  const DArgs a{(const uint16_t*)x->ptr, geo_of(x), (unsigned)view_bytes(x), w, kpad,
+                (unsigned)((long long)y->c * kpad * 2), bias, (uint16_t*)y->ptr, geo_of(y), nullptr, 0, ksize, stride,
+                relu, 0, x->c};
+  launch_conv<0>(a, pick_conv<0>(a.gs, a.go, ksize, stride, conv_fits(x, y, kpad)), (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
 lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const lbm_tensor5* dx,
                                const lbm_tensor5* act, int32_t ksize, int32_t stride, int32_t accumulate,
                                void* stream) {
-  if (!tensor_ok(dy) || !tensor_ok(dx) || !w_t || (ksize != 1 && ksize != 3) || (stride != 1 && stride != 2) ||
-      (ksize == 1 && stride != 1))
-    return LBM_EINVAL;
-  if (dy->n != dx->n || dy->d != outdim(dx->d, stride) || dy->h != outdim(dx->h, stride) ||
-      dy->w != outdim(dx->w, stride))
-    return LBM_EINVAL;
+  if (!conv_ok(dx, dy, ksize, stride) || !w_t) return LBM_EINVAL;
   if (act && (!tensor_ok(act) || act->n != dx->n || act->d != dx->d || act->h != dx->h || act->w != dx->w ||
               act->c < dx->c))
     return LBM_EINVAL;
-  const int taps = ksize * ksize * ksize;
-  const int kpad = lbm_conv_kpad(taps, dy->c);
-  const long long M = (long long)dx->n * dx->d * dx->h * dx->w;
-  hipStream_t s = (hipStream_t)stream;
-  const Geo gs = geo_of(dy), go = geo_of(dx);
-  const uint16_t* ap = act ? (const uint16_t*)act->ptr : nullptr;
-  const int aldc = act ? act->ldc : 0;
-  const dim3 b(256);
-  const bool rows = ksize == 3 && stride == 1, point = point_fits(ksize, dy, dx);
-  if ((dy->c % 32 == 0 || rows || point) && tap_fits(dy) && tap_fits(dx) && (long long)dx->c * kpad < (1ll << 30)) {
-    const DArgs a{(const uint16_t*)dy->ptr, gs, (unsigned)view_bytes(dy), w_t, kpad,
-                  (unsigned)((long long)dx->c * kpad * 2), nullptr, (uint16_t*)dx->ptr, go, ap, aldc, ksize, stride,
-                  0, accumulate, dy->c};
-    if (point) {
-      launch_point(a, s);
-    } else if (stride == 2) {
-      if (!launch_up(a, s)) {
-        // rows of the largest parity class; smaller classes mask their tail
-        const long long rows = (long long)dx->n * ((dx->d + 1) / 2) * ((dx->h + 1) / 2) * ((dx->w + 1) / 2);
-        launch_tap_cols<1, true>(a, rows, 8, s);
-      }
-    } else if (!rows || !launch_rows<1>(a, s)) {
-      launch_tap_cols<1, false>(a, M, 1, s);
-    }
-  } else if (dx->c <= 16) {
-    dim3 g((unsigned)((M + BM - 1) / BM), (dx->c + 15) / 16);
-    hipLaunchKernelGGL((k_conv_gemm<1, 16>), g, b, 0, s, (const uint16_t*)dy->ptr, gs, w_t, kpad,
-                       (const float*)nullptr, (uint16_t*)dx->ptr, go, ap, aldc, ksize, stride, 0, accumulate, dy->c);
-  } else if (dx->c <= 32) {
-    dim3 g((unsigned)((M + BM - 1) / BM), 1);
-    hipLaunchKernelGGL((k_conv_gemm<1, 32>), g, b, 0, s, (const uint16_t*)dy->ptr, gs, w_t, kpad,
-                       (const float*)nullptr, (uint16_t*)dx->ptr, go, ap, aldc, ksize, stride, 0, accumulate, dy->c);
-  } else {
-    dim3 g((unsigned)((M + BM - 1) / BM), (dx->c + 63) / 64);
-    hipLaunchKernelGGL((k_conv_gemm<1, 64>), g, b, 0, s, (const uint16_t*)dy->ptr, gs, w_t, kpad,
-                       (const float*)nullptr, (uint16_t*)dx->ptr, go, ap, aldc, ksize, stride, 0, accumulate, dy->c);
-  }
+  const int kpad = lbm_conv_kpad(ksize * ksize * ksize, dy->c);
+  const DArgs a{(const uint16_t*)dy->ptr, geo_of(dy), (unsigned)view_bytes(dy), w_t, kpad,
+                (unsigned)((long long)dx->c * kpad * 2), nullptr, (uint16_t*)dx->ptr, geo_of(dx),
+                act ? (const uint16_t*)act->ptr : nullptr, act ? act->ldc : 0, ksize, stride, 0, accumulate, dy->c};
+  launch_conv<1>(a, pick_conv<1>(a.gs, a.go, ksize, stride, conv_fits(dy, dx, kpad)), (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
-static bool wgrad_ok(const lbm_tensor5* x, const lbm_tensor5* dy, int32_t ksize, int32_t stride) {
-  if (!tensor_ok(x) || !tensor_ok(dy) || (ksize != 1 && ksize != 3) || (stride != 1 && stride != 2) ||
-      (ksize == 1 && stride != 1))
-    return false;
-  return dy->n == x->n && dy->d == outdim(x->d, stride) && dy->h == outdim(x->h, stride) &&
-         dy->w == outdim(x->w, stride);
+int32_t lbm_conv3d_kernel(int32_t pass, const lbm_tensor5* x, const lbm_tensor5* y, int32_t ksize, int32_t stride) {
+  if (!conv_ok(x, y, ksize, stride) || pass < 0 || pass > 2) return -1;
+  const int taps = ksize * ksize * ksize;
+  if (pass == 0)
+    return pick_conv<0>(geo_of(x), geo_of(y), ksize, stride, conv_fits(x, y, lbm_conv_kpad(taps, x->c)));
+  if (pass == 1)
+    return pick_conv<1>(geo_of(y), geo_of(x), ksize, stride, conv_fits(y, x, lbm_conv_kpad(taps, y->c)));
+  const WPlan p = wgrad_plan(x, y, ksize, stride, true);
+  switch (p.kind) {
+    case WPlan::kRows: return p.bm == 32 ? LBM_WGRAD_ROWS32 : LBM_WGRAD_ROWS64;
+    case WPlan::kC8: return LBM_WGRAD_C8;
+    case WPlan::kPoint: return LBM_WGRAD_POINT;
+    default: return LBM_WGRAD_GENERAL;
+  }
 }
 
 lbm_status lbm_conv3d_bwd_weight(const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* dbias,
                                  int32_t ksize, int32_t stride, void* stream) {
-  if (!wgrad_ok(x, dy, ksize, stride) || !dw || (dbias && dy->c > 2048)) return LBM_EINVAL;
+  if (!conv_ok(x, dy, ksize, stride) || !dw || (dbias && dy->c > 2048)) return LBM_EINVAL;
   launch_wgrad(wgrad_plan(x, dy, ksize, stride, false), x, dy, dw, dbias, ksize, stride, nullptr,
                (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
 int64_t lbm_conv3d_bwd_weight_scratch(const lbm_tensor5* x, const lbm_tensor5* dy, int32_t ksize, int32_t stride) {
-  if (!wgrad_ok(x, dy, ksize, stride)) return -1;
+  if (!conv_ok(x, dy, ksize, stride)) return -1;
   return 4 * wgrad_floats(wgrad_plan(x, dy, ksize, stride, true), geo_of(dy),
                           lbm_conv_kpad(ksize * ksize * ksize, x->c));
 }
@@ -2375,7 +2418,7 @@ int64_t lbm_conv3d_bwd_weight_scratch(const lbm_tensor5* x, const lbm_tensor5* d
 lbm_status lbm_conv3d_bwd_weight_ordered(const lbm_tensor5* x, const lbm_tensor5* dy, float* dw, float* dbias,
                                          int32_t ksize, int32_t stride, void* scratch, int64_t scratch_bytes,
                                          void* stream) {
-  if (!wgrad_ok(x, dy, ksize, stride) || !dw || (dbias && dy->c > 2048)) return LBM_EINVAL;
+  if (!conv_ok(x, dy, ksize, stride) || !dw || (dbias && dy->c > 2048)) return LBM_EINVAL;
   const WPlan p = wgrad_plan(x, dy, ksize, stride, true);
   const int64_t need = 4 * wgrad_floats(p, geo_of(dy), lbm_conv_kpad(ksize * ksize * ksize, x->c));
   if (need > 0 && (!scratch || scratch_bytes < need || ((uintptr_t)scratch & 15))) return LBM_EINVAL;

@@ -32,7 +32,8 @@ class lbm_tensor5(ctypes.Structure):
 
 
 SYMBOLS = ["lbm_conv_kpad", "lbm_conv3d_fwd", "lbm_conv3d_bwd_data", "lbm_conv3d_bwd_weight",
-           "lbm_conv3d_bwd_weight_scratch", "lbm_conv3d_bwd_weight_ordered", "lbm_conv3d_weight_t", "lbm_upsample2", "lbm_upsample2_bwd", "lbm_mse_loss", "lbm_adam_step",
+           "lbm_conv3d_bwd_weight_scratch", "lbm_conv3d_bwd_weight_ordered", "lbm_conv3d_kernel",
+           "lbm_conv3d_weight_t", "lbm_upsample2", "lbm_upsample2_bwd", "lbm_mse_loss", "lbm_adam_step",
            "lbm_surrogate_input", "lbm_surrogate_target", "lbm_surrogate_fields"]
 
 
@@ -50,6 +51,7 @@ def lib():
             "lbm_conv3d_bwd_data": [T, P, T, T, i32, i32, i32, P],
             "lbm_conv3d_bwd_weight": [T, T, P, P, i32, i32, P],
             "lbm_conv3d_bwd_weight_ordered": [T, T, P, P, i32, i32, P, ctypes.c_int64, P],
+            "lbm_conv3d_kernel": [i32, T, T, i32, i32],
             "lbm_conv3d_weight_t": [P, i32, i32, i32, P, P, P],
             "lbm_upsample2": [T, T, P],
             "lbm_upsample2_bwd": [T, T, i32, P],
@@ -156,6 +158,19 @@ class Scratch:
                     self._bufs.pop(next(iter(self._bufs)))
                 buf = self._bufs[key] = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         return buf
+
+
+# kernels that lbm_conv3d_kernel names
+KERNELS = {0: "general", 1: "tap", 2: "point", 3: "c8", 4: "rows2", 5: "rows4", 6: "plane small", 7: "plane mid",
+           8: "plane big", 9: "up", 16: "wgrad general", 17: "wgrad point", 18: "wgrad c8", 19: "wgrad rows32",
+           20: "wgrad rows64"}
+PASSES = ("forward", "input gradient", "weight gradient")
+
+
+def kernel_of(which, x, y, ksize=3, stride=1):
+    """The kernel that a pass of a layer from x to y (Act, or lbm_tensor5) runs: chosen by shape alone."""
+    t = [ctypes.byref(getattr(a, "t5", a)) for a in (x, y)]
+    return KERNELS[lib().lbm_conv3d_kernel(PASSES.index(which), *t, ksize, stride)]
 
 
 class Conv:
