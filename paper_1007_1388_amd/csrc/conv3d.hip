@@ -548,6 +548,14 @@ __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rs, uint16_t* d
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, (int)voff, (int)soff, 0, 0);
 }
 
+// A barrier that every wave's LDS-direct loads end before: vmcnt(0), said
+// outright, as the barrier alone orders LDS accesses and not these loads (the
+// other counters at their no-wait values).
+__device__ __forceinline__ void load_barrier() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __syncthreads();
+}
+
 // The stride-1 3x3x3 products.  A workgroup owns a TH x 16 tile of output
 // voxels (rows h0.., columns w0.. of one plane) and 32 output channels; per
 // source plane and 32-channel chunk it brings the input halo (TH + 2) x 18 x 32
@@ -666,7 +674,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
         if (i * 4 + wave < NWI)
           lds_dma16(rw, Ws + (i * 4 + wave) * 512, !TAIL || c0 + wq * 8 < C ? woff : OOB,
                     (unsigned)((kd * 9 + i * TPI) * C + c0) * 2u);
-      __syncthreads();  // (waits for the loads)
+      load_barrier();
       bf16x8 wf[9][FN];
 #pragma unroll
       for (int t = 0; t < 9; ++t)
@@ -806,7 +814,7 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
 #pragma unroll
         for (int k = 0; k < NC; ++k) lds_dma16(rs, Xs[k] + (i * NWV + wave) * 512, vo, (unsigned)k * 64u);
       }
-    __syncthreads();  // (waits for the loads)
+    load_barrier();
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
       if (t < 8) load_w(kd * 9 + t + 1, (t + 1) & 1);  // in flight while this tap runs
@@ -823,7 +831,7 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
           for (int j = 0; j < FN; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf, acc[r][j], 0, 0, 0);
         }
       }
-      __syncthreads();  // this tap's weights are read, the next one's have arrived
+      load_barrier();  // this tap's weights are read, the next one's have arrived
     }
   }
   const int w = w0 + vc, d = d0 + vp, col = n0 + nc0 + g * 8;
@@ -916,7 +924,7 @@ __global__ void __launch_bounds__(256) k_conv_up(DArgs a) {
 #pragma unroll
   for (int o = 0; o < 2; ++o) xb[o] = (wave * R * HC + L + o) * 32 + ((g ^ (((L + o) >> 1) & 3)) * 8);
   const int wb = ((L >> 2) * 8 + (L & 3)) * 32 + ((g ^ (L >> 2)) * 8);
-  __syncthreads();  // (waits for the loads)
+  load_barrier();
 
   const int col = n0 + g * 8, w = 2 * (w0 + L);
   f32x4 acc[R][2][2];  // [row][parity along w][column fragment]
@@ -961,7 +969,7 @@ __global__ void __launch_bounds__(256) k_conv_up(DArgs a) {
             store8(a, (((long long)n * go.d + d) * go.h + h) * go.w + w + o, col, acc[r][o][0], acc[r][o][1]);
       }
     }
-    __syncthreads();  // this stage's weights are read, the next one's have arrived
+    load_barrier();  // this stage's weights are read, the next one's have arrived
   }
 }
 
@@ -1070,7 +1078,7 @@ __global__ void __launch_bounds__(256) k_conv_fwd_c8(DArgs a) {
     xo[s] = ((t / 9 * HR + t / 3 % 3) * HC + t % 3 + L) * 8;
   }
   const bool none = g == 3;  // tap 27 of the last step
-  __syncthreads();  // (waits for the loads)
+  load_barrier();
   const int w = w0 + L, col = n0 + g * 8;
   for (int p = 0; p < kPl; ++p) {
     if (d0 + p >= go.d) break;
@@ -1303,7 +1311,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2
     const int c3 = hb == a.nhb;
     hb = c3 ? 0 : hb;
     nn += c3;
-    __syncthreads();  // (waits for the loads)
+    load_barrier();
     bf16x8 af[RW][2];
     // an x row serves every tap row kh whose dy row it meets
 #pragma unroll
@@ -1493,7 +1501,7 @@ __global__ void __launch_bounds__(256) k_conv_wgrad_c8(WArgs a) {
     const int c3 = hb == a.nhb;
     hb = c3 ? 0 : hb;
     nn += c3;
-    __syncthreads();  // (waits for the loads)
+    load_barrier();
 #pragma unroll
     for (int r = 0; r < RR; ++r) {
       bf16x8 af[2];
@@ -1580,7 +1588,7 @@ __global__ void __launch_bounds__(512) k_conv_wgrad_point(WArgs a) {
       lds_dma16(rd, As + slot * 512, aok && v < V ? (unsigned)(v * gy.ldc + co0 + q) * 2u : OOB, 0);
       lds_dma16(rx, Xs + slot * 512, xok && v < V ? (unsigned)(v * gx.ldc + ci0 + q) * 2u : OOB, 0);
     }
-    __syncthreads();  // (waits for the loads)
+    load_barrier();
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       bf16x8 af[2], bx[2];
