@@ -417,11 +417,12 @@ void build_items(lbm_ctx* c) {
 
 lbm_status upload_list(lbm_ctx* c, const std::vector<ItemDev>& h, ItemDev** d, size_t* cap) {
   const size_t need = std::max<size_t>(1, h.size()) * sizeof(ItemDev);
-  if (need > *cap) {
+  if (need > *cap) {  // (a failed allocation leaves the old list)
+    ItemDev* const larger = (ItemDev*)dalloc(c, need);
+    if (!larger) return fail(LBM_ENOMEM, "item list allocation failed");
     if (*d) dfree(c, *d);
-    *d = (ItemDev*)dalloc(c, need);
-    *cap = *d ? need : 0;
-    if (!*d) return fail(LBM_ENOMEM, "item list allocation failed");
+    *d = larger;
+    *cap = need;
   }
   if (!h.empty()) HIPCHK(hipMemcpy(*d, h.data(), h.size() * sizeof(ItemDev), hipMemcpyHostToDevice));
   return LBM_OK;
@@ -1438,19 +1439,25 @@ lbm_status lbm_set_geometry(lbm_ctx* c, const uint8_t* solid) {
     lbm_status s = ensure_stage(c, (size_t)c->n_cells);
     if (s != LBM_OK) return s;
     HIPCHK(hipMemcpyAsync(c->d_stage, solid, (size_t)c->n_cells, hipMemcpyHostToDevice, c->stream));
-    c->has_mask = true;
-    CellArgs a = cell_args(c);
-    a.has_mask = 0;
-    launch_linkmask((const uint8_t*)c->d_stage, a, c->d_mask, c->stream);
-    HIPCHK(hipGetLastError());
-  } else {
-    c->has_mask = false;
   }
+  c->has_mask = any;
   if (c->has_mask != had_mask) {  // the items' size depends on obstacles
     HIPCHK(hipStreamSynchronize(c->stream));
     build_items(c);
     lbm_status si = upload_items(c);
-    if (si != LBM_OK) return si;
+    if (si != LBM_OK) {  // the lattice stays as it was
+      const std::string why = g_last_error;
+      c->has_mask = had_mask;
+      build_items(c);
+      (void)upload_items(c);
+      return fail(si, why);
+    }
+  }
+  if (any) {
+    CellArgs a = cell_args(c);
+    a.has_mask = 0;
+    launch_linkmask((const uint8_t*)c->d_stage, a, c->d_mask, c->stream);
+    HIPCHK(hipGetLastError());
   }
   c->n_fluid = c->n_cells - nsolid;
   lbm_status s = zero_grids(c);
