@@ -119,9 +119,13 @@ typedef struct {
                               1 = the sweep writes every ghost value into the neighbours'
                               ghost layers itself; 2 = the sweep writes the x-face ghost
                               planes for rows off the y/z faces, the copy kernel the rest */
-  int32_t item_cells;      /* target cells per work item (whole x-rows), >= 1; sweeps bound by
-                              memory take half of it, 16-bit storage on large grids
-                              without obstacles twice (neither with fused_exchange = 1) */
+  int32_t item_cells;      /* target cells per work item (whole x-rows), >= 1.  512 (the
+                              default) leaves the size to the sweep: FP64 and FP32 sweeps
+                              bound by memory, or on small grids, take about 256, 16-bit
+                              storage on large grids without obstacles up to 1024, the rest
+                              512 (and all with fused_exchange = 1 or persistent > 0);
+                              any other value is taken as it is.  lbm_info.n_items says
+                              what came of it */
   int32_t wg_size;         /* threads per workgroup: 64, 128 or 256 */
   int32_t persistent;      /* 0: one workgroup per item; k > 0: k workgroups per
                               compute unit loop over the item list */

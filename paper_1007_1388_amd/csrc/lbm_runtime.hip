@@ -316,87 +316,92 @@ void order_items_by_xcd(lbm_ctx* c) {
       if (k < q[x].size()) c->items_h.push_back(q[x][k]);
 }
 
-// Cells per work item of this sweep: the schedule's item_cells, whose default
-// 512 gives each wave of a 4-wave workgroup two 64-cell tasks, halved or
-// doubled by what bounds the sweep (measured on gfx950, default schedule, us
-// per step; results do not depend on it).
+// Cells per work item: the schedule's item_cells as it stands, except for its
+// default 512, which leaves the choice to the sweep.  512 gives each wave of a
+// 4-wave workgroup two 64-cell tasks; it is halved or doubled by what bounds
+// the sweep (measured on gfx950, us per step; results do not depend on it).
 //  * FP64, and FP32 without obstacles that does not write its Blocks' x faces
 //    itself: half, one task per wave.  These are bound by memory, and a
 //    second task's loads wait behind the first one's stores: 256^3 channel
-//    FP32 474 -> 454, FP64 951 -> 942, 200^3 FP32 250 -> 238, 128^3 FP64
-//    124 -> 117, one-Block open duct 100 -> 95; 2-8 % over 60 channels 64, 128
-//    and 256 wide but two (256x150x150 and 256x192x192 FP32, 4-5 % slower).
+//    FP32 474 -> 454, FP64 951 -> 942, 200^3 FP32 249 -> 239, 128^3 FP64
+//    123 -> 117, one-Block open duct 100 -> 95.  Over 68 one-Block channels 56
+//    to 257 cells wide 4 % less time on average.  Some sizes lose, next to sizes
+//    that gain as much (256x150x150 FP32 172 -> 179, 256x148x150 164 -> 155;
+//    256x192x192 272 -> 282, 256x192x200 279 -> 262; FP64 220x140x140 254 -> 267,
+//    220x132x140 239 -> 236): the sweep then runs at 4.9 to 5.2 TB/s whatever the
+//    items, so what they meet is where the arrays lie, for which there is no
+//    rule here.  lbm_autotune finds the larger items for them.
 //    Not where that leaves a wave without a task (rows of 129-192 cells, three
 //    tasks: FP32 3-8 % slower, build_items).  With obstacles, or sending x
 //    faces, FP32 keeps two tasks (128^3 porous 65.7 against 66.8, porous
 //    512x256x256 in 250 Blocks 1102 against 1146: more of a task is set-up).
-//  * Fewer than three items per compute unit: half, whatever the variant, to
-//    occupy the chip: 32^3 FP64 cavity 12.8 -> 8.7, 64^3 FP32 in 8 Blocks
-//    22.9 -> 21.3 (64x64x128 porous, four per unit, 18.7 against 19.1).
+//  * FP64 and FP32 with fewer than three items per compute unit: half, whatever
+//    the variant, to occupy the chip: 32^3 FP64 cavity 12.8 -> 8.7, 64^3 FP32 in
+//    8 Blocks 22.9 -> 21.3 (64x64x128 porous, four per unit, 18.7 against 19.1).
 //  * 16-bit storage without obstacles, with at least eight items per compute
-//    unit left: double,
-//    four tasks per wave.  The dispatcher starts about 240 workgroups per us,
-//    which half-size values outrun: 256^3 cavity FP16S 273 -> 263, 128^3 38.7
-//    -> 36.9, 256^3 in 8 Blocks 358 -> 318 (64^3, one per unit, 19.4
-//    against 23.8; 321x137x38 in 8 Blocks, six per unit, 54.9 against 57.8).  With
-//    obstacles whole items: 53x95x391 in 8 Blocks 101 against 135 doubled, 24x211x357
-//    85 against 93, 138x212x144 in 12 Blocks 153 against 161.
-//  * The fully fused exchange keeps the target: a wave spends more on looking
-//    up its rows' ghost targets, once per item (384^3 FP32 in 64 Blocks 1806
-//    against 1982 halved, in 216 Blocks 1742 against 1841, FP64 in 27 Blocks
-//    3421 against 3724; the other way by up to 4 % on 128^3 FP64).
-bool few_items(const lbm_ctx* c) {
-  return c->n_cells / std::max(1, c->sched.item_cells) < 3 * c->cu_count;
-}
+//    unit left: double.  The
+//    dispatcher starts about 240 workgroups per us, which half-size values
+//    outrun: 256^3 cavity FP16S 273 -> 263, 128^3 46.6 -> 44.8, 256^3 in 8 Blocks
+//    323 -> 304 (64^3, one per unit, 19.4 against 23.8; 321x137x38 in 8 Blocks, six
+//    per unit, 54.9 against 57.8).  With obstacles whole items: 53x95x391 in 8
+//    Blocks 101 against 135 doubled, 24x211x357 85 against 93, 138x212x144 in 12
+//    Blocks 153 against 161.
+//  * The fully fused exchange keeps 512: a wave spends more on looking up its
+//    rows' ghost targets, once per item (384^3 FP32 in 64 Blocks 1806 against 1982
+//    halved, in 216 Blocks 1742 against 1841, FP64 in 27 Blocks 3421 against 3724;
+//    the other way by up to 4 % on 128^3 FP64).  So do workgroups that loop over
+//    the items (persistent).
+constexpr int kItemCells = 512;  // the default, and the choice by the sweep
+
+bool few_items(const lbm_ctx* c) { return c->n_cells / kItemCells < 3 * c->cu_count; }
+
 int item_target(const lbm_ctx* c) {
-  const int t = std::max(1, c->sched.item_cells);
-  if (c->sched.persistent > 0) return t;  // workgroups loop over the items anyway
-  if (c->sched.fused_exchange == 1) return t;
+  const int t = c->sched.item_cells;
+  if (t != kItemCells || c->sched.persistent > 0 || c->sched.fused_exchange == 1) return t;
   if (c->prec >= 2) return !c->has_mask && c->n_cells / t >= 16 * c->cu_count ? 2 * t : t;
   const bool streams = c->prec == 0 || (!c->has_mask && c->sched.fused_exchange != 2);
-  return streams || few_items(c) ? std::max(1, t / 2) : t;
+  return streams || few_items(c) ? t / 2 : t;
 }
 
 void build_items(lbm_ctx* c) {
   c->items_h.clear();
-  const int target = item_target(c), whole = std::max(1, c->sched.item_cells);
+  const int target = item_target(c), whole = c->sched.item_cells;
   const bool halved = target < whole && !few_items(c);
   const int vec = cells_per_lane(c, c->sched), nw = std::max(1, c->sched.wg_size / 64);
   for (int j = 0; j < (int)c->bh.size(); ++j) {
     const BlockDev& B = c->bh[j];
     const int a = B.dim[0], b = B.dim[1], cz = B.dim[2];
-    int rows = std::max(1, std::min(b, target / a));
-    if (B.pack) rows = std::max(2, rows & ~1);  // pairs of packed rows share a line
     const bool flat = flat_rows(B, vec, (int)c->sbytes);
-    if (flat) {
-      // flat runs: whole waves per item where a few rows make a multiple of
-      // 64 cells (48-cell rows: 4; packed rows' multiple is even)
-      int m = 64;
-      while (m > 1 && (a * (m / 2)) % 64 == 0) m /= 2;
-      if (m <= b && m * a <= 2 * target) rows = std::max(m, rows / m * m);
-    }
     // The sweep's waves take an item's (row group, 64-lane segment) tasks in
-    // turn.  With 16-bit storage, round rows up so that their count is a
-    // multiple of the waves per workgroup (a 384-cell row is 6 segments: one
-    // row per item leaves half of a 4-wave workgroup idle in its second
-    // round).  Measured on gfx950 (same box, 320^3 and 384^3 cavities):
-    // +12-15 % for F16S, but -3-4 % for FP32 and FP64, whose sweeps gain
-    // more from the larger number of smaller items.
+    // turn.
     const int lanes = (a + vec - 1) / vec;
     int xw = 64;
     while (xw > 1 && xw / 2 >= lanes) xw >>= 1;
     const int rpw = 64 / xw, nseg = (lanes + 63) / 64;
     auto tasks = [&](int r) { return flat ? ((long long)r * a + 63) / 64 : (long long)((r + rpw - 1) / rpw) * nseg; };
-    if (halved && !flat && tasks(rows) % nw != 0) {
-      rows = std::max(1, std::min(b, whole / a));
-      if (B.pack) rows = std::max(2, rows & ~1);
-    }
-    for (int r = rows; r <= b && c->prec >= 2; ++r) {
-      if (tasks(r) % nw == 0 || r == b) {
-        rows = r;
-        break;
+    // rows of an item of about t cells
+    auto rows_of = [&](int t) {
+      int r = std::max(1, std::min(b, t / a));
+      if (B.pack) r = std::max(2, r & ~1);  // pairs of packed rows share a line
+      if (flat) {
+        // flat runs: whole waves per item where a few rows make a multiple of
+        // 64 cells (48-cell rows: 4; packed rows' multiple is even)
+        int m = 64;
+        while (m > 1 && (a * (m / 2)) % 64 == 0) m /= 2;
+        if (m <= b && m * a <= 2 * t) r = std::max(m, r / m * m);
       }
-    }
+      // With 16-bit storage, round rows up so that their count is a
+      // multiple of the waves per workgroup (a 384-cell row is 6 segments: one
+      // row per item leaves half of a 4-wave workgroup idle in its second
+      // round).  Measured on gfx950 (same box, 320^3 and 384^3 cavities):
+      // +12-15 % for F16S, but -3-4 % for FP32 and FP64, whose sweeps gain
+      // more from the larger number of smaller items.
+      for (int q = r; q <= b && c->prec >= 2; ++q)
+        if (tasks(q) % nw == 0 || q == b) return q;
+      return r;
+    };
+    int rows = rows_of(target);
+    if (halved && !flat && tasks(rows) % nw != 0) rows = rows_of(whole);
     // (flat runs in a Block that wraps along y: rows 0 and b - 1 alone, and
     // row 1 too with packed rows, so that the flat items start on even rows)
     const bool wy = flat && (B.wrap & 2) && b > 3;
@@ -1329,7 +1334,7 @@ lbm_status lbm_create_blocks(const lbm_params* p, const lbm_aabb* blocks, int32_
   // whose rim leaves the copy kernel contiguous rows.  The fully fused
   // epilogue (mode 1) holds the sweep to fewer resident waves.
   c->sched.fused_exchange = nblocks > 1 ? 2 : 0;
-  c->sched.item_cells = 512;
+  c->sched.item_cells = kItemCells;
   c->sched.wg_size = 256;
   c->sched.persistent = 0;
   c->sched.graph_steps = 0;
@@ -1900,7 +1905,8 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* cache_path, int32_t trial_steps,
   std::ostringstream key;
   hipDeviceProp_t prop;
   HIPCHK(hipGetDeviceProperties(&prop, c->device));
-  key << prop.gcnArchName << "|p" << c->prec << "m" << c->f64math << "o" << c->has_mask << "|" << c->p.dims[0]
+  // (i2: what item_cells means, so that lines tuned under another meaning are skipped)
+  key << prop.gcnArchName << "|i2|p" << c->prec << "m" << c->f64math << "o" << c->has_mask << "|" << c->p.dims[0]
       << "x" << c->p.dims[1] << "x" << c->p.dims[2] << "|nb" << c->bh.size() << "|f";
   // face kinds (open faces restrict the sweep variants) and row padding
   for (int f = 0; f < 6; ++f) key << (int)c->p.face[f];
@@ -1969,7 +1975,8 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* cache_path, int32_t trial_steps,
   double best_ms = 1e30;
   lbm_status st = timeit(best, &best_ms);
   // coordinate descent over the schedule knobs
-  const std::vector<int> cells = {128, 256, 512, 1024, 2048, 4096};
+  // (512: the sweep's choice; 520: two tasks per wave in any case)
+  const std::vector<int> cells = {128, 256, 512, 520, 1024, 2048, 4096};
   const std::vector<int> wgs = {64, 128, 256};
   const std::vector<int> pers = {0, 2, 4, 8, 16};
   for (int pass = 0; pass < 2 && st == LBM_OK; ++pass) {
