@@ -339,11 +339,15 @@ void order_items_by_xcd(lbm_ctx* c) {
 //    the variant, to occupy the chip: 32^3 FP64 cavity 12.8 -> 8.7, 64^3 FP32 in
 //    8 Blocks 22.9 -> 21.3 (64x64x128 porous, four per unit, 18.7 against 19.1).
 //  * 16-bit storage without obstacles, with at least eight items per compute
-//    unit left: double.  The
+//    unit left, where a row fills its own waves and rounding up to whole rounds
+//    of them has not enlarged the items anyway (build_items): double.  The
 //    dispatcher starts about 240 workgroups per us, which half-size values
 //    outrun: 256^3 cavity FP16S 273 -> 263, 128^3 46.6 -> 44.8, 256^3 in 8 Blocks
 //    323 -> 304 (64^3, one per unit, 19.4 against 23.8; 321x137x38 in 8 Blocks, six
-//    per unit, 54.9 against 57.8).  With obstacles whole items: 53x95x391 in 8
+//    per unit, 54.9 against 57.8; 160 cells wide, 640-cell items already, 2 to 5 %
+//    slower doubled; Blocks 32 wide, two rows a wave, 118 against 126).  Over 20
+//    widths from 48 to 384 then 6 % less time where it applies, 80 cells wide and
+//    Blocks 75 wide 1 and 3 % more.  With obstacles whole items: 53x95x391 in 8
 //    Blocks 101 against 135 doubled, 24x211x357 85 against 93, 138x212x144 in 12
 //    Blocks 153 against 161.
 //  * The fully fused exchange keeps 512: a wave spends more on looking up its
@@ -402,6 +406,7 @@ void build_items(lbm_ctx* c) {
     };
     int rows = rows_of(target);
     if (halved && !flat && tasks(rows) % nw != 0) rows = rows_of(whole);
+    if (target > whole && (rpw > 1 || rows_of(whole) * a > whole)) rows = rows_of(whole);
     // (flat runs in a Block that wraps along y: rows 0 and b - 1 alone, and
     // row 1 too with packed rows, so that the flat items start on even rows)
     const bool wy = flat && (B.wrap & 2) && b > 3;

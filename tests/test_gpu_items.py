@@ -83,7 +83,7 @@ def test_explicit_item_cells_are_taken_as_they_are():
     ("f64", (64, 32, 32), 4, 8),                                     # half: few items
     ("f64", (192, 40, 64), 2, 2),                                    # three tasks a row: whole
     ("f16s", (128, 128, 128), 8, 4), ("bf16s", (256, 96, 96), 4, 2),  # double
-    ("f16s", (128, 64, 64), 4, 4),                                   # few items
+    ("f16s", (160, 128, 110), 4, 4), ("f16s", (128, 64, 64), 4, 4),  # 640-cell items already; few items
 ])
 def test_the_sweeps_choice_of_items(prec, dims, chosen, whole):
     """item_cells = 512 against the same lattice with whole items (520 cells): fewer or more items, the same bits."""
