@@ -16,7 +16,10 @@
  * stride 1).  Weights of a layer with Cin inputs, Cout outputs and T taps
  * (27 or 1) are stored "K-major": w[co][t*Cin + ci], with K = T*Cin rounded up
  * to a multiple of 32 (the padding is zero).  All arithmetic accumulates in
- * FP32.  Every call enqueues on `stream` (hipStream_t, NULL = null stream),
+ * FP32.  Operands are finite: tiles past a volume's end multiply real values by
+ * zeros, so an infinity or NaN in x may also reach weight gradients of taps that
+ * do not read it.  A 1x1x1 layer of at most 64 channels may run in place.
+ * Every call enqueues on `stream` (hipStream_t, NULL = null stream),
  * allocates nothing and returns lbm_status (LBM_EINVAL on bad shapes).
  */
 #ifndef LBM_SURROGATE_H_

@@ -2138,9 +2138,14 @@ void launch_conv(const DArgs& a, int32_t k, hipStream_t s) {
   }
 }
 
-// Whether the kernels that index in 32 bits take the call.
-bool conv_fits(const lbm_tensor5* src, const lbm_tensor5* out, int kpad) {
-  return tap_fits(src) && tap_fits(out) && (long long)out->c * kpad < (1ll << 30);
+// Whether the kernels that index in 32 bits take the call.  A 1x1x1 layer in
+// place, onto 33 to 64 channels off 32s, stays with the general kernel, which
+// has them all in one workgroup: the pointwise kernel's second column tile
+// would read what the first has written.
+bool conv_fits(const lbm_tensor5* src, const lbm_tensor5* out, int ksize) {
+  const int kpad = lbm_conv_kpad(ksize * ksize * ksize, src->c);
+  const bool in_place = ksize == 1 && src->ptr == out->ptr && out->c > 32 && src->c % 32 != 0;
+  return !in_place && tap_fits(src) && tap_fits(out) && (long long)out->c * kpad < (1ll << 30);
 }
 
 // How a weight gradient runs: its kernel and tile, its steps (kGeneral: voxels),
@@ -2374,7 +2379,7 @@ lbm_status lbm_conv3d_fwd(const lbm_tensor5* x, const uint16_t* w, const float* 
   const DArgs a{(const uint16_t*)x->ptr, geo_of(x), (unsigned)view_bytes(x), w, kpad,
                 (unsigned)((long long)y->c * kpad * 2), bias, (uint16_t*)y->ptr, geo_of(y), nullptr, 0, ksize, stride,
                 relu, 0, x->c};
-  launch_conv<0>(a, pick_conv<0>(a.gs, a.go, ksize, stride, conv_fits(x, y, kpad)), (hipStream_t)stream);
+  launch_conv<0>(a, pick_conv<0>(a.gs, a.go, ksize, stride, conv_fits(x, y, ksize)), (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
@@ -2389,17 +2394,16 @@ lbm_status lbm_conv3d_bwd_data(const lbm_tensor5* dy, const uint16_t* w_t, const
   const DArgs a{(const uint16_t*)dy->ptr, geo_of(dy), (unsigned)view_bytes(dy), w_t, kpad,
                 (unsigned)((long long)dx->c * kpad * 2), nullptr, (uint16_t*)dx->ptr, geo_of(dx),
                 act ? (const uint16_t*)act->ptr : nullptr, act ? act->ldc : 0, ksize, stride, 0, accumulate, dy->c};
-  launch_conv<1>(a, pick_conv<1>(a.gs, a.go, ksize, stride, conv_fits(dy, dx, kpad)), (hipStream_t)stream);
+  launch_conv<1>(a, pick_conv<1>(a.gs, a.go, ksize, stride, conv_fits(dy, dx, ksize)), (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
 int32_t lbm_conv3d_kernel(int32_t pass, const lbm_tensor5* x, const lbm_tensor5* y, int32_t ksize, int32_t stride) {
   if (!conv_ok(x, y, ksize, stride) || pass < 0 || pass > 2) return -1;
-  const int taps = ksize * ksize * ksize;
   if (pass == 0)
-    return pick_conv<0>(geo_of(x), geo_of(y), ksize, stride, conv_fits(x, y, lbm_conv_kpad(taps, x->c)));
+    return pick_conv<0>(geo_of(x), geo_of(y), ksize, stride, conv_fits(x, y, ksize));
   if (pass == 1)
-    return pick_conv<1>(geo_of(y), geo_of(x), ksize, stride, conv_fits(y, x, lbm_conv_kpad(taps, y->c)));
+    return pick_conv<1>(geo_of(y), geo_of(x), ksize, stride, conv_fits(y, x, ksize));
   const WPlan p = wgrad_plan(x, y, ksize, stride, true);
   switch (p.kind) {
     case WPlan::kRows: return p.bm == 32 ? LBM_WGRAD_ROWS32 : LBM_WGRAD_ROWS64;

@@ -87,3 +87,19 @@ def test_narrow_stride2_weight_gradient(dims, ci, co):
     gw = layer.gw.cpu().numpy()[:, :27 * ci].reshape(dw.shape)
     assert np.abs(gw - dw).max() <= 1e-5 * np.abs(dw).max()
     assert np.abs(layer.gb.cpu().numpy() - db).max() <= 1e-5 * np.abs(db).max()
+
+
+@pytest.mark.parametrize("c", [24, 32, 40, 56, 64])
+def test_pointwise_in_place(c):
+    from paper_1007_1388_amd import surrogate as S
+    x, w, b, _ = _operands(2, 9, 31, 33, c, c, 1, 1, 1200 + c)
+    layer = S.Conv(c, c, k=1)
+    layer.set_weights(w, b)
+    X, Y, DX = S.from_numpy(x), S.Act(2, 9, 31, 33, c), S.Act(2, 9, 31, 33, c)
+    layer.forward(X, Y)
+    assert S.lib().lbm_conv3d_bwd_data(X.ref, layer.wt.data_ptr(), DX.ref, None, 1, 1, 0, None) == 0
+    for run, out in ((lambda a: layer.forward(a, a), Y), (lambda a: S.lib().lbm_conv3d_bwd_data(
+            a.ref, layer.wt.data_ptr(), a.ref, None, 1, 1, 0, None), DX)):
+        a = S.from_numpy(x)
+        run(a)
+        assert np.array_equal(a.to_numpy(), out.to_numpy())
