@@ -2185,7 +2185,7 @@ int row_voxels(const Geo& g, int shortest) {
 //    1 128x64x64 32->32 129 us with 342, 76 with 90.)
 // A sum of n products one after the other is off by about sqrt(n / 2) * 2^-24, so
 // N also keeps the chains short (per_step products a step; V voxels, 32 a
-// product): with parts, which are added in FP64, to 24 + V / 3072 products; with
+// product): with parts, which are added in FP64, to 44 + V / 3200 products; with
 // atomics, which go on in FP32, chain and adds together to 48 + V / 1536.
 void wgrad_splits(WPlan& p, long long V, int per_step, long long values, long long slots, double step_us, bool parts) {
   const long long v32 = (V + 31) / 32, sum = p.steps * per_step;
@@ -2193,7 +2193,7 @@ void wgrad_splits(WPlan& p, long long V, int per_step, long long values, long lo
   long long n = (long long)std::sqrt(step_us * (double)p.steps / each);
   n = std::max<long long>(1, std::min(slots / p.tiles, n));
   if (parts)
-    n = std::max(n, sum / (24 + v32 / 96));
+    n = std::max(n, sum / (44 + v32 / 100));
   else if (sum / n + n > 48 + v32 / 48)
     n = std::max(n, std::min(v32 / 48, 2048 / p.tiles));
   n = std::min(n, p.steps);

@@ -483,10 +483,18 @@ def warmstart_study(train=512, test=64, epochs=30, batch=4, lr=1e-3, concurrent=
 def conv_layers(n=8, D=128, H=64, W=64, reps=5):
     """Per-layer times of the three convolution kernels at the given shape
     (HIP events on the current stream): TFLOP/s (2 * voxels * taps * Cin *
-    Cout per kernel)."""
+    Cout per kernel).  As training runs them: activations of a random input,
+    random output gradients, input gradients masked by ReLU' (stride 2: added to
+    what is there), weight gradients with the bias and their ordered sums."""
     import torch
     from paper_1007_1388_amd import surrogate as S
     net = S.UNet(n, D, H, W, seed=1)
+    g = torch.Generator(device="cuda").manual_seed(1)
+
+    def fill(act, scale):
+        v = scale * torch.randn(act.buf.shape, generator=g, device="cuda")
+        act.buf.copy_(v.bfloat16().view(torch.int16))
+    fill(net.x, 1.0)
     net.forward()
     torch.cuda.synchronize()
     st = torch.cuda.current_stream()
@@ -504,19 +512,19 @@ def conv_layers(n=8, D=128, H=64, W=64, reps=5):
         return e0.elapsed_time(e1) / reps
 
     for name, l, x, y in net.io():
-        dx = S.Act(x.n, x.d, x.h, x.w, x.c)
+        dx, dy = S.Act(x.n, x.d, x.h, x.w, x.c), S.Act(y.n, y.d, y.h, y.w, y.c)
+        fill(dy, 1e-3)
         fl = l.flops(y.n * y.d * y.h * y.w)
         t_f = timed(lambda: l.forward(x, y))
-        t_d = timed(lambda: S._ck(L.lbm_conv3d_bwd_data(y.ref, l.wt.data_ptr(), dx.ref, None, l.k, l.stride, 0,
-                                                          None), "lbm_conv3d_bwd_data"))
-        t_w = timed(lambda: S._ck(L.lbm_conv3d_bwd_weight(x.ref, y.ref, l.gw.data_ptr(), l.gb.data_ptr(), l.k,
-                                                            l.stride, None), "lbm_conv3d_bwd_weight"))
+        t_d = timed(lambda: S._ck(L.lbm_conv3d_bwd_data(dy.ref, l.wt.data_ptr(), dx.ref, x.ref, l.k, l.stride,
+                                                          1 if l.stride == 2 else 0, None), "lbm_conv3d_bwd_data"))
+        t_w = timed(lambda: l.backward(x, dy, None))
         r = dict(study="conv", layer=name, cin=l.cin, cout=l.cout, k=l.k, stride=l.stride, out=(y.d, y.h, y.w),
                  gflop=fl / 1e9, fwd_ms=t_f, bwd_data_ms=t_d, bwd_weight_ms=t_w, fwd_tflops=fl / t_f / 1e9,
                  bwd_data_tflops=fl / t_d / 1e9, bwd_weight_tflops=fl / t_w / 1e9)
         rows.append(r)
         print(json.dumps(r), flush=True)
-        del dx
+        del dx, dy
     tot = sum(r["gflop"] for r in rows)
     for kind in ("fwd", "bwd_data", "bwd_weight"):
         t = sum(r[kind + "_ms"] for r in rows)
