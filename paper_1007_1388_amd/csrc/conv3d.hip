@@ -583,12 +583,11 @@ __device__ __forceinline__ void load_barrier() {
 // cycle meet 8 different bank groups.
 // MODE 1 (input gradient) runs the mirrored taps on the transposed weights.
 // Channels in 8s: the part of a chunk past C loads zeros (TAIL).
-// Measured on gfx950, forward / input gradient, against the kernels this
-// replaced (batch 8): 128x64x64 32->32 346 / 465 -> 237 / 256 us, 64->32 540 /
-// 1033 -> 417 / 489; 64x32x32 128->64 238 / 378 -> 187 / 222 (1240 TFLOP/s; a
-// large library matrix product reaches 1280-1380 here); input gradients of
-// 32x16x16 256->128 157 -> 95 and of 16x8x8 256->256 90 -> 52 (half of each
-// tile is padding).  The full-resolution layers are held by HBM (0.54 GB
+// Measured on gfx950 at batch 8, us, forward / input gradient with its mask,
+// against the halo-staged and tap-major kernels before: 128x64x64 32->32 370 / 477
+// -> 236 / 272, 64->32 555 / 1047 -> 407 / 522; 64x32x32 64->64 146 / 163 -> 102 /
+// 107, 128->64 forward 235 -> 192 (1210 TFLOP/s; a large library matrix product
+// reaches 1280-1380 here).  The full-resolution layers are held by HBM (0.54 GB
 // forward, 0.8 with the mask) beside the MFMAs, the rest by the matrix cores.
 template <int MODE, int R, bool TAIL>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_conv_rows(DArgs a) {
@@ -725,9 +724,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // Bound by LDS reads (four for four MFMAs per chunk with R = 2) at full chips
 // and by the chain of nine weight loads per plane at small ones.  Measured on
 // gfx950, us, against the tap-major kernel: batch 1 16x8x8 256->256 67.6 ->
-// 18.5, 32x16x16 128->128 41 -> 15.8 and 256->128 85 -> 24.5; batch 8 88 -> 52,
-// 88 -> 56 and 160 -> 128 (904 TFLOP/s); input gradients alike (89 -> 59, 88 ->
-// 65, 157 -> 120; 64x32x32 128->64 378 -> 234).  MODE 1 runs mirrored taps.
+// 19.0, 32x16x16 128->128 41 -> 16.2 and 256->128 85 -> 26; batch 8 87 -> 56,
+// 85 -> 64 and 155 -> 140 (831 TFLOP/s); input gradients alike (89 -> 58, 91 ->
+// 65, 165 -> 130; 64x32x32 128->64 380 -> 251).  MODE 1 runs mirrored taps.
 template <int MODE, int NC, int WF, int R, int WN>
 __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
   constexpr int FN = 2, BN = 16 * FN * WN;
@@ -858,8 +857,9 @@ __global__ void __launch_bounds__(256 * WN) k_conv_plane(DArgs a) {
 // writes two neighbouring voxels.  Cells, weight rows and stores as in
 // k_conv_rows; the order of the sums is the tap-major kernel's (kd, kh, kw,
 // chunk), bit for bit.  Bound by HBM (the mask and the accumulated gradient).
-// Measured on gfx950, batch 8: 128x64x64 32 <- 64 channels 478 us before, 186
-// now (312 TFLOP/s); batch 4, 100x60x52 32 <- 64: 125 before, 63 now.
+// Measured on gfx950, with the mask: batch 8 128x64x64 32 <- 64 channels 479 us
+// before, 178 now, adding to a gradient that is there 665 and 275; batch 4
+// 100x60x52 32 <- 64 125 before, 63 now.
 template <int NC, int R>
 __global__ void __launch_bounds__(256) k_conv_up(DArgs a) {
   constexpr int TH = 4 * R, HC = 17, HR = TH + 1, CELLS = 2 * HR * HC;
@@ -979,7 +979,7 @@ __global__ void __launch_bounds__(256) k_conv_up(DArgs a) {
 // 32 columns; the operands are direct 16-byte loads, whole lines of the
 // channels-last rows, all of a chunk's issued before its MFMAs.  A wave's
 // weights of the chunk come from L1.  No LDS: no value is used twice.  Bound by
-// HBM.  Measured on gfx950 at 8 x 128x64x64: 32->8 forward 127 -> 70 us, its input
+// HBM.  Measured on gfx950 at 8 x 128x64x64: 32->8 forward 122 -> 69 us, its input
 // gradient 233 -> 104 (against the tap-major and the general kernel).
 __global__ void __launch_bounds__(256) k_conv_point(DArgs a) {
   constexpr unsigned OOB = 0x80000000u;
@@ -1029,7 +1029,7 @@ __global__ void __launch_bounds__(256) k_conv_point(DArgs a) {
 // output channels: it brings the kPl + 2 source planes' halos into LDS (16-byte
 // cells, LDS-direct loads) once; wave v takes rows 4 v .. 4 v + 3 of every plane.
 // A voxel operand is one LDS read per lane, at the lane's own tap.  Bound by the
-// stores of its 32 channels.  Measured on gfx950 at 8 x 128x64x64: 346 -> 110 us
+// stores of its 32 channels.  Measured on gfx950 at 8 x 128x64x64: 366 -> 108 us
 // against the general kernel, which gathered every tap from memory.
 __global__ void __launch_bounds__(256) k_conv_fwd_c8(DArgs a) {
   constexpr int kPl = 4, HC = 18, HR = 18, CELLS = (kPl + 2) * HR * HC;
@@ -1190,9 +1190,9 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 //    -> 49 us).
 // Channels in 8s: the part of a tile past Cin or Cout loads zeros.
 // Measured on gfx950 at batch 8, us with the sum and the bias, against the
-// tap-by-tap kernel with atomics: 128x64x64 32->32 349 -> 235; 64x32x32 64->64
-// 190 -> 114; 32x16x16 256->128 182 -> 119; 16x8x8 256->256 69 -> 44; stride 2
-// 128x64x64 32->64 141 -> 126; batch 1 128x64x64 32->32 136 -> 49.  Bound by HBM at
+// tap-by-tap kernel with atomics: 128x64x64 32->32 349 -> 242, 64->32 590 -> 495;
+// 64x32x32 64->64 190 -> 114; 32x16x16 256->128 182 -> 121; 16x8x8 256->256 69 ->
+// 45; stride 2 128x64x64 32->64 141 -> 126; batch 1 128x64x64 32->32 136 -> 50.  Bound by HBM at
 // full resolution, by LDS reads and MFMAs otherwise.
 template <int S, int BM, int WP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2 || WP <= 8 ? 2 : (BM == 64 && WP == 32 ? 3 : 4)))) k_conv_wgrad_rows(WArgs a) {
@@ -2185,15 +2185,17 @@ int row_voxels(const Geo& g, int shortest) {
 //    1 128x64x64 32->32 129 us with 342, 76 with 90.)
 // A sum of n products one after the other is off by about sqrt(n / 2) * 2^-24, so
 // N also keeps the chains short (per_step products a step; V voxels, 32 a
-// product): with parts, which are added in FP64, to 44 + V / 3200 products; with
-// atomics, which go on in FP32, chain and adds together to 48 + V / 1536.
+// product): with parts, which are added in FP64, to 44 + V / 3200 products, as far
+// as the parts stay under 128 MB, which the memory-side cache holds (4 x 42x37x19
+// 128->256 269 us with 233 MB of them); with atomics, which go on in FP32, chain and
+// adds together to 48 + V / 1536.
 void wgrad_splits(WPlan& p, long long V, int per_step, long long values, long long slots, double step_us, bool parts) {
   const long long v32 = (V + 31) / 32, sum = p.steps * per_step;
   const double each = (double)(p.tiles * values) * (parts ? 2e-6 : 1.0 / 95000.0) + (parts ? 0.0 : 0.16);
   long long n = (long long)std::sqrt(step_us * (double)p.steps / each);
   n = std::max<long long>(1, std::min(slots / p.tiles, n));
   if (parts)
-    n = std::max(n, sum / (44 + v32 / 100));
+    n = std::max(n, std::min(v32 / (44 + v32 / 100), (32ll << 20) / (p.tiles * values)));
   else if (sum / n + n > 48 + v32 / 48)
     n = std::max(n, std::min(v32 / 48, 2048 / p.tiles));
   n = std::min(n, p.steps);
@@ -2261,9 +2263,10 @@ WPlan wgrad_plan(const lbm_tensor5* x, const lbm_tensor5* dy, int ksize, int str
     p.nco = (gy.c + BM - 1) / BM;
     p.nci = (kpad + 63) / 64;
     p.tiles = (long long)p.nco * p.nci;
-    // split the voxel range so that the grid holds about 2048 workgroups
-    p.per_wg = (V + std::max<long long>(1, 2048 / p.tiles) - 1) / std::max<long long>(1, 2048 / p.tiles);
-    p.per_wg = (p.per_wg + BK - 1) / BK * BK;
+    // split the voxel range so that the grid holds about 2048 workgroups, 1024
+    // where their sums are stored and read again
+    const long long n = std::max<long long>(1, (parts ? 1024 : 2048) / p.tiles);
+    p.per_wg = ((V + n - 1) / n + BK - 1) / BK * BK;
     p.splits = (V + p.per_wg - 1) / p.per_wg;
     p.splits_b = (V + kBiasVoxels - 1) / kBiasVoxels;
     return p;

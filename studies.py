@@ -480,7 +480,7 @@ def warmstart_study(train=512, test=64, epochs=30, batch=4, lr=1e-3, concurrent=
 
 
 # ------------------------------------------------------------ convolutions
-def conv_layers(n=8, D=128, H=64, W=64, reps=5):
+def conv_layers(n=8, D=128, H=64, W=64, reps=20):
     """Per-layer times of the three convolution kernels at the given shape
     (HIP events on the current stream): TFLOP/s (2 * voxels * taps * Cin *
     Cout per kernel).  As training runs them: activations of a random input,
