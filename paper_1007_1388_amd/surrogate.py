@@ -142,20 +142,25 @@ class Scratch:
         return (Scratch, ())
 
     def get(self, nbytes, stream):
-        """A buffer of at least nbytes for work on `stream` (a raw handle, None: the
-        null stream), or None while that stream is being captured and the buffer
-        at hand is too small (a capture allocates nothing)."""
+        """A buffer of at least nbytes for work on `stream` (a raw handle, None: the null stream), or None while that
+        stream is being captured: a graph would keep the address, and may be replayed when the buffer is gone or in
+        use on another stream."""
         import torch
         key = (torch.cuda.current_device(), int(stream or 0))
-        buf = self._bufs.get(key)
-        if buf is None or buf.numel() < nbytes:
-            on = torch.cuda.ExternalStream(key[1]) if key[1] else torch.cuda.default_stream()
+        on = None
+        if key[1]:   # (the null stream cannot be captured)
+            on = torch.cuda.current_stream()
+            if on.cuda_stream != key[1]:
+                on = torch.cuda.ExternalStream(key[1])
             with torch.cuda.stream(on):
                 if torch.cuda.is_current_stream_capturing():
                     return None
-                self._bufs.pop(key, None)
-                while len(self._bufs) >= self.STREAMS:
-                    self._bufs.pop(next(iter(self._bufs)))
+        buf = self._bufs.get(key)
+        if buf is None or buf.numel() < nbytes:
+            self._bufs.pop(key, None)
+            while len(self._bufs) >= self.STREAMS:
+                self._bufs.pop(next(iter(self._bufs)))
+            with torch.cuda.stream(on or torch.cuda.default_stream()):
                 buf = self._bufs[key] = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         return buf
 
@@ -221,8 +226,8 @@ class Conv:
     def backward(self, x, dy, dx, x_act=True, accumulate=False, stream=None):
         """Accumulate weight grads; write (or add) dx masked by ReLU'(x) when x
         came out of a ReLU layer (x_act).  The weight grads' sums have a fixed
-        order, so that a repeated step repeats bit for bit; only in a capture that
-        finds no scratch memory from an earlier call are they atomics' sums."""
+        order, so that a repeated step repeats bit for bit; only in a capture are
+        they atomics' sums, which need no scratch memory."""
         L = lib()
         need = L.lbm_conv3d_bwd_weight_scratch(x.ref, dy.ref, self.k, self.stride)
         with self.scratch.lock:

@@ -92,7 +92,7 @@ def test_scratch_is_checked_and_a_capture_allocates_nothing():
         assert L.lbm_conv3d_bwd_weight_ordered(*args, ptr, size, None) == lbm.LBM_EINVAL
     assert L.lbm_conv3d_bwd_weight_scratch(x.ref, dy.ref, 3, 2) == -1
     dw, db = conv.conv3d_bwd_weight(x.to_numpy(), dy.to_numpy(), 3, 1)
-    for warm in (False, True):   # a capture without and with scratch memory from an earlier call
+    for warm in (False, True):   # a graph holds no scratch memory, be it at hand or not
         layer = S.Conv(32, 32)
         stream = torch.cuda.Stream()
         if warm:
@@ -101,7 +101,10 @@ def test_scratch_is_checked_and_a_capture_allocates_nothing():
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=stream):
             layer.backward(x, dy, None, stream=stream.cuda_stream)
-        assert bool(layer.scratch._bufs) == warm
+        bufs = list(layer.scratch._bufs.values())
+        assert len(bufs) == warm
+        for buf in bufs:
+            buf.fill_(0x55)
         for _ in range(3):
             layer.zero_grad()
             torch.cuda.synchronize()
@@ -109,3 +112,28 @@ def test_scratch_is_checked_and_a_capture_allocates_nothing():
             torch.cuda.synchronize()
             assert np.abs(layer.gw.cpu().numpy()[:, :864].reshape(dw.shape) - dw).max() <= 1e-5 * np.abs(dw).max()
             assert np.abs(layer.gb.cpu().numpy() - db).max() <= 1e-5 * np.abs(db).max()
+        assert all(bool((buf == 0x55).all()) for buf in bufs)
+
+
+def test_scratch_of_streams_and_copies():
+    """One buffer per stream, at most four kept, none in a copy; gradients on several streams agree bit for bit."""
+    import copy
+    import torch
+    from paper_1007_1388_amd import surrogate as S
+    rng = np.random.default_rng(6)
+    x = S.from_numpy(rng.standard_normal((1, 12, 16, 32, 32)))
+    dy = S.from_numpy(rng.standard_normal((1, 12, 16, 32, 32)))
+    layer = S.Conv(32, 32)
+    layer.backward(x, dy, None)
+    torch.cuda.synchronize()
+    want = layer.gw.clone()
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    for st in streams:
+        layer.zero_grad()
+        torch.cuda.synchronize()
+        layer.backward(x, dy, None, stream=st.cuda_stream)
+        st.synchronize()
+        assert torch.equal(layer.gw, want)
+    assert len(layer.scratch._bufs) == S.Scratch.STREAMS
+    assert len({b.data_ptr() for b in layer.scratch._bufs.values()}) == S.Scratch.STREAMS
+    assert not copy.deepcopy(layer.scratch)._bufs
