@@ -11,6 +11,7 @@
 //   stride-2 bwd-data      k_conv_up (all parities of a tile in one workgroup)
 //   1x1x1                  k_conv_point, k_conv_wgrad_point
 //   3x3x3 bwd-weight       k_conv_wgrad_rows
+//   parts of bwd-weight    k_wgrad_sum: added in a fixed order
 //   forward of stride 2 and what those leave, channels a multiple of 32: k_conv_tap
 //   the rest               k_conv_gemm, k_conv_wgrad: a 128 x BN tile per workgroup
 //                          (4 waves of 32 rows), operands staged in LDS with K fastest
@@ -1166,12 +1167,12 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 // dy tile once).  A workgroup owns one kernel plane kd, 32 input channels and
 // BM output channels, i.e. a BM x (9 taps x 32) block of dw, and walks steps of
 // RR rows of 32 voxels of dy (a row: 32 along w, or WP along w of 32 / WP planes,
-// whichever pads the volume least).  Per step it brings the dy
-// tile and the x halo of plane d S + kd - 1, the sources of all nine (kh, kw)
-// taps, into LDS by 16-byte buffer loads that write LDS directly; both MFMA
-// operands (voxels as K) are then transposing reads (ds_read_b64_tr_b16: a
-// 16-lane group gives the addresses of four rows of four 16-bit values; lane l
-// receives column l%16 of that 4 x 16 block).
+// whichever pads the volume least).  Per step it brings the dy tile and the x
+// halo of plane d S + kd - 1, the sources of all nine (kh, kw) taps, into LDS by
+// 16-byte buffer loads that write LDS directly; both MFMA operands (voxels as K)
+// are then transposing reads (ds_read_b64_tr_b16: a 16-lane group gives the
+// addresses of four rows of four 16-bit values; lane l receives column l%16 of
+// that 4 x 16 block).
 //  * The dy rows stay in registers, and an x row read once per column shift kw
 //    serves the three taps kh whose dy row it meets: 26 reads for 72 MFMAs of
 //    a wave (tap by tap it takes 44; 40 for 36 with 32 output channels, whose
@@ -1192,10 +1193,14 @@ __device__ __forceinline__ bf16x8 tr_load8(const uint16_t* p, int off_lo, int of
 // Measured on gfx950 at batch 8, us with the sum and the bias, against the
 // tap-by-tap kernel with atomics: 128x64x64 32->32 349 -> 242, 64->32 590 -> 495;
 // 64x32x32 64->64 190 -> 114; 32x16x16 256->128 182 -> 121; 16x8x8 256->256 69 ->
-// 45; stride 2 128x64x64 32->64 141 -> 126; batch 1 128x64x64 32->32 136 -> 50.  Bound by HBM at
-// full resolution, by LDS reads and MFMAs otherwise.
+// 45; stride 2 128x64x64 32->64 141 -> 126; batch 1 128x64x64 32->32 136 -> 50.
+// Bound by HBM at full resolution, by LDS reads and MFMAs otherwise.
+// (Waves per SIMD: four fit without spills but where the halo or its addresses
+// take more registers; asked for four, 64 columns on rows of 32 spill.)
+constexpr int wgrad_waves(int S, int BM, int WP) { return S == 2 || WP <= 8 ? 2 : (BM == 64 && WP == 32 ? 3 : 4); }
 template <int S, int BM, int WP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == 2 || WP <= 8 ? 2 : (BM == 64 && WP == 32 ? 3 : 4)))) k_conv_wgrad_rows(WArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wgrad_waves(S, BM, WP))))
+k_conv_wgrad_rows(WArgs a) {
   constexpr int KS = BM == 32 ? 2 : 1;             // waves that share a dw tile, each with RW of a step's rows
   constexpr int RW = S == 2 && BM == 32 ? 2 : 4;   // (eight rows of stride 2 would leave one workgroup per compute unit)
   constexpr int RR = RW * KS;
